@@ -36,7 +36,7 @@ namespace lcd {
 namespace {
 
 constexpr double kMargin = 0x1p-40;   // improvement threshold on the log-fitness gain
-constexpr double kFilter = 1e-9;      // certified pre-test margin (see improves_add)
+constexpr double kCert = 1e-10;       // certified comparisons' margin (see improves_add)
 constexpr uint32_t kDMask = (1u << 27) - 1;   // d (weighted degrees stay below 2^27)
 constexpr uint32_t kMember = 1u << 31;
 constexpr uint32_t kLive = 1u << 30;
@@ -213,7 +213,7 @@ struct St {
     int32_t count;     // dense entries in use
     int32_t nmem;      // members
     int64_t K, V;      // k_in and volume of the community
-    double LK, LV;     // L(K), L(V) when positive
+    double rK2, rV;    // 2 / K and 1 / V when positive, for the certified comparisons
     double alpha;
     double pr;         // rank and id of the entry added last in this call
     int32_t pu;
@@ -431,79 +431,161 @@ __device__ void row_update(const Tab &t, St &st, const Ctx &c, int32_t n, int la
 }
 
 // Full decision "f(Kp, Vp) > f(K, V)" in the log domain (K, V > 0 here).
-__device__ __forceinline__ bool decide(const St &st, int64_t Kp, int64_t Vp) {
-    if (Kp == 0)
-        return false;
-    if (st.K == 0)
-        return true;
-    const double a = ilog((uint64_t)Kp) - st.LK;
-    const double b = ilog((uint64_t)Vp) - st.LV;
-    const double cc = st.alpha * b;
+// Four logs of eleven dependent steps and a division each: reached only by
+// the few entries that the certified comparisons below leave open.
+__device__ __forceinline__ bool decide(int64_t K, int64_t V, int64_t Kp, int64_t Vp, double alpha) {
+    const double a = ilog((uint64_t)Kp) - ilog((uint64_t)K);
+    const double b = ilog((uint64_t)Vp) - ilog((uint64_t)V);
+    const double cc = alpha * b;
     const double t = a - cc;
     return t > kMargin;
 }
 
-// Would adding a non-member with (d, k) raise f?  The pre-test uses
-// ln(1+x) <= x and ln(1+y) >= y/(1+y):  the exact gain is at most
-//   2d/K - alpha k/(V+k),
-// evaluated multiplied out by K (V+k) (every product of integers below 2^53
-// is exact); when that bound is below -1e-9 the exact gain, and therefore
-// the computed one (error < 1e-11 for alpha <= 1000), is far below the
-// threshold, so the full test would reject as well.
+// Would adding a non-member with (d, k) raise f?  The exact gain is
+//   T = ln(1 + x) - alpha ln(1 + y),  x = 2d / K,  y = k / V,
+// and for z > 0   2z / (2 + z) < ln(1 + z) < z (6 + z) / (6 + 4z).
+// A bound on T that clears zero by 1e-10 settles the decision: the computed
+// gain differs from T by less than 1e-11 (alpha <= 1000), the threshold is
+// 2^-40, and the bounds, multiplied out by their denominators, carry a
+// relative rounding error below 1e-14 (x, y from one reciprocal per state;
+// x <= 1024 keeps every term within 1e4 of the denominators near a tie).
+// The bounds are x^2 / 12 apart, so for communities of more than a few
+// members nearly every entry is settled by about twenty multiplications
+// instead of two logs with a division each.  Bound by instruction issue on
+// LDS tables and by latency on global ones; with the VALU reductions below
+// the 1,000-node sweep's workgroup tier went from 6.0 to 4.4 ms, tier 2 of a
+// 1,000,000-node share from 209 to 188 ms.
 __device__ __forceinline__ bool improves_add(const St &st, int32_t d, int32_t k) {
     if (st.K == 0)
         return true;
-    const int64_t Kp = st.K + 2 * (int64_t)d;
-    const int64_t Vp = st.V + k;
-    const double X = (double)(2 * (int64_t)d) * (double)Vp - st.alpha * ((double)k * (double)st.K);
-    if (X < -kFilter * ((double)st.K * (double)Vp))
+    const double x = (double)d * st.rK2;
+    const double y = (double)k * st.rV;
+    const double ay = st.alpha * y;
+    const double p = 2.0 + x, q = __builtin_fma(4.0, y, 6.0);
+    const double n1 = __builtin_fma(2.0 * x, q, -(ay * (6.0 + y)) * p);
+    const double r = 2.0 + y, u = __builtin_fma(4.0, x, 6.0);
+    const double n2 = __builtin_fma(x * (6.0 + x), r, -2.0 * ay * u);
+    const bool small = x <= 1024.0;
+    if (small && n1 > kCert * (p * q))
+        return true;
+    if (small && n2 < -kCert * (r * u))
         return false;
-    return decide(st, Kp, Vp);
+    return decide(st.K, st.V, st.K + 2 * (int64_t)d, st.V + k, st.alpha);
 }
 
-// Would removing a member with internal weight d and degree k raise f?
-// Bound: ln(1-x) <= -x and -ln(1-y) <= y/(1-y) give a gain of at most
-//   -2d/K + alpha k/(V-k).
+// Would removing a member with internal weight d and degree k raise f?  The
+// same with T = alpha lny - lnx, lnx = -ln(1 - x), and for 0 < z < 1
+//   2z / (2 - z) <= -ln(1 - z) <= z (6 - 5z) / ((1 - z) (6 - 2z)).
+// Only x, y <= 1/2 are settled this way (1 - z would lose digits near 1).
 __device__ __forceinline__ bool improves_remove(const St &st, int32_t d, int32_t k) {
     const int64_t Kp = st.K - 2 * (int64_t)d;
     if (Kp <= 0)
         return false;
-    const int64_t Vp = st.V - k;
-    const double X = -(double)(2 * (int64_t)d) * (double)Vp + st.alpha * ((double)k * (double)st.K);
-    if (X < -kFilter * ((double)st.K * (double)Vp))
+    const double x = (double)d * st.rK2;
+    const double y = (double)k * st.rV;
+    const double ay = st.alpha * y;
+    const double p = 2.0 - y, q = (1.0 - x) * __builtin_fma(-2.0, x, 6.0);
+    const double n1 = __builtin_fma(2.0 * ay, q, -(x * __builtin_fma(-5.0, x, 6.0)) * p);
+    const double r = 2.0 - x, u = (1.0 - y) * __builtin_fma(-2.0, y, 6.0);
+    const double n2 = __builtin_fma(ay * __builtin_fma(-5.0, y, 6.0), r, -2.0 * x * u);
+    const bool small = x <= 0.5 && y <= 0.5;
+    if (small && n1 > kCert * (p * q))
+        return true;
+    if (small && n2 < -kCert * (r * u))
         return false;
-    return decide(st, Kp, Vp);
+    return decide(st.K, st.V, Kp, st.V - k, st.alpha);
 }
 
-__device__ __forceinline__ void set_logs(St &st) {
-    st.LK = st.K > 0 ? ilog((uint64_t)st.K) : 0.0;
-    st.LV = st.V > 0 ? ilog((uint64_t)st.V) : 0.0;
+// The reciprocals of the state, after K or V changed.
+__device__ __forceinline__ void set_rates(St &st) {
+    st.rK2 = st.K > 0 ? 2.0 / (double)st.K : 0.0;
+    st.rV = st.V > 0 ? 1.0 / (double)st.V : 0.0;
 }
 
+// Lane exchanges inside the VALU: lane i reads lane i - n of its row of 16
+// (row_shr) or the last lane of the rows before (row_bcast); a lane with no
+// source keeps its own value, so min and max need no neutral element.  Six
+// such steps leave the wave's result in lane 63.  A shuffle through LDS costs
+// an LDS round trip per step instead, and the argmax of (rank, id, index)
+// took four of them in each of six steps.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_from(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_from(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = dpp_from<CTRL>((uint32_t)b);
+    const uint32_t hi = dpp_from<CTRL>((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+constexpr int kShr1 = 0x111, kShr2 = 0x112, kShr4 = 0x114, kShr8 = 0x118, kBcast15 = 0x142, kBcast31 = 0x143;
+
+__device__ __forceinline__ double read_lane(double v, int l) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_from<kShr1>(v));
+    v = fmax(v, dpp_from<kShr2>(v));
+    v = fmax(v, dpp_from<kShr4>(v));
+    v = fmax(v, dpp_from<kShr8>(v));
+    v = fmax(v, dpp_from<kBcast15>(v));
+    v = fmax(v, dpp_from<kBcast31>(v));
+    return read_lane(v, 63);
+}
+
+__device__ __forceinline__ int32_t wave_min(int32_t x) {
+    uint32_t v = (uint32_t)x ^ 0x80000000u;   // unsigned order
+    v = min(v, dpp_from<kShr1>(v));
+    v = min(v, dpp_from<kShr2>(v));
+    v = min(v, dpp_from<kShr4>(v));
+    v = min(v, dpp_from<kShr8>(v));
+    v = min(v, dpp_from<kBcast15>(v));
+    v = min(v, dpp_from<kBcast31>(v));
+    return (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)v, 63) ^ 0x80000000u);
+}
+
+// The lane that holds the entry popping first among (r, u) (i < 0: no entry;
+// -1 when no lane has one): the highest rank, and among equal ranks the
+// smallest id.  Called by all 64 lanes; the result is wave-uniform.
+__device__ __forceinline__ int wave_first(double r, int32_t u, int32_t i) {
+    const double m = wave_max(i >= 0 ? r : -__builtin_huge_val());
+    uint64_t at = __ballot(i >= 0 && r == m);
+    if (at == 0)
+        return -1;
+    if (at & (at - 1)) {
+        const int32_t lo = wave_min(i >= 0 && r == m ? u : INT32_MAX);
+        at = __ballot(i >= 0 && r == m && u == lo);
+    }
+    return (int)__builtin_ctzll(at);
+}
+
+// (r, u, i) of the wave's first entry in every lane; i = -1 if there is none.
 __device__ __forceinline__ void wave_argmax(double &r, int32_t &u, int32_t &i) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double r2 = __shfl_xor(r, off);
-        const int32_t u2 = __shfl_xor(u, off);
-        const int32_t i2 = __shfl_xor(i, off);
-        if (before(r2, u2, r, u)) {
-            r = r2;
-            u = u2;
-            i = i2;
-        }
+    const int l = wave_first(r, u, i);
+    if (l < 0) {
+        r = -__builtin_huge_val();
+        u = INT32_MAX;
+        i = -1;
+        return;
     }
+    r = read_lane(r, l);
+    u = __builtin_amdgcn_readlane(u, l);
+    i = __builtin_amdgcn_readlane(i, l);
 }
 
+// The wave's smallest u with its i (u = INT32_MAX, i = -1: none).
 __device__ __forceinline__ void wave_argmin(int32_t &u, int32_t &i) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const int32_t u2 = __shfl_xor(u, off);
-        const int32_t i2 = __shfl_xor(i, off);
-        if (u2 < u) {
-            u = u2;
-            i = i2;
-        }
-    }
+    const int32_t lo = wave_min(u);
+    const uint64_t at = __ballot(u == lo);
+    i = __builtin_amdgcn_readlane(i, (int)__builtin_ctzll(at));
+    u = lo;
 }
 
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
@@ -586,7 +668,7 @@ __device__ int64_t grow(const Tab &t, St &st, const Ctx &c, uint32_t k_prune, in
         moves += 1;
         st.pr = br;
         st.pu = bu;
-        set_logs(st);
+        set_rates(st);
         wsync<GLOBAL>();
         row_update<GLOBAL, ROW_ADD>(t, st, c, bu, lane);
         if (st.ovf)
@@ -636,7 +718,7 @@ __device__ int64_t grow(const Tab &t, St &st, const Ctx &c, uint32_t k_prune, in
             st.nmem -= 1;
             st.M += 1;
             moves += 1;
-            set_logs(st);
+            set_rates(st);
             wsync<GLOBAL>();
             row_update<GLOBAL, ROW_REMOVE>(t, st, c, cu, lane);
             removed = true;
@@ -811,7 +893,7 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
         st.nmem = 0;
         st.K = 0;
         st.V = 0;
-        st.LK = st.LV = 0.0;
+        st.rK2 = st.rV = 0.0;
         st.alpha = 0.0;
         st.pr = 0.0;
         st.pu = 0;
@@ -903,7 +985,7 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
                 st.alpha = A.alpha_set[set];
             else
                 st.alpha = A.scales[s];
-            set_logs(st);
+            set_rates(st);
             st.Gl = st.Rl = 0;
             st.Gu = 0;
             st.M = 0;
@@ -1312,9 +1394,7 @@ __device__ __forceinline__ void team_pick_max(TeamSh &sh, const TeamId &id, cons
 
 // Workgroup minimum of v (every thread gets it).
 __device__ __forceinline__ int32_t team_min_i32(TeamSh &sh, const TeamId &id, int32_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        v = min(v, __shfl_xor(v, off));
+    v = wave_min(v);
     if (id.lane == 0)
         sh.u[id.wid] = v;
     __syncthreads();
@@ -1408,7 +1488,7 @@ __device__ bool removal_scan(const Tab &t, TeamSh &sh, St &st, const Ctx &c, con
             st.nmem -= 1;
             st.M += 1;
             moves += 1;
-            set_logs(st);
+            set_rates(st);
             team_row<GLOBAL, ROW_REMOVE>(t, sh, st, c, id, cu);
             removed = true;
             cursor = cu;
@@ -1487,11 +1567,8 @@ __device__ __forceinline__ int32_t bucket_at(const TeamSh &sh, int32_t lo, int32
 __device__ __forceinline__ void team_max_range(TeamSh &sh, const TeamId &id, double &r, int32_t &u, int32_t &i,
                                                double &lo, double &hi) {
     wave_argmax(r, u, i);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        lo = fmin(lo, __shfl_xor(lo, off));
-        hi = fmax(hi, __shfl_xor(hi, off));
-    }
+    lo = -wave_max(-lo);
+    hi = wave_max(hi);
     if (id.lane == 0) {
         sh.r[id.wid] = r;
         sh.u[id.wid] = u;
@@ -1525,17 +1602,12 @@ __device__ __forceinline__ void team_window(TeamSh &sh, const TeamId &id, double
                                             int32_t &mu) {
     wave_argmax(fr, fu, fi);
     wave_argmax(wr, wu, wi);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double r2 = __shfl_xor(mr, off);
-        const int32_t u2 = __shfl_xor(mu, off);
-        const int32_t i2 = __shfl_xor(mi, off);
-        if (i2 >= 0 && (mi < 0 || pops_after(r2, u2, mr, mu))) {
-            mr = r2;
-            mu = u2;
-            mi = i2;
-        }
-    }
+    // the entry that pops last is the first one in the reversed order
+    mr = -mr;
+    mu = -1 - mu;
+    wave_argmax(mr, mu, mi);
+    mr = -mr;
+    mu = -1 - mu;
     if (id.lane == 0) {
         sh.r[id.wid] = fr;
         sh.u[id.wid] = fu;
@@ -1930,7 +2002,7 @@ __device__ bool bq_additions(const Tab &t, TeamSh &sh, St &st, const Ctx &c, con
         moves += 1;
         st.pr = br;
         st.pu = bu;
-        set_logs(st);
+        set_rates(st);
         team_row<GLOBAL, ROW_ADD>(t, sh, st, c, id, bu, true);
         if (st.ovf)
             return false;
@@ -2071,7 +2143,7 @@ __device__ bool removal_members(const Tab &t, TeamSh &sh, St &st, const Ctx &c, 
             st.nmem -= 1;
             st.M += 1;
             moves += 1;
-            set_logs(st);
+            set_rates(st);
             team_row<GLOBAL, ROW_REMOVE>(t, sh, st, c, id, cu);
             removed = true;
             cursor = cu;
@@ -2180,7 +2252,7 @@ __device__ int64_t team_grow(const Tab &t, TeamSh &sh, St &st, const Ctx &c, con
         moves += 1;
         st.pr = br;
         st.pu = bu;
-        set_logs(st);
+        set_rates(st);
         team_row<GLOBAL, ROW_ADD>(t, sh, st, c, id, bu);
         if (st.ovf)
             return moves;
@@ -2370,7 +2442,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
         st.nmem = 0;
         st.K = 0;
         st.V = 0;
-        st.LK = st.LV = 0.0;
+        st.rK2 = st.rV = 0.0;
         st.alpha = 0.0;
         st.pr = 0.0;
         st.pu = 0;
@@ -2461,7 +2533,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
                 st.alpha = A.alpha_set[set];
             else
                 st.alpha = A.scales[s];
-            set_logs(st);
+            set_rates(st);
             st.Gl = st.Rl = 0;
             st.Gu = 0;
             st.M = 0;
