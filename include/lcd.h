@@ -100,24 +100,26 @@ typedef struct {
                                 stops with LCD_EDEVICE.  0 = default (20000);
                                 negative = no budget at all (tests the error path) */
     int32_t spill_mode;      /* sets whose table outgrows tier 0: 0 = workgroup tiers
-                                (one workgroup per community: an LDS table of
-                                team_capacity entries, then global-memory tables);
+                                (one workgroup per community: LDS tables, then
+                                global-memory tables);
                                 1 = one-wave global-memory tiers; 2 = one-wave
                                 global tables of 16,384 entries, then workgroups
                                 on tables that hold every node */
-    int32_t team_capacity;   /* spill_mode 0: entries of the workgroup tier's LDS table;
-                                0 = max(1,024, 2 lds_capacity), within one workgroup's LDS */
+    int32_t team_capacity;   /* spill_mode 0: entries of one workgroup tier with LDS
+                                tables; 0 = chosen by the number of seed sets: three
+                                tiers of LDS tables for few sets (four per compute
+                                unit at most), none for more */
     int32_t team_waves;      /* waves per community in the workgroup tiers, 1..8;
-                                0 = 4 (2 on graphs of 4M+ nodes) */
+                                0 = 2 (4 on the largest LDS tables, 8 on the tables
+                                that hold every node) */
     int32_t grow_calls;      /* growth calls per (seed set, scale): 0 = until a call
                                 changes nothing (the default); n > 0 stops after
                                 n calls (lcd_sweep_merge makes one per round) */
-    int32_t queue_min_entries; /* workgroup tiers on global tables: once the table of a
-                                growth call holds this many entries (checked after
-                                each addition) the call keeps its queue bucketed by
-                                rank (a step looks at the queue's head, not the
-                                whole table); 0 = default (1,024); results never
-                                depend on it */
+    int32_t queue_min_entries; /* workgroup tiers on tables of 65,536 entries or more:
+                                from 16 x this many entries on, a growth call's
+                                removal passes search a list of the members sorted
+                                by ranges of node id; 0 = default (1,024); results
+                                never depend on it */
     int32_t output_mode;     /* LCD_OUT_FULL (default) or LCD_OUT_DELTA: lcd_sweep and
                                 lcd_sweep_batch only (the other calls store full
                                 lists); it changes what the member pool holds, never
@@ -314,7 +316,7 @@ typedef struct {
  * lcd_server_create() calls whose params leave every sizing field at 0 use
  * it.  k_prune and watchdog_ms come from base (NULL = defaults).  Results
  * of a sweep never depend on the sizing; only the time does.  Blocking;
- * runs 2 x 14 sample sweeps, then the three fastest sizings once on every
+ * runs 2 x 16 sample sweeps, then the three fastest sizings once on every
  * set when that full sweep is expected to take under 5 s.
  */
 lcd_status lcd_tune(lcd_graph *g, const double *scales, int32_t n_scales, const int32_t *seed_ptr,

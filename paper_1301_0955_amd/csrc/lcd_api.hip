@@ -58,26 +58,36 @@ lcd_status device_info(DevInfo &d) {
     return LCD_OK;
 }
 
-lcd_status ensure_slab(Slab &sl, int32_t cap, int32_t slots, hipStream_t st) {
+lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipStream_t st) {
     const int32_t hbits = next_pow2_bits(2 * (int64_t)cap);
-    const int64_t stride = slab_stride(cap);
-    if (sl.buf && sl.cap == cap && sl.slots == slots && !sl.dirty)
+    const int64_t bytes = slab_bytes(kind, cap) * slots;
+    if (sl.buf && sl.kind == kind && sl.cap == cap && sl.slots == slots && !sl.dirty)
         return LCD_OK;
-    if (!(sl.buf && sl.cap == cap && sl.slots == slots)) {
+    if (!(sl.buf && sl.kind == kind && sl.cap == cap && sl.slots == slots)) {
         dev_free(sl.buf);
-        CHK(dev_alloc(&sl.buf, (size_t)(stride * slots)));
+        CHK(dev_alloc(&sl.buf, (size_t)bytes));
     }
-    sl.stride = stride;
+    sl.kind = kind;
+    sl.stride = slab_stride(kind, cap);
     sl.cap = cap;
     sl.hbits = hbits;
     sl.slots = slots;
-    // all-ones bytes: every hash slot empty (-1); other arrays need no init
-    HIPCHK(launch_fill_i32((int32_t *)sl.buf, -1, stride * slots / 4, st));
+    // all-ones bytes: every hash slot empty; the rest of a table needs no init
+    HIPCHK(launch_fill_i32((int32_t *)sl.buf, -1, kind == TIER_TEAM_GLOBAL ? (int64_t)slots << hbits : bytes / 4, st));
     sl.dirty = false;
     return LCD_OK;
 }
 
-lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPlan &tp) {
+// Entries of the largest table held in LDS (a multiple of 64) whose workgroup
+// takes at most `bytes` of LDS.
+static int32_t block_capacity(int64_t bytes) {
+    int32_t cap = 8192;
+    while (cap > 64 && block_table_bytes(cap, block_hbits(cap)) + kTeamShBytes > bytes)
+        cap -= 64;
+    return cap;
+}
+
+lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp) {
     int32_t cap = p.lds_capacity > 0 ? p.lds_capacity : 512;
     if (cap % 64 != 0 || cap < 64 || cap > 8192)
         return fail(LCD_EINVAL, "lds_capacity must be a multiple of 64 in [64, 8192]");
@@ -96,20 +106,23 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPl
                                       : (int32_t)std::max<int64_t>(1, dev.lds_cu / (wpb * tb));
     bpc = std::min(bpc, 32);
     tp.n = 0;
-    tp.t[tp.n++] = TierSpec{TIER_WAVE_LDS, cap, hbits0, wpb, dev.cus * bpc, 0, -1};
+    tp.t[tp.n++] = TierSpec{TIER_WAVE_LDS, cap, hbits0, wpb, dev.cus * bpc, 0, -1, 0};
     const int64_t need = std::max<int64_t>(64, n);
     const int32_t capn = (int32_t)((int64_t)1 << next_pow2_bits(need));
     int32_t have = cap;   // largest table so far
     auto add_global = [&](int32_t kind, int32_t c, int32_t waves, int32_t slots, int32_t slab) {
-        tp.t[tp.n++] = TierSpec{kind, c, next_pow2_bits(2 * (int64_t)c), waves, 0, slots, slab};
+        tp.t[tp.n] = TierSpec{kind, c, next_pow2_bits(2 * (int64_t)c), waves, 0, slots, slab, tp.t[tp.n - 1].stat + 1};
+        tp.n += 1;
         have = c;
     };
     if (p.team_waves < 0 || 64 * p.team_waves > kTeamMaxThreads)
         return fail(LCD_EINVAL, "team_waves must be in [0, %d]", kTeamMaxThreads / 64);
-    // graphs of millions of nodes: their sets are chains of thousands of
-    // dependent steps on global tables, and two waves per set keep twice as
-    // many sets in flight at a step cost little above four waves'
-    const int32_t team_waves = p.team_waves > 0 ? p.team_waves : (n >= (4 << 20) ? 2 : 4);
+    // waves per community on global tables: with two, a community's step takes
+    // about 0.8 of its time with one, and six communities share a compute unit
+    // instead of twelve; the tables of twelve miss the L2 more often (sweeps of
+    // the 100k-, 1M- and 4M-node graphs: 26, 151 and 450 ms with two, 25, 148
+    // and 546 ms with one, 42, 219 and 505 ms with four)
+    const int32_t team_waves = p.team_waves > 0 ? p.team_waves : 2;
     // workgroups of a workgroup tier that stay resident on the whole chip
     auto resident = [&](int32_t kind, int32_t waves, size_t lds) -> int32_t {
         int32_t nb = 0;
@@ -122,7 +135,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPl
         if (c1 > have && n > have)
             add_global(TIER_WAVE_GLOBAL, c1, 4, 4096, 0);
         if (capn > have && n > have) {
-            int64_t slots = ((int64_t)4 << 30) / slab_stride(capn);
+            int64_t slots = ((int64_t)4 << 30) / slab_bytes(p.spill_mode == 1 ? TIER_WAVE_GLOBAL : TIER_TEAM_GLOBAL, capn);
             if (p.spill_mode == 1)
                 add_global(TIER_WAVE_GLOBAL, capn, 4, (int32_t)std::max<int64_t>(4, std::min<int64_t>(256, slots)), 1);
             else
@@ -131,21 +144,33 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPl
         }
         return LCD_OK;
     }
-    // workgroup tiers: an LDS table per workgroup, then global tables
-    int32_t cl = std::max(1024, 2 * cap);
+    // workgroup tiers.  A launch of few communities lasts as long as the
+    // longest chain of steps in it, and a step on an LDS table takes about 0.7
+    // of one on a global table: tables of the largest sizes that let three, two
+    // and one workgroup share a compute unit, then global ones.  A launch of
+    // many communities lasts as long as the chip needs for all their steps, and
+    // LDS tables leave too few in flight: all on global tables (1,000 sets: 5.5
+    // ms with the LDS tiers, 6.5 without; 20,000 sets: 55 and 26 ms).
+    struct Want { int32_t cap, waves; } want[3];
+    int n_want = 0;
     if (p.team_capacity > 0) {
-        cl = p.team_capacity;
+        const int32_t cl = p.team_capacity;
         if (cl % 64 != 0 || cl > 8192 ||
             table_bytes(cl, next_pow2_bits(2 * (int64_t)cl)) + 1024 > dev.lds_block)
             return fail(LCD_EINVAL, "team_capacity must be a multiple of 64 whose table fits one workgroup's LDS");
-    } else {
-        while (cl > 64 && table_bytes(cl, next_pow2_bits(2 * (int64_t)cl)) + 1024 > dev.lds_block)
-            cl >>= 1;
+        want[n_want++] = Want{cl, 2};
+    } else if (n_sets <= 4 * dev.cus) {
+        for (int share = 3; share >= 1; --share)
+            want[n_want++] = Want{block_capacity(std::min(dev.lds_block, dev.lds_cu / share)), share == 1 ? 4 : 2};
     }
-    if (cl > have && n > have) {
-        const int32_t hb = next_pow2_bits(2 * (int64_t)cl);
-        tp.t[tp.n++] = TierSpec{TIER_TEAM_LDS, cl, hb, team_waves,
-                                resident(TIER_TEAM_LDS, team_waves, (size_t)table_bytes(cl, hb)), 0, -1};
+    for (int q = 0; q < n_want; ++q) {
+        const int32_t cl = want[q].cap;
+        if (cl <= have || n <= have)
+            continue;
+        const int32_t hb = block_hbits(cl);
+        const int32_t waves = p.team_waves > 0 ? p.team_waves : want[q].waves;
+        tp.t[tp.n++] = TierSpec{TIER_TEAM_LDS, cl, hb, waves,
+                                resident(TIER_TEAM_LDS, waves, (size_t)block_table_bytes(cl, hb)), 0, -1, 1};
         have = cl;
     }
     // graphs of millions of nodes grow communities of thousands of members
@@ -159,7 +184,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPl
         // the whole-graph tier gets the few largest communities, whose
         // step-by-step chain is the tier's time: the widest workgroups
         const int32_t wide = kTeamMaxThreads / 64;
-        int64_t slots = ((int64_t)4 << 30) / slab_stride(capn);
+        int64_t slots = ((int64_t)4 << 30) / slab_bytes(TIER_TEAM_GLOBAL, capn);
         add_global(TIER_TEAM_GLOBAL, capn, wide,
                    (int32_t)std::max<int64_t>(4, std::min<int64_t>(resident(TIER_TEAM_GLOBAL, wide, 0), slots)), 1);
     }
@@ -179,6 +204,7 @@ lcd_status enqueue_tiers(const SweepArgs &a0, const TierPlan &tp, int first, int
             HIPCHK(hipEventRecord(ev[k], st));
         SweepArgs b = a0;
         b.tier = k;
+        b.stat_slot = T.stat;
         b.kind = T.kind;
         b.in_from = k > 0 ? k - 1 : 0;
         b.work_in = k > 0 ? work[k - 1] : nullptr;
@@ -246,8 +272,8 @@ struct lcd_result {
     int32_t n_ctl = 0;
     unsigned long long *cursor = nullptr;
     uint32_t *err = nullptr;
-    int32_t *work[kMaxTiers - 1] = {nullptr, nullptr, nullptr};
-    int32_t *ordered[kMaxTiers - 1] = {nullptr, nullptr, nullptr};   // work, by overflow scale
+    int32_t *work[kMaxTiers - 1] = {};
+    int32_t *ordered[kMaxTiers - 1] = {};   // work, by overflow scale
     std::vector<double> scales_h;
     lcd_sweep_stats stats{};
     int32_t *into = nullptr;          // merge mode: per record, -1 live or the live id merged into
@@ -265,7 +291,7 @@ namespace {
 lcd_status prepare_slabs(lcd_graph *g, const TierPlan &tp, hipStream_t st) {
     for (int k = 0; k < tp.n; ++k)
         if (tp.t[k].slab >= 0)
-            CHK(ensure_slab(g->slab[tp.t[k].slab], tp.t[k].cap, tp.t[k].slots, st));
+            CHK(ensure_slab(g->slab[tp.t[k].slab], tp.t[k].kind, tp.t[k].cap, tp.t[k].slots, st));
     return LCD_OK;
 }
 
@@ -284,7 +310,7 @@ lcd_status run_group(lcd_result *r, const TierPlan &tp, int32_t s_begin, int32_t
     a.n_sets = r->n_sets;
     a.k_prune = r->prm.k_prune;
     a.max_calls = r->prm.grow_calls > 0 ? (uint32_t)r->prm.grow_calls : 0u;
-    a.queue_min = queue_min_of(r->prm);
+    a.by_id_min = by_id_min_of(r->prm);
     a.resume = s_begin > 0 ? 1 : 0;
     a.rec = r->rec;
     a.pool = r->pool;
@@ -362,16 +388,17 @@ lcd_status capture_sweep(lcd_result *r, const TierPlan &tp) {
 lcd_status run_sweep(lcd_result *r, hipStream_t st) {
     lcd_graph *g = const_cast<lcd_graph *>(r->g);
     TierPlan tp;
-    CHK(plan_tiers(g->dev, g->n, r->prm, tp));
+    CHK(plan_tiers(g->dev, g->n, r->n_sets, r->prm, tp));
     CHK(prepare_slabs(g, tp, st));
     r->stats = lcd_sweep_stats{};
     r->stats.lds_capacity = tp.t[0].cap;
     r->stats.waves_per_block = tp.t[0].waves;
     r->stats.grid_blocks = tp.t[0].blocks;
-    r->stats.tiers = tp.n;
+    r->stats.tiers = tp.t[tp.n - 1].stat + 1;
     for (int k = 0; k < tp.n; ++k) {
-        r->stats.tier_kind[k] = tp.t[k].kind;
-        r->stats.tier_capacity[k] = tp.t[k].cap;
+        // tiers that share a slot report the largest one's capacity
+        r->stats.tier_kind[tp.t[k].stat] = tp.t[k].kind;
+        r->stats.tier_capacity[tp.t[k].stat] = tp.t[k].cap;
     }
     // ev[0 .. n]: before each tier and after the last; ev[kMaxTiers + 1]:
     // before the work-queue reset
@@ -422,7 +449,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
         HIPCHK(hipMemcpy(ctl.data(), r->ctl, sizeof(Counters) * r->n_ctl, hipMemcpyDeviceToHost));
         float ms_total = 0.f, ms_main = 0.f, ms_spill = 0.f;
         HIPCHK(hipEventElapsedTime(&ms_total, ev_begin, ev_end));
-        for (int k = 0; k < kMaxTiers; ++k)
+        for (int k = 0; k < kStatSlots; ++k)
             r->stats.ms_tier[k] = 0.0;
         if (timed) {
             HIPCHK(hipEventElapsedTime(&ms_main, ev[0], ev[1]));
@@ -431,7 +458,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
             for (int k = 0; k < tp.n; ++k) {
                 float x = 0.f;
                 HIPCHK(hipEventElapsedTime(&x, ev[k], ev[k + 1]));
-                r->stats.ms_tier[k] = x;
+                r->stats.ms_tier[tp.t[k].stat] += x;
             }
         }
         const uint32_t err = (uint32_t)(cur[1] & 0xffffffffu);
@@ -453,7 +480,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
         r->stats.n_spilled = sp;
         r->stats.n_spilled_big = spb;
         r->stats.pool_used = (int64_t)cur[0];
-        for (int t = 0; t < kMaxTiers; ++t) {
+        for (int t = 0; t < kStatSlots; ++t) {
             const unsigned long long *x = cur + 2 + kStatWords * t;
             r->stats.tier[t].rows_gathered = (int64_t)x[0];
             r->stats.tier[t].row_entries = (int64_t)x[1];
@@ -506,10 +533,7 @@ void result_release(lcd_result *r) {
     dev_free(r->pool);
     dev_free(r->ctl);
     dev_free(r->cursor);
-    for (auto &w : r->work)
-        dev_free(w);
-    for (auto &w : r->ordered)
-        dev_free(w);
+    dev_free(r->work[0]);   // and the queues after it
     delete r;
 }
 
@@ -647,6 +671,9 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
         dev_free(g->w);
         dev_free(g->kdeg);
         dev_free(g->logtab);
+        dev_free(g->info);
+        dev_free(g->adj);
+        dev_free(g->adjl);
         delete g;
         return s;
     };
@@ -662,10 +689,20 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
     if ((s = dev_alloc(&g->row_ptr, (size_t)n + 1)) != LCD_OK ||
         (s = dev_alloc(&g->col, (size_t)nnz)) != LCD_OK ||
         (s = dev_alloc(&g->kdeg, (size_t)std::max(n, 1))) != LCD_OK ||
-        (s = dev_alloc(&g->logtab, (size_t)g->logtab_n)) != LCD_OK)
+        (s = dev_alloc(&g->logtab, (size_t)g->logtab_n)) != LCD_OK ||
+        (s = dev_alloc(&g->info, (size_t)std::max(n, 1))) != LCD_OK)
         return bail(s);
     if (w && (s = dev_alloc(&g->w, (size_t)nnz)) != LCD_OK)
         return bail(s);
+    // the adjacency records (24 bytes per directed entry) shorten a step on
+    // LDS tables; a graph that would give them more than an eighth of the
+    // free memory goes without
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && (uint64_t)nnz * 24 <= free_b / 8 &&
+        (dev_alloc(&g->adj, (size_t)nnz) != LCD_OK || dev_alloc(&g->adjl, (size_t)nnz) != LCD_OK)) {
+        dev_free(g->adj);
+        dev_free(g->adjl);
+    }
     hipError_t e = hipSuccess;
     if (e == hipSuccess)
         e = hipMemcpyAsync(g->row_ptr, rp.data(), sizeof(int32_t) * ((size_t)n + 1),
@@ -677,7 +714,11 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
     if (e == hipSuccess)
         e = launch_degrees(g->row_ptr, g->w, g->kdeg, n, st);
     if (e == hipSuccess)
+        e = launch_node_info(g->row_ptr, g->kdeg, g->info, n, st);
+    if (e == hipSuccess)
         e = launch_logtab(g->logtab, g->logtab_n, st);
+    if (e == hipSuccess && g->adj)
+        e = launch_adj(g->row_ptr, g->col, g->w, g->kdeg, g->logtab, nnz, g->adj, g->adjl, st);
     if (e == hipSuccess)
         e = hipStreamSynchronize(st);
     if (e != hipSuccess)
@@ -806,6 +847,9 @@ lcd_status lcd_graph_free(lcd_graph *g) {
     dev_free(g->w);
     dev_free(g->kdeg);
     dev_free(g->logtab);
+    dev_free(g->info);
+    dev_free(g->adj);
+    dev_free(g->adjl);
     dev_free(g->slab[0].buf);
     dev_free(g->slab[1].buf);
     dev_free(g->seed_ws);
@@ -898,18 +942,17 @@ lcd_status lcd_sweep(const lcd_graph *g, const double *scales, int32_t n_scales,
         (s = dev_alloc(&r->pool, (size_t)est)) != LCD_OK ||
         (s = dev_alloc(&r->ctl, (size_t)r->n_ctl)) != LCD_OK ||
         (s = dev_alloc(&r->cursor, kCursorWords)) != LCD_OK ||
-        (s = dev_alloc(&r->work[0], (size_t)std::max(n_sets, 1))) != LCD_OK ||
-        (s = dev_alloc(&r->work[1], (size_t)std::max(n_sets, 1))) != LCD_OK ||
-        (s = dev_alloc(&r->work[2], (size_t)std::max(n_sets, 1))) != LCD_OK ||
-        (s = dev_alloc(&r->ordered[0], (size_t)std::max(n_sets, 1))) != LCD_OK ||
-        (s = dev_alloc(&r->ordered[1], (size_t)std::max(n_sets, 1))) != LCD_OK ||
-        (s = dev_alloc(&r->ordered[2], (size_t)std::max(n_sets, 1))) != LCD_OK ||
+        (s = dev_alloc(&r->work[0], 2 * (kMaxTiers - 1) * (size_t)std::max(n_sets, 1))) != LCD_OK ||
         (prm.output_mode == LCD_OUT_DELTA &&
          ((s = dev_alloc(&r->rec.dadd, std::max<size_t>(R, 1))) != LCD_OK ||
           (s = dev_alloc(&r->rec.drem, std::max<size_t>(R, 1))) != LCD_OK))) {
         result_release(r);
         return s;
     }
+    // one allocation for the overflow queues and their ordered copies
+    for (int k = 1; k < 2 * (kMaxTiers - 1); ++k)
+        (k < kMaxTiers - 1 ? r->work[k] : r->ordered[k - (kMaxTiers - 1)]) =
+            r->work[0] + (size_t)k * (size_t)std::max(n_sets, 1);
     r->pool_cap = est;
     r->err = (uint32_t *)(r->cursor + 1);
     hipError_t e = hipMemcpyAsync(r->scales, sc.data(), sizeof(double) * n_scales,
@@ -1516,12 +1559,12 @@ lcd_status lcd_tune(lcd_graph *g, const double *scales, int32_t n_scales, const 
     if (base)
         b = *base;
     b.mode = LCD_PERSISTENT;
-    // candidate sizings: {tier-0 table, spill mode, workgroup LDS table, waves per community}
+    // candidate sizings: {tier-0 table, spill mode, workgroup LDS table, waves per community}; 0: default
     static const int32_t cand[][4] = {
         {256, 0, 1024, 2}, {256, 0, 1024, 4}, {512, 0, 1024, 2}, {512, 0, 1024, 4},
         {512, 0, 2048, 4}, {1024, 0, 2048, 4}, {256, 0, 768, 2},  {256, 0, 768, 4},
         {512, 0, 768, 2},  {512, 0, 768, 4},  {256, 2, 0, 8},     {512, 2, 0, 8},
-        {512, 1, 0, 0},    {1024, 1, 0, 0},
+        {512, 1, 0, 0},    {1024, 1, 0, 0},    {512, 0, 0, 0},    {256, 0, 0, 0},
     };
     const int nc = (int)(sizeof(cand) / sizeof(cand[0]));
     lcd_tune_report rep{};

@@ -91,6 +91,7 @@ lcd_status device_info(DevInfo &d);
 // Global-memory table workspace of one spill tier.
 struct Slab {
     char *buf = nullptr;
+    int32_t kind = -1;
     int64_t stride = 0;
     int32_t cap = 0;
     int32_t hbits = 0;
@@ -99,11 +100,11 @@ struct Slab {
 };
 
 // pool cursor, error word, then kStatWords statistics per tier
-constexpr int kCursorWords = 2 + kStatWords * kMaxTiers;
+constexpr int kCursorWords = 2 + kStatWords * kStatSlots;
 
-// The table size from which a growth call keeps its queue bucketed by rank.
-inline int32_t queue_min_of(const lcd_params &p) {
-    return p.queue_min_entries > 0 ? p.queue_min_entries : 1024;
+// Table entries above which a removal pass sorts its member list.
+inline int32_t by_id_min_of(const lcd_params &p) {
+    return (int32_t)std::min<int64_t>(16 * (int64_t)(p.queue_min_entries > 0 ? p.queue_min_entries : 1024), INT32_MAX);
 }
 
 // One tier of the launch chain.
@@ -115,6 +116,7 @@ struct TierSpec {
     int32_t blocks;    // workgroups of an LDS tier (tier 0: the full-size grid)
     int32_t slots;     // global tiers: tables wanted in the slab
     int32_t slab;      // global tiers: slab index; -1 for LDS tiers
+    int32_t stat;      // statistics slot
 };
 
 struct TierPlan {
@@ -122,20 +124,34 @@ struct TierPlan {
     TierSpec t[kMaxTiers];
 };
 
-inline int64_t slab_stride(int32_t cap) {
-    return (global_table_bytes(cap, next_pow2_bits(2 * (int64_t)cap)) + 255) / 256 * 256;
+// Hash bits of a table indexed in LDS: at least 4/3 slots per entry (groups
+// of four slots keep the probes short at that load), two groups at least.
+inline int32_t block_hbits(int32_t cap) { return std::max(3, next_pow2_bits(((int64_t)cap * 4 + 2) / 3)); }
+
+// Bytes between the tables of a slab, and of a table in all (a workgroup
+// table's hash lies apart, see carve_slab in the kernels).
+inline int64_t slab_stride(int32_t kind, int32_t cap) {
+    return kind == TIER_TEAM_GLOBAL ? team_table_bytes(cap)
+                                    : (table_bytes(cap, next_pow2_bits(2 * (int64_t)cap)) + 255) / 256 * 256;
 }
 
-// The tier chain for a graph of n nodes: tier 0 one wave per community with
-// an LDS table (lds_capacity entries), then tiers with larger tables.
-// spill_mode 0: workgroup tiers (LDS table of 4,096 entries, global tables of
-// 16,384 entries, global tables that hold every node); 1: one-wave global
-// tiers (16,384 entries x 4,096 tables, then every node).
-lcd_status plan_tiers(const DevInfo &dev, int32_t n, const lcd_params &p, TierPlan &tp);
+inline int64_t slab_bytes(int32_t kind, int32_t cap) {
+    return slab_stride(kind, cap) +
+           (kind == TIER_TEAM_GLOBAL ? (int64_t)4 << next_pow2_bits(2 * (int64_t)cap) : 0);
+}
 
-// (Re)allocate a slab for cap entries x slots tables and mark every hash
-// slot empty; a clean slab of the same shape is kept as it is.
-lcd_status ensure_slab(Slab &sl, int32_t cap, int32_t slots, hipStream_t st);
+// The tier chain for n_sets communities on a graph of n nodes: tier 0 one
+// wave per community with an LDS table (lds_capacity entries), then tiers with
+// larger tables.  spill_mode 0: workgroup tiers (LDS tables for few sets,
+// global tables of 16,384 entries, or 131,072 on graphs of millions of nodes,
+// global tables that hold every node); 1: one-wave global tiers (16,384
+// entries x 4,096 tables, then every node); 2: a one-wave global tier, then
+// workgroups.
+lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp);
+
+// (Re)allocate a slab for cap entries x slots tables of a tier kind and mark
+// every hash slot empty; a clean slab of the same shape is kept as it is.
+lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipStream_t st);
 
 // Enqueue one launch group on st: tiers first .. last-1 of tp in order, tier
 // k > 0 fed by the overflow queue work[k - 1] (count in ctl->ovf_count[k-1])
@@ -170,6 +186,9 @@ struct lcd_graph {
     uint8_t *w = nullptr;
     int32_t *kdeg = nullptr;
     double *logtab = nullptr;
+    int2 *info = nullptr;
+    int4 *adj = nullptr;        // adjacency records; null when memory is short
+    double *adjl = nullptr;
     int32_t logtab_n = 0;
     lcd::DevInfo dev;
     lcd::Slab slab[2];          // spill-tier tables of lcd_sweep on this graph
@@ -191,6 +210,10 @@ static inline lcd::GraphDev graph_dev(const lcd_graph *g) {
     d.w = g->w;
     d.kdeg = g->kdeg;
     d.logtab = g->logtab;
+    d.info = g->info;
+    d.adj = g->adj;
+    d.adjl = g->adjl;
+    d.nnz = g->nnz;
     d.n = g->n;
     d.logtab_n = g->logtab_n;
     return d;

@@ -14,6 +14,10 @@ struct GraphDev {
     const uint8_t *w;         // [nnz] or nullptr (all weights 1)
     const int32_t *kdeg;      // [n] weighted degree
     const double *logtab;     // [logtab_n] L(x) for x < logtab_n
+    const int2 *info;         // [n] row start and weighted degree (one load for a table entry)
+    const int4 *adj;          // [nnz] adjacency records, or nullptr (see Ctx)
+    const double *adjl;       // [nnz] log of the neighbour's degree
+    int64_t nnz;
     int32_t n;
     int32_t logtab_n;
 };
@@ -48,9 +52,12 @@ enum : uint32_t {
 
 // Work-queue state of one launch group (all tiers of one scale range),
 // zeroed before the group runs.
+constexpr int kMaxTiers = 6;    // tiers of a launch chain
+constexpr int kStatSlots = 4;   // tier statistics kept (lcd_sweep_stats): the LDS workgroup tiers share one
+
 struct Counters {
-    uint32_t work_next[4];    // per tier: next work item
-    uint32_t ovf_count[4];    // per tier: items pushed to the next tier
+    uint32_t work_next[kMaxTiers];    // per tier: next work item
+    uint32_t ovf_count[kMaxTiers];    // per tier: items pushed to the next tier
 };
 
 struct SweepArgs {
@@ -63,8 +70,8 @@ struct SweepArgs {
     int32_t n_sets;
     uint32_t k_prune;
     uint32_t max_calls;       // growth calls per (set, scale); 0 = until one changes nothing
-    int32_t queue_min;        // workgroup tiers on global tables: a growth call switches to
-                              // the bucketed queue once its table holds this many entries
+    int32_t by_id_min;        // workgroup tiers, tables of 32-bit indices: a removal pass sorts
+                              // its member list by id once the table holds more entries
     int32_t resume;           // 1: start from the records of scale s_begin - 1
     Records rec;
     int32_t *pool;
@@ -72,14 +79,15 @@ struct SweepArgs {
     Counters *ctl;
     unsigned long long *pool_cursor;   // entries claimed in the pool (may pass pool_cap)
     uint32_t *err;                     // ERR_* bits
-    unsigned long long *stat;          // per tier (kStatWords each), over the sets the tier
+    unsigned long long *stat;          // per statistics slot (kStatWords each), over the sets the tier
                                        // finished: rows gathered, their length, entries
                                        // created, pool entries written, sets finished, table
                                        // entries scanned; over every set the tier ran, for
                                        // the scales whose records it wrote: rows gathered by
                                        // moves, their length, seed-set rows, their length,
                                        // entries created after the set's start
-    int32_t tier;             // 0 = LDS; 1, 2 = global-memory tiers
+    int32_t tier;             // position in the launch chain
+    int32_t stat_slot;        // where the tier's statistics are counted
     int32_t in_from;          // tier > 0: the tier whose pushes this one consumes
     const int32_t *work_in;   // tier > 0: set ids pushed by that tier
     int32_t *work_out;        // sets pushed to the next tier (nullptr for the last)
@@ -103,7 +111,6 @@ enum : int32_t {
     TIER_TEAM_LDS = 2,        // one workgroup per community, table in LDS
     TIER_TEAM_GLOBAL = 3      // one workgroup per community, table in global memory
 };
-constexpr int kMaxTiers = 4;
 constexpr int kStatWords = 11;  // statistics words per tier
 constexpr int kTeamMaxThreads = 512;
 
@@ -116,27 +123,36 @@ __host__ __device__ constexpr int64_t table_bytes(int32_t cap, int32_t hbits) {
     return (int64_t)cap * kEntryBytes + ((int64_t)1 << hbits) * kSlotBytes;
 }
 
-// Global tables hold the LDS layout plus the workgroup kernel's
-// rank-bucketed queue and fresh list (one int32 entry index per table entry
-// each); from kRecordMinEntries entries on, the fields of an entry are one
-// 32-byte record instead (d|flags, node, k, rank), since the steps on such
-// tables reach most entries at random through the queue.
-// Their hash slots hold the node id beside the entry index (8 bytes), so a
-// lookup is one load.
+// Workgroup tables: 32-bit hash slots, a queue of entry indices and the fresh
+// list, and per entry rank, node, d|flags, degree and row start.  In LDS (with
+// a copy of the first logs) these are arrays and the indices have 16 bits; in
+// global memory an entry is a 32-byte record, with scratch i32[cap] beside,
+// and tables from kRecordMinEntries entries on have 32-bit indices.
+constexpr int kBlockLogs = 512;
 constexpr int kRecordBytes = 32;
 constexpr int32_t kRecordMinEntries = 65536;
-constexpr int kPairSlotBytes = 8;
-constexpr int kQueueBytes = 4 /*bucketed queue*/ + 4 /*fresh list*/;
+constexpr int kBlockEntryBytes = 8 /*rank*/ + 4 /*node*/ + 4 /*d|flags*/ + 4 /*k*/ + 4 /*row start*/ + 2 /*queue*/;
+constexpr int kFreshMax = 512;       // fresh-list entries of an LDS table
+constexpr int kFreshRebuild = 256;   // ... from which the queue is rebuilt, at least
+constexpr int kTeamShBytes = 3072;   // LDS a workgroup uses beside its table, at most
 
-__host__ __device__ constexpr int64_t global_table_bytes(int32_t cap, int32_t hbits) {
-    return cap >= kRecordMinEntries
-               ? (int64_t)cap * (kRecordBytes + kQueueBytes) + (((int64_t)cap * 4 /*scratch*/ + 7) & ~(int64_t)7) +
-                     ((int64_t)1 << hbits) * kPairSlotBytes
-               : table_bytes(cap, hbits) + (int64_t)cap * kQueueBytes;
+__host__ __device__ constexpr int64_t block_table_bytes(int32_t cap, int32_t hbits) {
+    return (int64_t)kBlockLogs * 8 + ((int64_t)1 << hbits) * 4 + (int64_t)cap * kBlockEntryBytes + kFreshMax * 2;
+}
+
+__host__ __device__ constexpr int32_t fresh_max(int32_t cap) { return kFreshMax + cap / 64; }
+
+// One workgroup table in global memory, without its hash (4 << hbits bytes).
+__host__ __device__ constexpr int64_t team_table_bytes(int32_t cap) {
+    return ((int64_t)cap * (kRecordBytes + 4) +
+            ((int64_t)cap + fresh_max(cap)) * (cap >= kRecordMinEntries ? 4 : 2) + 255) & ~(int64_t)255;
 }
 
 hipError_t launch_degrees(const int32_t *row_ptr, const uint8_t *w, int32_t *kdeg, int32_t n,
                           hipStream_t st);
+hipError_t launch_node_info(const int32_t *row_ptr, const int32_t *kdeg, int2 *info, int32_t n, hipStream_t st);
+hipError_t launch_adj(const int32_t *row_ptr, const int32_t *col, const uint8_t *w, const int32_t *kdeg,
+                      const double *logtab, int64_t nnz, int4 *adj, double *adjl, hipStream_t st);
 hipError_t launch_logtab(double *tab, int32_t m, hipStream_t st);
 hipError_t launch_log(const uint64_t *x, double *out, int64_t n, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);

@@ -105,90 +105,38 @@ __device__ __forceinline__ bool before(double r, int32_t u, double pr, int32_t p
     return r > pr || (r == pr && u < pu);
 }
 
-// A community's table.  Field f of entry i is at fb + i * fs: separate
-// arrays in LDS tables and small global tables (a scan reads one field of
-// consecutive entries), one 32-byte record per entry in global tables of
-// kRecordMinEntries or more (a step reads the fields of entries it reaches
-// through the queue or the fresh list at random: one cache line per entry
-// instead of four; 19 % off the 10M-node sweep, 2 % slower on 16,384-entry
-// tables, which stay arrays).
+// A wave's community table: one array per field (a scan reads one field of
+// consecutive entries).
 struct Tab {
-    char *rkb, *nodeb, *dvb, *kvb;
-    uint32_t rks, nodes, dvs, kvs;
-    __device__ __forceinline__ double &RK(int32_t i) const { return *(double *)(rkb + (uint32_t)i * rks); }
-    __device__ __forceinline__ int32_t &NODE(int32_t i) const { return *(int32_t *)(nodeb + (uint32_t)i * nodes); }
-    __device__ __forceinline__ uint32_t &DV(int32_t i) const { return *(uint32_t *)(dvb + (uint32_t)i * dvs); }
-    __device__ __forceinline__ int32_t &KV(int32_t i) const { return *(int32_t *)(kvb + (uint32_t)i * kvs); }
+    double *rk;
+    int32_t *node;
+    uint32_t *dv;
+    int32_t *kv;
+    __device__ __forceinline__ double &RK(int32_t i) const { return rk[i]; }
+    __device__ __forceinline__ int32_t &NODE(int32_t i) const { return node[i]; }
+    __device__ __forceinline__ uint32_t &DV(int32_t i) const { return dv[i]; }
+    __device__ __forceinline__ int32_t &KV(int32_t i) const { return kv[i]; }
     int32_t *scr;
-    int32_t *hs;      // hash slots: entry index (LDS and array-layout tables)
-    uint64_t *hp;     // hash slots: node id << 32 | entry index (record tables)
-    int32_t *sq;      // global tables: rank-bucketed queue (entry indices)
-    int32_t *fr;      // global tables: fresh list (entry indices)
+    int32_t *hs;      // hash slots: entry index
     uint32_t hmask;
     int hbits;
     int cap;
 };
 
-// LDS table: rank f64[cap], node i32[cap], d|flags u32[cap], degree
-// i32[cap], scratch i32[cap], hash slots i32[2^hbits].
+// Rank f64[cap], node i32[cap], d|flags u32[cap], degree i32[cap], scratch
+// i32[cap], hash slots i32[2^hbits], in LDS or global memory.
 __device__ __forceinline__ Tab carve(char *base, int cap, int hbits) {
     Tab t;
-    t.rkb = base;
-    t.nodeb = base + (size_t)cap * 8;
-    t.dvb = base + (size_t)cap * 12;
-    t.kvb = base + (size_t)cap * 16;
-    t.rks = 8;
-    t.nodes = t.dvs = t.kvs = 4;
-    t.scr = (int32_t *)(base + (size_t)cap * 20);
-    t.hs = (int32_t *)(base + (size_t)cap * 24);
-    t.hp = nullptr;
-    t.sq = nullptr;
-    t.fr = nullptr;
+    t.rk = (double *)base;
+    t.node = (int32_t *)(t.rk + cap);
+    t.dv = (uint32_t *)(t.node + cap);
+    t.kv = t.node + 2 * (size_t)cap;
+    t.scr = t.node + 3 * (size_t)cap;
+    t.hs = t.node + 4 * (size_t)cap;
     t.hbits = hbits;
     t.hmask = (1u << hbits) - 1;
     t.cap = cap;
     return t;
-}
-
-// Global table: the LDS layout then the bucketed queue i32[cap] and the
-// fresh list i32[cap]; from kRecordMinEntries entries on, records
-// {d|flags u32, node i32, degree i32, -, rank f64, -} of kRecordBytes, then
-// scratch i32[cap] (padded to 8 bytes), hash slots u64[2^hbits] of
-// node << 32 | index, queue and fresh list.
-template <bool REC>
-__device__ __forceinline__ Tab carve_global_as(char *base, int cap, int hbits) {
-    if constexpr (!REC) {
-        Tab t = carve(base, cap, hbits);
-        char *q = base + table_bytes(cap, hbits);
-        t.sq = (int32_t *)q;
-        t.fr = (int32_t *)(q + (size_t)cap * 4);
-        return t;
-    } else {
-        Tab t;
-        t.dvb = base;
-        t.nodeb = base + 4;
-        t.kvb = base + 8;
-        t.rkb = base + 16;
-        t.rks = t.nodes = t.dvs = t.kvs = kRecordBytes;
-        char *p = base + (size_t)cap * kRecordBytes;
-        t.scr = (int32_t *)p;
-        const size_t scr_bytes = ((size_t)cap * 4 + 7) & ~(size_t)7;
-        t.hs = nullptr;
-        t.hp = (uint64_t *)(p + scr_bytes);
-        char *q = p + scr_bytes + ((size_t)1 << hbits) * kPairSlotBytes;
-        t.sq = (int32_t *)q;
-        t.fr = (int32_t *)(q + (size_t)cap * 4);
-        t.hbits = hbits;
-        t.hmask = (1u << hbits) - 1;
-        t.cap = cap;
-        return t;
-    }
-}
-
-// The layout a global table of cap entries has.
-__device__ __forceinline__ Tab carve_global(char *base, int cap, int hbits) {
-    return cap >= kRecordMinEntries ? carve_global_as<true>(base, cap, hbits)
-                                    : carve_global_as<false>(base, cap, hbits);
 }
 
 template <bool GLOBAL>
@@ -237,6 +185,9 @@ struct St {
     uint64_t ins_mark, c_ins;       // entries created: not counted before ins_mark;
                                     // committed count at the last record written
     uint64_t srows, srow_len;       // seed-set rows of a set in its first tier
+    double qtop, qscale;            // compact LDS tables: rank range of the queue's buckets
+    double nqtop, nqscale;          // ... of the next growth call
+    int32_t flen;                   // ... entries on the fresh list
     bool emitted;                   // a record was written in this tier
 };
 
@@ -258,7 +209,27 @@ struct Ctx {
     const double *logtab;
     int32_t logtab_last;   // largest valid index of logtab
     int32_t n;             // nodes
+    int64_t nnz;           // directed entries
+    const int2 *info;      // per node: row start, weighted degree
+    const int4 *adj;       // per directed entry: neighbour, its degree, its row start, weight; or null
+    const double *adjl;    // ... and the log of its degree
 };
+
+__device__ __forceinline__ Ctx make_ctx(const GraphDev &g) {
+    Ctx c;
+    c.row_ptr = g.row_ptr;
+    c.col = g.col;
+    c.w = g.w;
+    c.kdeg = g.kdeg;
+    c.logtab = g.logtab;
+    c.logtab_last = g.logtab_n - 1;
+    c.n = g.n;
+    c.nnz = g.nnz;
+    c.info = g.info;
+    c.adj = g.adj;
+    c.adjl = g.adjl;
+    return c;
+}
 
 // queue rank R(d, k) = L(2d) - alpha L(k); 2d <= 2k <= 2 max degree, so both
 // logs come from the table (the clamp only keeps a broken table in bounds)
@@ -268,25 +239,9 @@ __device__ __forceinline__ double rank_of(const Ctx &c, int32_t d, int32_t k, do
     return c.logtab[i2] - alpha * c.logtab[ik];
 }
 
-constexpr uint64_t kEmptyPair = ~0ull;   // node -1, index -1
-
 template <bool GLOBAL>
 __device__ __forceinline__ int32_t tab_find(const Tab &t, int32_t u, uint32_t &err) {
     uint32_t p = hash_of(u, t.hbits);
-    if constexpr (GLOBAL) {
-        if (t.hp) {
-            for (uint32_t it = 0; it <= t.hmask; ++it) {
-                const uint64_t s = __hip_atomic_load(&t.hp[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (s == kEmptyPair)
-                    return -1;
-                if ((int32_t)(uint32_t)(s >> 32) == u)
-                    return (int32_t)(uint32_t)s;
-                p = (p + 1) & t.hmask;
-            }
-            err |= ERR_PROBE;
-            return -1;
-        }
-    }
     for (uint32_t it = 0; it <= t.hmask; ++it) {
         int32_t i = hs_load<GLOBAL>(&t.hs[p]);
         if (i < 0)
@@ -304,20 +259,10 @@ template <bool GLOBAL>
 __device__ __forceinline__ void tab_slot_insert(const Tab &t, int32_t u, int32_t idx, uint32_t &err) {
     uint32_t p = hash_of(u, t.hbits);
     uint32_t it = 0;
-    if (GLOBAL && t.hp) {
-        const uint64_t v = ((uint64_t)(uint32_t)u << 32) | (uint32_t)idx;
-        for (; it <= t.hmask; ++it) {
-            if (atomicCAS((unsigned long long *)&t.hp[p], (unsigned long long)kEmptyPair,
-                          (unsigned long long)v) == (unsigned long long)kEmptyPair)
-                break;
-            p = (p + 1) & t.hmask;
-        }
-    } else {
-        for (; it <= t.hmask; ++it) {
-            if (atomicCAS(&t.hs[p], -1, idx) == -1)
-                break;
-            p = (p + 1) & t.hmask;
-        }
+    for (; it <= t.hmask; ++it) {
+        if (atomicCAS(&t.hs[p], -1, idx) == -1)
+            break;
+        p = (p + 1) & t.hmask;
     }
     if (it > t.hmask)
         err |= ERR_PROBE;
@@ -329,13 +274,7 @@ template <bool GLOBAL>
 __device__ __forceinline__ void tab_slot_clear(const Tab &t, int32_t i) {
     uint32_t p = hash_of(t.NODE(i), t.hbits);
     for (uint32_t it = 0; it <= t.hmask; ++it) {
-        if (t.hp) {
-            const uint64_t s = __hip_atomic_load(&t.hp[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((int32_t)(uint32_t)s == i) {
-                __hip_atomic_store(&t.hp[p], kEmptyPair, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return;
-            }
-        } else if (hs_load<GLOBAL>(&t.hs[p]) == i) {
+        if (hs_load<GLOBAL>(&t.hs[p]) == i) {
             hs_store<GLOBAL>(&t.hs[p], -1);
             return;
         }
@@ -434,6 +373,9 @@ __device__ void row_update(const Tab &t, St &st, const Ctx &c, int32_t n, int la
 // Four logs of eleven dependent steps and a division each: reached only by
 // the few entries that the certified comparisons below leave open.
 __device__ __forceinline__ bool decide(int64_t K, int64_t V, int64_t Kp, int64_t Vp, double alpha) {
+    // K and V do not change inside a scan: kept opaque here, or the compiler
+    // moves their logs before it and every scan pays for both
+    asm volatile("" : "+v"(K), "+v"(V));
     const double a = ilog((uint64_t)Kp) - ilog((uint64_t)K);
     const double b = ilog((uint64_t)Vp) - ilog((uint64_t)V);
     const double cc = alpha * b;
@@ -455,9 +397,9 @@ __device__ __forceinline__ bool decide(int64_t K, int64_t V, int64_t Kp, int64_t
 // LDS tables and by latency on global ones; with the VALU reductions below
 // the 1,000-node sweep's workgroup tier went from 6.0 to 4.4 ms, tier 2 of a
 // 1,000,000-node share from 209 to 188 ms.
-__device__ __forceinline__ bool improves_add(const St &st, int32_t d, int32_t k) {
-    if (st.K == 0)
-        return true;
+//
+// settle_add: 1 raises f, 0 does not, -1 left open (K > 0).
+__device__ __forceinline__ int settle_add(const St &st, int32_t d, int32_t k) {
     const double x = (double)d * st.rK2;
     const double y = (double)k * st.rV;
     const double ay = st.alpha * y;
@@ -465,12 +407,15 @@ __device__ __forceinline__ bool improves_add(const St &st, int32_t d, int32_t k)
     const double n1 = __builtin_fma(2.0 * x, q, -(ay * (6.0 + y)) * p);
     const double r = 2.0 + y, u = __builtin_fma(4.0, x, 6.0);
     const double n2 = __builtin_fma(x * (6.0 + x), r, -2.0 * ay * u);
-    const bool small = x <= 1024.0;
-    if (small && n1 > kCert * (p * q))
+    const bool yes = n1 > kCert * (p * q), no = n2 < -kCert * (r * u);
+    return x <= 1024.0 ? (yes ? 1 : no ? 0 : -1) : -1;
+}
+
+__device__ __forceinline__ bool improves_add(const St &st, int32_t d, int32_t k) {
+    if (st.K == 0)
         return true;
-    if (small && n2 < -kCert * (r * u))
-        return false;
-    return decide(st.K, st.V, st.K + 2 * (int64_t)d, st.V + k, st.alpha);
+    const int t = settle_add(st, d, k);
+    return t >= 0 ? t != 0 : decide(st.K, st.V, st.K + 2 * (int64_t)d, st.V + k, st.alpha);
 }
 
 // Would removing a member with internal weight d and degree k raise f?  The
@@ -793,6 +738,23 @@ __device__ __forceinline__ int32_t record_len(const Records &rec, int64_t r) {
     return rec.drem[r] < 0 ? rec.cnt[r] : rec.dadd[r] + rec.drem[r];
 }
 
+// Scales that a set did not reach (its start lies outside an overflowed
+// pool, or an error ended it) get records that no later launch of the same
+// sweep takes for lists: a per-scale loop reads every record of the scale
+// before, and what the memory held earlier could name any ids.  Every calling
+// thread stores the same values.
+__device__ __forceinline__ void void_records(const SweepArgs &A, int32_t set, int32_t s_from) {
+    for (int32_t s = s_from; s < A.s_end; ++s) {
+        const int64_t r = (int64_t)set * A.S + s;
+        A.rec.off[r] = -1;
+        A.rec.cnt[r] = 0;
+        if (A.rec.drem) {
+            A.rec.dadd[r] = 0;
+            A.rec.drem[r] = -1;
+        }
+    }
+}
+
 // Delta output, one wave: rebuild in the table the members recorded for
 // scale s_last by toggling kMember | kWas for every id of the last full
 // list and of each delta after it (an id joins and leaves alternately, so
@@ -829,14 +791,7 @@ __device__ bool wave_toggle_records(const SweepArgs &A, const Tab &t, St &st, co
 
 template <bool GLOBAL, bool PERSET>
 __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
-    Ctx c;
-    c.row_ptr = A.g.row_ptr;
-    c.col = A.g.col;
-    c.w = A.g.w;
-    c.kdeg = A.g.kdeg;
-    c.logtab = A.g.logtab;
-    c.logtab_last = A.g.logtab_n - 1;
-    c.n = A.g.n;
+    const Ctx c = make_ctx(A.g);
     const uint32_t n_items = A.tier == 0 ? (uint32_t)A.n_sets : A.ctl->ovf_count[A.in_from];
     // What one item leaves for the device-wide counters is published by
     // lane 0 at the top of the next iteration, in the same lane-0 block that
@@ -863,7 +818,7 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
                 }
                 if (pend_err)
                     atomicOr(A.err, pend_err);
-                unsigned long long *sx = A.stat + kStatWords * A.tier;
+                unsigned long long *sx = A.stat + kStatWords * A.stat_slot;
                 for (int q = 0; q < kStatWords; ++q)
                     if (q >= 6 || !pend_ovf)
                         atomicAdd(&sx[q], (unsigned long long)pend_stat[q]);
@@ -1116,6 +1071,8 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
             st.c_ins = st.inserted - st.ins_mark;
             st.emitted = true;
         }
+        if (bad || st.err || (st.ovf && !A.work_out))
+            void_records(A, set, s_at);
         pend = true;
         pend_ovf = st.ovf;
         pend_push = (uint32_t)(set * A.S + s_at);
@@ -1156,7 +1113,7 @@ __global__ void __launch_bounds__(256) sweep_global_kernel(SweepArgs A) {
     const int slot = blockIdx.x * (blockDim.x >> 6) + wave;
     if (slot >= A.n_slots)
         return;
-    Tab t = carve_global(A.gtab + (int64_t)slot * A.gtab_stride, A.cap, A.hbits);
+    Tab t = carve(A.gtab + (int64_t)slot * A.gtab_stride, A.cap, A.hbits);
     run_wave<true, false>(A, t, lane);
 }
 
@@ -1176,7 +1133,7 @@ __global__ void __launch_bounds__(256) query_global_kernel(SweepArgs A) {
     const int slot = blockIdx.x * (blockDim.x >> 6) + wave;
     if (slot >= A.n_slots)
         return;
-    Tab t = carve_global(A.gtab + (int64_t)slot * A.gtab_stride, A.cap, A.hbits);
+    Tab t = carve(A.gtab + (int64_t)slot * A.gtab_stride, A.cap, A.hbits);
     run_wave<true, true>(A, t, lane);
 }
 
@@ -1197,27 +1154,38 @@ constexpr int kBuckets = 256;
 struct TeamSh {
     double r[kTeamMaxWaves];
     int32_t u[kTeamMaxWaves];
-    int32_t i[kTeamMaxWaves];
     unsigned long long v[kTeamMaxWaves];
     unsigned long long off;
-    int32_t count;    // dense entries claimed (may pass cap on overflow)
+    // what a row leaves behind, read together after its barrier
+    struct __align__(16) Row {
+        int32_t count;    // dense entries claimed (may pass cap on overflow)
+        int32_t flen;     // fresh-list appends (may pass the capacity)
+        uint32_t ovf;
+        uint32_t stop;
+    } row;
     int32_t m;        // members gathered for emission
     int32_t m2;       // delta output: ids that left, gathered for emission
-    int32_t bidx;     // broadcast dense index
     uint32_t item;
-    uint32_t ovf;
-    uint32_t stop;
     uint32_t abort;
-    // rank-bucketed queue (global tables)
-    int32_t flen;                       // fresh-list appends (may pass the capacity)
-    uint32_t ev;                        // the chosen addition's d|flags and degree
-    int32_t ek;
-    int32_t bstart[kBuckets + 1];       // queue positions of each bucket
-    uint32_t fill[kBuckets];            // bucket counts, then fill cursors
-    double r2[2 * kTeamMaxWaves];       // more reduction slots
-    int32_t u2[2 * kTeamMaxWaves];
-    int32_t i2[2 * kTeamMaxWaves];
+    union {
+        struct {
+            int32_t bstart[kBuckets + 1];   // queue positions of each bucket
+            uint32_t fill[kBuckets];        // bucket counts, then fill cursors
+        };
+        int32_t resv[2 * kBuckets];     // (id, entry) of a claiming thread (initialisation)
+    };
+    double r2[kTeamMaxWaves];
+    // the waves' candidates, two sets used in turn (a
+    // set is written again only after a barrier that every reader has passed)
+    struct Slot {
+        double r;
+        int32_t u, i;
+        uint32_t v;
+        int32_t k, beg;
+    } slot[2][kTeamMaxWaves];
+    int32_t done;     // waves whose rows are finished (initialisation)
 };
+static_assert(sizeof(TeamSh) <= kTeamShBytes, "the tier sizes count the workgroup's own LDS");
 
 struct TeamId {
     int tid, nt, lane, wid, nw;
@@ -1252,144 +1220,13 @@ __device__ __forceinline__ uint32_t team_or(TeamSh &sh, const TeamId &id, uint32
 __device__ __forceinline__ bool team_over_budget(TeamSh &sh, const TeamId &id, St &st) {
     __syncthreads();
     if (id.tid == 0 && wall_clock64() - st.t0 > st.budget)
-        sh.stop = 1u;
+        sh.row.stop = 1u;
     __syncthreads();
-    if (sh.stop) {
+    if (sh.row.stop) {
         st.err |= ERR_TIMEOUT;
         return true;
     }
     return false;
-}
-
-// Dense index of u for every active thread, inserting absent ids (all
-// active ids of one call are distinct).  All probes finish before any
-// insert.  On overflow sh.ovf is set (read it after the call).
-template <bool GLOBAL>
-__device__ int32_t team_ensure(const Tab &t, TeamSh &sh, St &st, const Ctx &c, bool act, int32_t u) {
-    int32_t idx = act ? tab_find<GLOBAL>(t, u, st.err) : -1;
-    __syncthreads();
-    if (act && idx < 0) {
-        const int32_t k = atomicAdd(&sh.count, 1);
-        if (k >= t.cap) {
-            atomicOr(&sh.ovf, 1u);
-        } else {
-            idx = k;
-            t.NODE(idx) = u;
-            t.KV(idx) = c.kdeg[u];
-            t.DV(idx) = 0u;
-            st.inserted += 1;
-            tab_slot_insert<GLOBAL>(t, u, idx, st.err);
-        }
-    }
-    __syncthreads();
-    return idx;
-}
-
-// bqm: the table's queue is the rank-bucketed one (global tables only);
-// otherwise pops are applied lazily, by the next table scan.
-template <bool GLOBAL, int MODE>
-__device__ void team_row(const Tab &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, int32_t n,
-                         bool bqm = false) {
-    const int32_t beg = c.row_ptr[n];
-    const int32_t end = c.row_ptr[n + 1];
-    st.rows += 1;
-    st.row_len += (uint64_t)(end - beg);
-    if constexpr (MODE != ROW_INIT) {
-        st.mrows += 1;
-        st.mrow_len += (uint64_t)(end - beg);
-    }
-    for (int32_t base = beg; base < end; base += id.nt) {
-        const int32_t j = base + id.tid;
-        const bool act = j < end;
-        const int32_t u = act ? c.col[j] : 0;
-        const int32_t wt = act ? (c.w ? (int32_t)c.w[j] : 1) : 0;
-        int32_t idx;
-        if constexpr (MODE == ROW_REMOVE) {
-            idx = act ? tab_find<GLOBAL>(t, u, st.err) : -1;
-            if (act && idx < 0)
-                st.err |= ERR_MISSING;
-        } else {
-            idx = team_ensure<GLOBAL>(t, sh, st, c, act, u);
-            if (sh.ovf) {
-                st.ovf = true;
-                return;
-            }
-        }
-        if (act && idx >= 0) {
-            const uint32_t v = t.DV(idx);
-            int32_t d = (int32_t)(v & kDMask);
-            if constexpr (MODE == ROW_REMOVE) {
-                d -= wt;
-                t.DV(idx) = (v & ~kDMask) | (uint32_t)d;
-            } else if constexpr (MODE == ROW_INIT) {
-                d += wt;
-                t.DV(idx) = (v & ~kDMask) | (uint32_t)d;
-            } else {
-                d += wt;
-                if (v & kMember) {
-                    t.DV(idx) = (v & ~kDMask) | (uint32_t)d;
-                } else if (GLOBAL && bqm) {
-                    // bucketed queue: queue entries are popped eagerly (flag
-                    // cleared); fresh-list entries ranked above the addition
-                    // just made were popped before it, which the next
-                    // fresh-list scan applies.  An entry whose rank changes
-                    // moves to the fresh list (its queue slot is stale while
-                    // kFresh is set), marked kTouch until that scan.
-                    const bool popped = !(v & kLive) || ((v & kFresh) && before(t.RK(idx), u, st.pr, st.pu));
-                    if (popped)
-                        st.Gl += 1;
-                    const int32_t k = t.KV(idx);
-                    t.RK(idx) = rank_of(c, d, k, st.alpha);
-                    st.Rl += 1;
-                    if (!(v & kFresh)) {
-                        const int32_t pos = atomicAdd(&sh.flen, 1);
-                        if (pos < t.cap)
-                            t.fr[pos] = idx;
-                    }
-                    t.DV(idx) = (v & kWas) | (uint32_t)d | kLive | kFresh | kTouch;
-                } else {
-                    const bool queued = (v & kLive) && !before(t.RK(idx), u, st.pr, st.pu);
-                    if (!queued)
-                        st.Gl += 1;
-                    const int32_t k = t.KV(idx);
-                    t.RK(idx) = rank_of(c, d, k, st.alpha);
-                    st.Rl += 1;
-                    t.DV(idx) = (v & kWas) | (uint32_t)d | kLive | kFresh;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    st.count = min(sh.count, t.cap);
-}
-
-// Block argmax of (rank, -id); also reads d|flags and k of the winner
-// before the closing barrier, so that thread 0 may update the winner's flags
-// right after it without another barrier.
-__device__ __forceinline__ void team_pick_max(TeamSh &sh, const TeamId &id, const Tab &t, double &r,
-                                              int32_t &u, int32_t &i, uint32_t &v, int32_t &k) {
-    wave_argmax(r, u, i);
-    if (id.lane == 0) {
-        sh.r[id.wid] = r;
-        sh.u[id.wid] = u;
-        sh.i[id.wid] = i;
-    }
-    __syncthreads();
-    r = sh.r[0];
-    u = sh.u[0];
-    i = sh.i[0];
-    for (int w = 1; w < id.nw; ++w) {
-        if (before(sh.r[w], sh.u[w], r, u)) {
-            r = sh.r[w];
-            u = sh.u[w];
-            i = sh.i[w];
-        }
-    }
-    if (i >= 0) {
-        v = t.DV(i);
-        k = t.KV(i);
-    }
-    __syncthreads();
 }
 
 // Workgroup minimum of v (every thread gets it).
@@ -1405,151 +1242,28 @@ __device__ __forceinline__ int32_t team_min_i32(TeamSh &sh, const TeamId &id, in
     return v;
 }
 
-__device__ __forceinline__ void team_pick_min(TeamSh &sh, const TeamId &id, const Tab &t, int32_t &u,
-                                              int32_t &i, uint32_t &v, int32_t &k) {
-    wave_argmin(u, i);
-    if (id.lane == 0) {
-        sh.u[id.wid] = u;
-        sh.i[id.wid] = i;
-    }
-    __syncthreads();
-    u = sh.u[0];
-    i = sh.i[0];
-    for (int w = 1; w < id.nw; ++w) {
-        if (sh.u[w] < u) {
-            u = sh.u[w];
-            i = sh.i[w];
-        }
-    }
-    if (i >= 0) {
-        v = t.DV(i);
-        k = t.KV(i);
-    }
-    __syncthreads();
-}
-
 // Entries each thread loads ahead in a table scan (independent loads in
 // flight per thread; the scans are latency-bound).
 constexpr int kScanAhead = 4;
 
-// Removal passes of one growth call over the whole table: members in
-// ascending id, each removal applied at once.  False when the call must
-// end early (move limit, budget).
-template <bool GLOBAL>
-__device__ bool removal_scan(const Tab &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
-                             uint32_t k_prune, int64_t &moves) {
-    for (uint32_t pass = 0; k_prune == 0 || pass < k_prune; ++pass) {
-        st.Gu += (uint64_t)st.nmem;
-        int32_t cursor = -1;
-        bool removed = false;
-        for (;;) {
-            int32_t cu = INT32_MAX;
-            int32_t ci = -1;
-            st.scanned += (uint64_t)st.count;
-            for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
-                uint32_t vv[kScanAhead];
-                int32_t nn[kScanAhead], kk[kScanAhead];
-#pragma unroll
-                for (int q = 0; q < kScanAhead; ++q) {
-                    const int32_t i = base + q * id.nt;
-                    vv[q] = 0u;
-                    nn[q] = 0;
-                    kk[q] = 0;
-                    if (i < st.count) {
-                        vv[q] = t.DV(i);
-                        nn[q] = t.NODE(i);
-                        kk[q] = t.KV(i);
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < kScanAhead; ++q) {
-                    const int32_t i = base + q * id.nt;
-                    if (i >= st.count || !(vv[q] & kMember))
-                        continue;
-                    const int32_t u = nn[q];
-                    if (u <= cursor || u >= cu)
-                        continue;
-                    if (improves_remove(st, (int32_t)(vv[q] & kDMask), kk[q])) {
-                        cu = u;
-                        ci = i;
-                    }
-                }
-            }
-            uint32_t v = 0;
-            int32_t k = 0;
-            team_pick_min(sh, id, t, cu, ci, v, k);
-            if (ci < 0)
-                break;
-            const int32_t d = (int32_t)(v & kDMask);
-            if (id.tid == 0)
-                t.DV(ci) = v & ~kMember;
-            st.K -= 2 * (int64_t)d;
-            st.V -= k;
-            st.nmem -= 1;
-            st.M += 1;
-            moves += 1;
-            set_rates(st);
-            team_row<GLOBAL, ROW_REMOVE>(t, sh, st, c, id, cu);
-            removed = true;
-            cursor = cu;
-            if ((int64_t)st.M > st.move_limit) {
-                st.err |= ERR_LIMIT;
-                return false;
-            }
-            if ((st.M & 15) == 0 && team_over_budget(sh, id, st))
-                return false;
-        }
-        if (!removed)
-            break;
-    }
-    return true;
-}
-
 // ---------------------------------------------------------------------------
-// Growth on a global-memory table with a rank-bucketed queue.
+// The queue of a workgroup's growth call.
 //
 // A table of thousands of entries makes a full scan per addition the cost
-// that dominates (a community adding A nodes scans its table A times).  For
-// global tables the queue is therefore kept ordered enough that a step only
-// looks at its head:
+// that dominates (a community adding A nodes scans its table A times).  The
+// queue is therefore kept ordered enough that a step only looks at its head:
 //   * the queue: every queued entry's index, counting-sorted into kBuckets
 //     rank buckets (bucket(r) is monotone non-increasing in r, so every
 //     entry of a later bucket ranks strictly below every entry of an earlier
-//     one); positions before q.cp hold only popped entries;
+//     one); positions before cp hold only popped entries;
 //   * the fresh list: entries re-ranked by an addition since the queue was
 //     built (flag kFresh; their queue slot is stale);
-//   * a step takes the best improving fresh entry and walks the queue from
-//     q.cp in windows of whole buckets (the best improving entry of a window
-//     is the first improving entry of the queue, if it ranks above the fresh
-//     candidate; a window with no improving entry ranked above the fresh
-//     candidate is popped whole), so it pops exactly the entries the
-//     sequential queue pops;
-//   * the queue is rebuilt (three table passes, read in order) when the
-//     fresh list grows past max(512, entries / 32): a rebuild costs fewer
-//     bytes than the random reads of a longer fresh list.
-// Removal passes walk a list of the members instead of the whole table.
-// Same decisions, counters and results as the scan-driven additions.
+//   * a step takes the best improving entry of the fresh list and of windows
+//     of whole buckets from the queue's head, and pops exactly the entries
+//     that the sequential queue pops;
+//   * the queue is rebuilt when the fresh list grows long.
+// Same decisions, counters and results as the scan-driven additions of a wave.
 // ---------------------------------------------------------------------------
-struct BQ {
-    double rtop;     // rank of bucket 0's upper end
-    double scale;    // buckets per unit of rank
-    int32_t ns;      // entries in the bucketed queue
-    int32_t cp;      // queue positions before cp hold only popped entries
-};
-
-__device__ __forceinline__ int32_t bucket_of(double r, const BQ &q) {
-    const double x = (q.rtop - r) * q.scale;
-    if (!(x > 0.0))
-        return 0;
-    if (x >= (double)(kBuckets - 1))
-        return kBuckets - 1;
-    return (int32_t)x;
-}
-
-// true when (r, u) pops after (pr, pu)
-__device__ __forceinline__ bool pops_after(double r, int32_t u, double pr, int32_t pu) {
-    return before(pr, pu, r, u);
-}
 
 // largest b in [lo, hi] with bstart[b] <= pos (bstart non-decreasing, bstart[lo] <= pos)
 __device__ __forceinline__ int32_t bucket_at(const TeamSh &sh, int32_t lo, int32_t hi, int32_t pos) {
@@ -1563,147 +1277,799 @@ __device__ __forceinline__ int32_t bucket_at(const TeamSh &sh, int32_t lo, int32
     return lo;
 }
 
-// Team argmax of (r, u, i) plus the team minimum and maximum of lo and hi.
-__device__ __forceinline__ void team_max_range(TeamSh &sh, const TeamId &id, double &r, int32_t &u, int32_t &i,
-                                               double &lo, double &hi) {
-    wave_argmax(r, u, i);
-    lo = -wave_max(-lo);
-    hi = wave_max(hi);
-    if (id.lane == 0) {
-        sh.r[id.wid] = r;
-        sh.u[id.wid] = u;
-        sh.i[id.wid] = i;
-        sh.r2[id.wid] = lo;
-        sh.r2[kTeamMaxWaves + id.wid] = hi;
+// ---------------------------------------------------------------------------
+// Workgroup tables.
+//
+// A step of a community is a chain of dependent accesses, and the chain's
+// length is its time: what a step follows is laid out so that each hop is one
+// access.
+//   * the hash: 32-bit slots of a tag over an entry index, read four at a time
+//     (a wave waits for its lane with the longest probe, so slot-by-slot
+//     probing cost a row eight and more rounds);
+//   * an entry's fields (d|flags, node, degree, row start, rank) lie together
+//     and are read together;
+//   * the bucketed queue (above) and its fresh list, entry indices,
+//     sorted when a growth call starts;
+//   * a copy of the first logs of the table L in LDS;
+//   * a row is read from adjacency records that carry the neighbour's degree,
+//     its log and its row start beside its id.
+// Layouts:
+//   T_LDS: everything in LDS (16-bit queue indices).  32 bytes per entry, so
+//     one to a few communities share a compute unit: for launches of few
+//     communities, where one community's chain is the time.
+//   T_PACK: hash, 32-byte records and queue in global memory, 16-bit tag and
+//     index, 16-bit queue indices: tables below kRecordMinEntries entries.
+//   T_WIDE: the same with 32-bit queue indices and as many index bits in a
+//     hash slot as the table needs.
+// ---------------------------------------------------------------------------
+enum { T_LDS = 0, T_PACK = 1, T_WIDE = 2 };
+
+template <int L>
+struct BTab {
+    static constexpr bool G = L != T_LDS;
+    using Q = std::conditional_t<L == T_WIDE, uint32_t, uint16_t>;
+    double *lt;        // L(x) for x < kBlockLogs (LDS)
+    uint32_t *hw;      // hash slots: tag over entry index
+    Q *sq;             // queue, cap entry indices, then the fresh list
+    double *rk;        // T_LDS: entries as arrays
+    int32_t *node, *kv, *beg;
+    uint32_t *dv;
+    char *rec;         // else: records {d|flags, node, degree, row start, rank, hash slot}
+    int32_t *scr;      // scratch i32[cap] (emission, resume, removal): T_LDS the ranks'
+                       // place, which hold nothing once a call's additions are over
+    uint32_t hmask;
+    int hbits, ibits;  // ibits: index bits of a hash slot, T_WIDE (16 otherwise)
+    int cap;
+    int fmax;          // fresh-list entries kept
+    __device__ __forceinline__ char *at(int32_t i) const { return rec + (size_t)(uint32_t)i * kRecordBytes; }
+    __device__ __forceinline__ double &RK(int32_t i) const {
+        return G ? *(double *)(at(i) + 16) : rk[i];
     }
-    __syncthreads();
-    r = sh.r[0];
-    u = sh.u[0];
-    i = sh.i[0];
-    lo = sh.r2[0];
-    hi = sh.r2[kTeamMaxWaves];
-    for (int w = 1; w < id.nw; ++w) {
-        if (before(sh.r[w], sh.u[w], r, u)) {
-            r = sh.r[w];
-            u = sh.u[w];
-            i = sh.i[w];
-        }
-        lo = fmin(lo, sh.r2[w]);
-        hi = fmax(hi, sh.r2[kTeamMaxWaves + w]);
+    __device__ __forceinline__ uint32_t &DV(int32_t i) const { return G ? *(uint32_t *)at(i) : dv[i]; }
+    __device__ __forceinline__ int32_t &NODE(int32_t i) const { return G ? *(int32_t *)(at(i) + 4) : node[i]; }
+    __device__ __forceinline__ int32_t &KV(int32_t i) const { return G ? *(int32_t *)(at(i) + 8) : kv[i]; }
+    __device__ __forceinline__ uint32_t &SLOT(int32_t i) const { return *(uint32_t *)(at(i) + 24); }
+    __device__ __forceinline__ int shift() const { return L == T_WIDE ? ibits : 16; }
+};
+
+// One entry's fields.
+struct Ent {
+    uint32_t v;
+    int32_t u, k, beg;
+    double r;
+};
+
+template <int L>
+__device__ __forceinline__ Ent ent_get(const BTab<L> &t, int32_t i) {
+    Ent e;
+    if constexpr (L != T_LDS) {
+        const char *p = t.at(i);
+        const int4 a = *(const int4 *)p;
+        e.v = (uint32_t)a.x;
+        e.u = a.y;
+        e.k = a.z;
+        e.beg = a.w;
+        e.r = *(const double *)(p + 16);
+    } else {
+        e.v = t.dv[i];
+        e.u = t.node[i];
+        e.k = t.kv[i];
+        e.beg = t.beg[i];
+        e.r = t.rk[i];
     }
-    __syncthreads();
+    return e;
 }
 
-// Team reduction of one queue window: the best improving fresh entry (f),
-// the best improving window entry (w) and the window entry that pops last
-// (m; mi < 0: none).
-__device__ __forceinline__ void team_window(TeamSh &sh, const TeamId &id, double &fr, int32_t &fu, int32_t &fi,
-                                            double &wr, int32_t &wu, int32_t &wi, double &mr, int32_t &mi,
-                                            int32_t &mu) {
-    wave_argmax(fr, fu, fi);
-    wave_argmax(wr, wu, wi);
-    // the entry that pops last is the first one in the reversed order
-    mr = -mr;
-    mu = -1 - mu;
-    wave_argmax(mr, mu, mi);
-    mr = -mr;
-    mu = -1 - mu;
-    if (id.lane == 0) {
-        sh.r[id.wid] = fr;
-        sh.u[id.wid] = fu;
-        sh.i[id.wid] = fi;
-        sh.r2[id.wid] = wr;
-        sh.u2[id.wid] = wu;
-        sh.i2[id.wid] = wi;
-        sh.r2[kTeamMaxWaves + id.wid] = mr;
-        sh.u2[kTeamMaxWaves + id.wid] = mu;
-        sh.i2[kTeamMaxWaves + id.wid] = mi;
+// A new entry with d = 0 (its rank follows with its first re-rank).
+template <int L>
+__device__ __forceinline__ void ent_new(const BTab<L> &t, int32_t i, int32_t u, int32_t k, int32_t beg) {
+    if constexpr (L != T_LDS) {
+        *(int4 *)t.at(i) = make_int4(0, u, k, beg);
+    } else {
+        t.dv[i] = 0u;
+        t.node[i] = u;
+        t.kv[i] = k;
+        t.beg[i] = beg;
     }
-    __syncthreads();
-    fr = sh.r[0];
-    fu = sh.u[0];
-    fi = sh.i[0];
-    wr = sh.r2[0];
-    wu = sh.u2[0];
-    wi = sh.i2[0];
-    mr = sh.r2[kTeamMaxWaves];
-    mu = sh.u2[kTeamMaxWaves];
-    mi = sh.i2[kTeamMaxWaves];
-    for (int w = 1; w < id.nw; ++w) {
-        if (before(sh.r[w], sh.u[w], fr, fu)) {
-            fr = sh.r[w];
-            fu = sh.u[w];
-            fi = sh.i[w];
-        }
-        if (before(sh.r2[w], sh.u2[w], wr, wu)) {
-            wr = sh.r2[w];
-            wu = sh.u2[w];
-            wi = sh.i2[w];
-        }
-        const int32_t i2 = sh.i2[kTeamMaxWaves + w];
-        const double r2 = sh.r2[kTeamMaxWaves + w];
-        const int32_t u2 = sh.u2[kTeamMaxWaves + w];
-        if (i2 >= 0 && (mi < 0 || pops_after(r2, u2, mr, mu))) {
-            mr = r2;
-            mu = u2;
-            mi = i2;
-        }
-    }
-    __syncthreads();
 }
 
-// Which queued entries a build pops first: those that pop before the last
-// addition (pr, pu) and were not re-ranked by it.  After lazy-scan
-// additions that is an entry without kFresh; in the bucketed queue, a
-// fresh-list entry without kTouch.
-enum { POP_LAZY_SCAN = 1, POP_FRESH_LIST = 2 };
-
-__device__ __forceinline__ bool build_pops(uint32_t v, int pop_mode) {
-    if (pop_mode == POP_LAZY_SCAN)
-        return !(v & kFresh);
-    if (pop_mode == POP_FRESH_LIST)
-        return (v & kFresh) && !(v & kTouch);
-    return false;
+__device__ __forceinline__ BTab<T_LDS> carve_lds(char *lds, int cap, int hbits) {
+    BTab<T_LDS> t;
+    t.lt = (double *)lds;
+    t.hw = (uint32_t *)(t.lt + kBlockLogs);
+    t.rk = (double *)(t.hw + ((size_t)1 << hbits));
+    t.node = (int32_t *)(t.rk + cap);
+    t.dv = (uint32_t *)(t.node + cap);
+    t.kv = t.node + 2 * cap;
+    t.beg = t.node + 3 * cap;
+    t.sq = (uint16_t *)(t.node + 4 * cap);
+    t.scr = (int32_t *)t.rk;
+    t.rec = nullptr;
+    t.hmask = (1u << hbits) - 1;
+    t.hbits = hbits;
+    t.ibits = 16;
+    t.cap = cap;
+    t.fmax = kFreshMax;
+    return t;
 }
 
-// Counting-sort the queued entries into rank buckets, ranks in [rbot, rtop].
-// Entries that build_pops names and that pop before (pr, pu) are popped
-// instead.  Clears every kFresh and kTouch flag and empties the fresh list.
-__device__ void bq_build(const Tab &t, TeamSh &sh, St &st, const TeamId &id, BQ &q, double rtop,
-                         double rbot, int pop_mode, double pr, int32_t pu) {
-    q.rtop = rtop;
-    q.scale = rtop > rbot ? (double)kBuckets / (rtop - rbot) : 0.0;
-    st.scanned += 2 * (uint64_t)st.count;
-    for (int32_t b = id.tid; b < kBuckets; b += id.nt)
-        sh.fill[b] = 0u;
+// Table `slot` of a slab: the hashes of all its tables come first, so that one
+// fill empties them.
+template <int L>
+__device__ __forceinline__ BTab<L> carve_slab(char *slab, int64_t stride, int32_t n_slots, int slot, double *lt,
+                                              int cap, int hbits) {
+    BTab<L> t;
+    t.lt = lt;
+    t.hw = (uint32_t *)(slab + ((size_t)slot << (hbits + 2)));
+    char *p = slab + ((size_t)n_slots << (hbits + 2)) + (size_t)slot * stride;
+    t.rec = p;
+    t.scr = (int32_t *)(p + (size_t)cap * kRecordBytes);
+    t.sq = (typename BTab<L>::Q *)(t.scr + cap);
+    t.rk = nullptr;
+    t.node = t.kv = t.beg = nullptr;
+    t.dv = nullptr;
+    t.hmask = (1u << hbits) - 1;
+    t.hbits = hbits;
+    t.ibits = 33 - __builtin_clz((uint32_t)cap - 1);   // an index and the claim bit
+    t.cap = cap;
+    t.fmax = fresh_max(cap);
+    return t;
+}
+
+constexpr uint32_t kNoSlot = 0xffffffffu;  // an empty hash slot (no entry has the largest index)
+
+// Index field of a slot that a thread has claimed, see block_edges.
+template <int L>
+__device__ __forceinline__ uint32_t claim_bit(const BTab<L> &t) { return 1u << (t.shift() - 1); }
+
+template <int L>
+__device__ __forceinline__ uint32_t index_mask(const BTab<L> &t) { return (1u << t.shift()) - 1u; }
+
+// LDS operations of one wave take effect in order; the compiler must keep
+// theirs.
+__device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
+
+// Reads and writes that other threads' LDS operations may meet in between.
+template <class V>
+__device__ __forceinline__ V lds_get(const V *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class V>
+__device__ __forceinline__ void lds_put(V *p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The slots of id u start at a group of four; its tag is the hash's low bits.
+__device__ __forceinline__ uint32_t hash_mul(int32_t u) { return (uint32_t)u * 2654435761u; }
+
+template <int L>
+__device__ __forceinline__ uint32_t group_of(const BTab<L> &t, uint32_t h) {
+    return (h >> (32 - t.hbits)) & ~3u;
+}
+
+// A group.  Global slots change by compare-and-swap in the L2, so they are read
+// from there.
+template <int L>
+__device__ __forceinline__ uint4 group_get(const BTab<L> &t, uint32_t p) {
+    if constexpr (L != T_LDS) {
+        const uint64_t *q = (const uint64_t *)(t.hw + p);
+        const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
+    } else {
+        return *(const uint4 *)(t.hw + p);
+    }
+}
+
+template <int L>
+__device__ __forceinline__ void slot_put(const BTab<L> &t, uint32_t p, uint32_t v) {
+    __hip_atomic_store(t.hw + p, v, __ATOMIC_RELAXED, L != T_LDS ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Before a hash slot is written that another wave may follow, and after one
+// was read: what it leads to is seen whole.
+template <int L>
+__device__ __forceinline__ void slot_release() {
+    if constexpr (L != T_LDS)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    else
+        lds_order();
+}
+
+template <int L>
+__device__ __forceinline__ void slot_acquire() {
+    if constexpr (L != T_LDS)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+__device__ __forceinline__ uint32_t slot_of(const uint4 &g, int j) {
+    return j == 0 ? g.x : j == 1 ? g.y : j == 2 ? g.z : g.w;
+}
+
+// Bits of the slots of a group that are empty / that carry the tag.
+__device__ __forceinline__ uint32_t group_empty(const uint4 &g) {
+    return (g.x == kNoSlot ? 1u : 0u) | (g.y == kNoSlot ? 2u : 0u) | (g.z == kNoSlot ? 4u : 0u) |
+           (g.w == kNoSlot ? 8u : 0u);
+}
+
+__device__ __forceinline__ uint32_t group_tagged(const uint4 &g, uint32_t h, int shift) {
+    const uint32_t tag = h << shift;
+    return ((g.x ^ tag) >> shift == 0u ? 1u : 0u) | ((g.y ^ tag) >> shift == 0u ? 2u : 0u) |
+           ((g.z ^ tag) >> shift == 0u ? 4u : 0u) | ((g.w ^ tag) >> shift == 0u ? 8u : 0u);
+}
+
+// The entry of u and its fields, or idx = -1 and the first empty slot of its
+// probe (kNoSlot: none left).  Slots of an id's probe fill in order and are
+// never emptied, so a lookup ends at the first empty one.
+template <int L>
+__device__ __forceinline__ void block_find(const BTab<L> &t, int32_t u, int32_t &idx, uint32_t &slot, Ent &e) {
+    const uint32_t h = hash_mul(u);
+    uint32_t p = group_of(t, h);
+    idx = -1;
+    slot = kNoSlot;
+    for (uint32_t it = 0; it <= t.hmask; it += 4) {
+        const uint4 g = group_get(t, p);
+        const uint32_t room = group_empty(g);
+        uint32_t m = group_tagged(g, h, t.shift()) & ~room;
+        slot_acquire<L>();
+        while (m) {
+            const int32_t i = (int32_t)(slot_of(g, __builtin_ctz(m)) & index_mask(t));
+            e = ent_get(t, i);
+            if (e.u == u) {
+                idx = i;
+                return;
+            }
+            m &= m - 1;
+        }
+        if (room) {
+            slot = p + (uint32_t)__builtin_ctz(room);
+            return;
+        }
+        p = (p + 4) & t.hmask;
+    }
+}
+
+// Put v into the first empty slot at or after p, its place or kNoSlot.
+template <int L>
+__device__ __forceinline__ uint32_t block_claim(const BTab<L> &t, uint32_t p, uint32_t v) {
+    if (p == kNoSlot)
+        return kNoSlot;
+    for (uint32_t it = 0; it <= t.hmask; ++it) {
+        if (atomicCAS(&t.hw[p], kNoSlot, v) == kNoSlot)
+            return p;
+        p = (p + 1) & t.hmask;
+    }
+    return kNoSlot;
+}
+
+// L(x): small arguments from the LDS copy of the table.
+template <int L>
+__device__ __forceinline__ double block_log(const BTab<L> &t, const Ctx &c, int32_t x) {
+    // (two loads of one kind would become one flat load of either memory)
+    if (x < kBlockLogs)
+        return lds_get(&t.lt[x]);
+    return c.logtab[min(x, c.logtab_last)];
+}
+
+// A directed entry: neighbour, its degree, its row start, the edge's weight,
+// the log of the degree.
+struct Edge {
+    int4 e;
+    double lk;
+};
+
+__device__ __forceinline__ Edge edge_at(const Ctx &c, int32_t j) {
+    Edge x;
+    if (c.adj) {
+        x.e = c.adj[j];
+        x.lk = c.adjl[j];
+        return x;
+    }
+    const int32_t u = c.col[j];
+    const int2 in = c.info[u];
+    x.e = make_int4(u, in.y, in.x, c.w ? (int32_t)c.w[j] : 1);
+    x.lk = c.logtab[min(in.y, c.logtab_last)];
+    return x;
+}
+
+__device__ __forceinline__ Edge no_edge() {
+    Edge x;
+    x.e = make_int4(0, 0, 0, 0);
+    x.lk = 0.0;
+    return x;
+}
+
+// Create the entries of the lanes that need one (ids distinct in the
+// workgroup, slot from block_find): index, fields with d = 0, then the hash
+// slot, so that another wave's lookup sees no slot or a whole entry.  solo:
+// only this wave adds entries before the next barrier.  A full table sets
+// sh.row.ovf (idx stays -1).
+template <int L>
+__device__ __forceinline__ void block_add(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id, bool need,
+                                          int32_t u, int32_t k, int32_t beg, uint32_t slot, bool solo,
+                                          int32_t &idx) {
+    const uint64_t m = __ballot(need);
+    if (m == 0)
+        return;
+    int32_t base = st.count;
+    if (solo) {
+        if (id.lane == 0)
+            sh.row.count = base + __popcll(m);
+    } else {
+        const int lead = (int)__builtin_ctzll(m);
+        if (id.lane == lead)
+            base = atomicAdd(&sh.row.count, __popcll(m));
+        base = __builtin_amdgcn_readlane(base, lead);
+    }
+    if (need) {
+        const int32_t at = base + __popcll(m & lanes_below(id.lane));
+        if (at >= t.cap) {
+            sh.row.ovf = 1u;
+        } else {
+            idx = at;
+            ent_new(t, at, u, k, beg);
+            st.inserted += 1;
+        }
+    }
+    if (solo)
+        lds_order();
+    else
+        slot_release<L>();
+    if (need && idx >= 0) {
+        slot = block_claim(t, slot, (hash_mul(u) << t.shift()) | (uint32_t)idx);
+        if (slot == kNoSlot)
+            st.err |= ERR_PROBE;
+        if constexpr (L != T_LDS)
+            t.SLOT(idx) = slot;
+    }
+    lds_order();
+}
+
+// Entries of distinct ids, absent ones created; a barrier at the end (see
+// the Tab version).
+template <int L>
+__device__ int32_t team_ensure(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, bool act,
+                               int32_t u) {
+    int32_t idx = -1;
+    uint32_t slot = kNoSlot;
+    Ent e;
+    if (act)
+        block_find(t, u, idx, slot, e);
+    const bool need = act && idx < 0;
+    const int2 in = need ? c.info[u] : make_int2(0, 0);
+    block_add(t, sh, st, id, need, u, in.y, in.x, slot, false, idx);
+    __syncthreads();
+    return idx;
+}
+
+// Apply the row of node n (row start beg, degree k) as team_row does on the
+// bucketed queue.  The first entries are loaded before the row's end is
+// known: a row holds at most k entries and stays below nnz.
+template <int MODE, int L>
+__device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
+                                          int32_t n, int32_t beg, int32_t k) {
+    int32_t j = beg + id.tid;
+    Edge x = id.tid < k && (int64_t)j < c.nnz ? edge_at(c, j) : no_edge();
+    const int32_t end = __builtin_amdgcn_readfirstlane(c.row_ptr[n + 1]);
+    const bool solo = end - beg <= 64;   // the row is wave 0's alone
+    st.rows += 1;
+    st.row_len += (uint64_t)(end - beg);
+    st.mrows += 1;
+    st.mrow_len += (uint64_t)(end - beg);
+    for (int32_t base = beg; base < end; base += id.nt) {
+        if (base + id.wid * 64 >= end)
+            break;
+        j = base + id.tid;
+        const bool act = j < end;
+        if (base > beg)
+            x = act ? edge_at(c, j) : no_edge();
+        const int4 e = x.e;
+        int32_t idx = -1;
+        uint32_t slot = kNoSlot;
+        Ent a;
+        a.v = 0u;
+        a.r = 0.0;
+        if (act)
+            block_find(t, e.x, idx, slot, a);
+        if constexpr (MODE == ROW_REMOVE) {
+            if (act) {
+                if (idx < 0)
+                    st.err |= ERR_MISSING;
+                else
+                    t.DV(idx) = a.v - (uint32_t)e.w;   // d stays >= 0: the flags above it are untouched
+            }
+        } else {
+            const bool fresh = act && idx < 0;
+            block_add(t, sh, st, id, fresh, e.x, e.y, e.z, slot, solo, idx);
+            bool list = false;
+            if (act && idx >= 0) {
+                const uint32_t v = fresh ? 0u : a.v;
+                const int32_t d = (int32_t)(v & kDMask) + e.w;
+                if (v & kMember) {
+                    t.DV(idx) = (v & ~kDMask) | (uint32_t)d;
+                } else {
+                    // in the queue unless popped (queue entries at once, fresh
+                    // ones by the next scan, see team_row)
+                    const bool popped = !(v & kLive) || ((v & kFresh) && before(a.r, e.x, st.pr, st.pu));
+                    if (popped)
+                        st.Gl += 1;
+                    list = !(v & kFresh);
+                    t.RK(idx) = block_log(t, c, 2 * d) - st.alpha * x.lk;
+                    st.Rl += 1;
+                    t.DV(idx) = (v & kWas) | (uint32_t)d | kLive | kFresh | kTouch;
+                }
+            }
+            // the fresh list; entries past its end are found by the rebuild
+            // that its length then asks for
+            const uint64_t m = __ballot(list);
+            if (m) {
+                int32_t at = st.flen;
+                if (solo) {
+                    if (id.lane == 0)
+                        sh.row.flen = at + __popcll(m);
+                } else {
+                    const int lead = (int)__builtin_ctzll(m);
+                    if (id.lane == lead)
+                        at = atomicAdd(&sh.row.flen, __popcll(m));
+                    at = __builtin_amdgcn_readlane(at, lead);
+                }
+                at += __popcll(m & lanes_below(id.lane));
+                if (list && at < t.fmax)
+                    t.sq[t.cap + at] = (typename BTab<L>::Q)idx;
+            }
+        }
+    }
+    if (id.tid == 0 && (st.M & 15) == 0 && wall_clock64() - st.t0 > st.budget)
+        sh.row.stop = 1u;
+    __syncthreads();
+    const int4 z = *(const int4 *)&sh.row;
+    st.count = __builtin_amdgcn_readfirstlane(min(z.x, t.cap));
+    st.flen = __builtin_amdgcn_readfirstlane(z.y);
+    if constexpr (MODE != ROW_REMOVE)
+        st.ovf = __builtin_amdgcn_readfirstlane(z.z) != 0;
+    if (__builtin_amdgcn_readfirstlane(z.w))
+        st.err |= ERR_TIMEOUT;
+}
+
+// A hash slot's index field against id u: an entry, or the claim of a thread.
+template <int L>
+__device__ __forceinline__ void match_slot(const BTab<L> &t, TeamSh &sh, uint32_t s, int32_t u, int32_t &idx,
+                                           int32_t &dup) {
+    if (s & claim_bit(t)) {
+        const int32_t c = (int32_t)(s & (claim_bit(t) - 1u));
+        if (lds_get(sh.resv + 2 * c) == u)
+            dup = c;
+    } else if (t.NODE((int32_t)s) == u) {
+        idx = (int32_t)s;
+    }
+}
+
+// The edges of the initial members: for every entry of their rows find or
+// create its table entry and add the weight to its d.  Ids repeat, also
+// among the edges in flight: a thread that meets an empty slot claims it
+// with its own number under the id's tag, and another thread that meets the
+// claim compares its id with the claimer's and takes over the entry after
+// the barrier.  Each wave flattens the rows of its share of the members, 64
+// edges at a time.
+template <int L>
+__device__ void block_edges(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
+                            const int32_t *init, int32_t n_init) {
+    const int32_t lanes = min(64, kBuckets / id.nw);   // claims in flight per wave
+    const int32_t q1 = (int32_t)((int64_t)n_init * (id.wid + 1) / id.nw);
+    int32_t q = (int32_t)((int64_t)n_init * id.wid / id.nw);   // next member of this wave
+    int32_t beg = 0, incl = 0, len = 0, total = 0, at = 0;     // the block of members in hand
+    bool counted = false;
+    const int32_t me = id.wid * lanes + id.lane;     // this thread's claim number
+    for (;;) {
+        while (at >= total && q < q1) {
+            // the next (at most) 64 members of the wave: row starts and the
+            // running sum of their lengths
+            const bool has = q + id.lane < q1;
+            const int32_t u = has ? init[q + id.lane] : 0;
+            beg = has ? c.row_ptr[u] : 0;
+            len = has ? c.row_ptr[u + 1] - beg : 0;
+            incl = len;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int32_t x = __shfl_up(incl, off);
+                if (id.lane >= off)
+                    incl += x;
+            }
+            total = __builtin_amdgcn_readlane(incl, 63);
+            st.rows += (uint64_t)min(64, q1 - q);
+            st.row_len += (uint64_t)total;
+            at = 0;
+            q += 64;
+        }
+        const int32_t e = at + id.lane;
+        const bool act = id.lane < lanes && e < total;
+        at += lanes;
+        // the member whose row holds edge e: the first with incl > e
+        int32_t lo = 0;
+#pragma unroll
+        for (int step = 32; step >= 1; step >>= 1) {
+            const int32_t x = __shfl(incl, lo + step - 1);
+            if (x <= e)
+                lo += step;
+        }
+        lo = min(lo, 63);
+        const int32_t row = __shfl(beg, lo), first = __shfl(incl, lo) - __shfl(len, lo);
+        const int4 ed = act ? edge_at(c, row + (e - first)).e : make_int4(0, 0, 0, 0);
+        const int32_t u = ed.x;
+        const uint32_t h = hash_mul(u);
+        int32_t idx = -1, dup = -1;
+        uint32_t mine = kNoSlot;   // the slot this thread claimed
+        if (act) {
+            lds_put(sh.resv + 2 * me, u);
+            lds_put(sh.resv + 2 * me + 1, -1);
+            slot_release<L>();
+            uint32_t p = group_of(t, h);
+            uint32_t from = 0;   // slots of the group already known to be others'
+            uint32_t it = 0;
+            for (; it <= t.hmask; ++it) {
+                const uint4 g = group_get(t, p);
+                uint32_t room = group_empty(g) & ~from;
+                uint32_t m = group_tagged(g, h, t.shift()) & ~group_empty(g);
+                slot_acquire<L>();
+                uint32_t s = 0;
+                int at_slot = -1;   // a slot that was claimed while it was looked at
+                if (room) {
+                    at_slot = __builtin_ctz(room);
+                    // (a match beyond the first empty slot is no match)
+                    m &= (1u << at_slot) - 1u;
+                }
+                while (m && idx < 0 && dup < 0) {
+                    s = slot_of(g, __builtin_ctz(m)) & index_mask(t);
+                    match_slot(t, sh, s, u, idx, dup);
+                    m &= m - 1;
+                }
+                if (idx >= 0 || dup >= 0)
+                    break;
+                if (at_slot >= 0) {
+                    const uint32_t q = p + (uint32_t)at_slot;
+                    const uint32_t old =
+                        atomicCAS(&t.hw[q], kNoSlot, (h << t.shift()) | claim_bit(t) | (uint32_t)me);
+                    if (old == kNoSlot) {
+                        mine = q;
+                        break;
+                    }
+                    slot_acquire<L>();
+                    if ((old ^ (h << t.shift())) >> t.shift() == 0u)
+                        match_slot(t, sh, old & index_mask(t), u, idx, dup);
+                    if (idx >= 0 || dup >= 0)
+                        break;
+                    from |= (2u << at_slot) - 1u;
+                    if (from & 8u) {
+                        from = 0;
+                        p = (p + 4) & t.hmask;
+                    }
+                } else {
+                    from = 0;
+                    p = (p + 4) & t.hmask;
+                }
+            }
+            if (it > t.hmask)
+                st.err |= ERR_PROBE;
+        }
+        const uint64_t m = __ballot(mine != kNoSlot);
+        if (m) {
+            const int lead = (int)__builtin_ctzll(m);
+            int32_t base = 0;
+            if (id.lane == lead)
+                base = atomicAdd(&sh.row.count, __popcll(m));
+            base = __builtin_amdgcn_readlane(base, lead);
+            if (mine != kNoSlot) {
+                const int32_t k = base + __popcll(m & lanes_below(id.lane));
+                if (k >= t.cap) {
+                    sh.row.ovf = 1u;
+                } else {
+                    idx = k;
+                    ent_new(t, k, u, ed.y, ed.z);
+                    if constexpr (L != T_LDS)
+                        t.SLOT(k) = mine;
+                    st.inserted += 1;
+                    lds_put(sh.resv + 2 * me + 1, k);
+                }
+            }
+        }
+        if (!counted && at >= total && q >= q1) {
+            counted = true;
+            if (id.lane == 0)
+                atomicAdd(&sh.done, 1);
+        }
+        __syncthreads();
+        // every claim is an entry now: the claims become its index
+        if (mine != kNoSlot)
+            slot_put(t, mine, idx >= 0 ? (h << t.shift()) | (uint32_t)idx : kNoSlot);
+        if (dup >= 0)
+            idx = lds_get(sh.resv + 2 * dup + 1);
+        if (idx >= 0)
+            atomicAdd(&t.DV(idx), (uint32_t)ed.w);
+        const bool last = sh.done >= id.nw || sh.row.ovf != 0u;
+        __syncthreads();
+        if (last)
+            break;
+    }
+}
+
+// The initial community: the ids init[0 .. n_init) become members and their
+// rows enter the table, all rows at once (K is the sum of the members' d,
+// every internal edge counted from both ends, whatever the order).
+template <int L>
+__device__ void team_init(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, const int32_t *init,
+                          int32_t n_init) {
     if (id.tid == 0)
-        sh.flen = 0;
+        sh.done = 0;
+    for (int32_t base = 0; base < n_init; base += id.nt) {
+        const bool act = base + id.tid < n_init;
+        const int32_t u = act ? init[base + id.tid] : 0;
+        const int32_t idx = team_ensure(t, sh, st, c, id, act, u);
+        if (act && idx >= 0)
+            t.DV(idx) |= kMember;
+    }
     __syncthreads();
+    const bool full = sh.row.ovf != 0u;
+    __syncthreads();   // read by all before a row may set it
+    if (!full)
+        block_edges(t, sh, st, c, id, init, n_init);
+    if (sh.row.ovf) {
+        st.ovf = true;
+        return;
+    }
+    // records: d was added in the L2, and the L1 may hold the lines of before
+    if constexpr (L != T_LDS)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    st.count = __builtin_amdgcn_readfirstlane(min(sh.row.count, t.cap));
+    uint64_t K = 0, V = 0;
     for (int32_t i = id.tid; i < st.count; i += id.nt) {
         const uint32_t v = t.DV(i);
-        if (!(v & kLive) || (v & kMember)) {
-            if (v & (kFresh | kTouch))
-                t.DV(i) = v & ~(kFresh | kTouch);   // a popped fresh-list entry
-            continue;
+        if (v & kMember) {
+            K += (uint64_t)(v & kDMask);
+            V += (uint64_t)t.KV(i);
         }
-        const double r = t.RK(i);
-        if (build_pops(v, pop_mode) && before(r, t.NODE(i), pr, pu)) {
-            t.DV(i) = v & ~(kLive | kFresh | kTouch);
-            continue;
+    }
+    st.K = (int64_t)team_sum(sh, id, K);
+    st.V = (int64_t)team_sum(sh, id, V);
+    st.nmem = n_init;
+    // the first call's buckets: ranks lie in [-L(kmax), L(2 kmax)] at alpha <= 1
+    // (a rank outside goes to the first or last bucket)
+    st.qtop = c.logtab[c.logtab_last];
+    st.qscale = (double)kBuckets / (2.0 * st.qtop + 1.0);
+    // rows were counted per wave
+    st.rows = team_sum(sh, id, id.lane == 0 ? st.rows : 0);
+    st.row_len = team_sum(sh, id, id.lane == 0 ? st.row_len : 0);
+}
+
+// Tables in a slab are emptied by the community that leaves them.
+template <int L>
+__device__ __forceinline__ void team_reset(const BTab<L> &t, const TeamId &id) {
+    if constexpr (L != T_LDS)
+        return;
+    for (uint32_t i = id.tid; i <= t.hmask >> 2; i += id.nt)
+        ((uint4 *)t.hw)[i] = make_uint4(kNoSlot, kNoSlot, kNoSlot, kNoSlot);
+}
+
+template <int L>
+__device__ __forceinline__ void team_leave(const BTab<L> &t, TeamSh &sh, const TeamId &id) {
+    if constexpr (L != T_LDS) {
+        __syncthreads();
+        const int32_t cnt = min(sh.row.count, t.cap);
+        for (int32_t i = id.tid; i < cnt; i += id.nt) {
+            const uint32_t s = t.SLOT(i);
+            if (s <= t.hmask)
+                slot_put(t, s, kNoSlot);
         }
-        if (v & (kFresh | kTouch))
-            t.DV(i) = v & ~(kFresh | kTouch);
-        atomicAdd(&sh.fill[bucket_of(r, q)], 1u);
+    }
+}
+
+// What the workgroup picked: an entry and its fields.
+struct Picked {
+    double r;
+    int32_t u, i;
+    uint32_t v;
+    int32_t k, beg;
+};
+
+// Lane l's candidate in every lane (scalar registers).
+__device__ __forceinline__ void pick_lane(int l, const Ent &e, int32_t i, Picked &o) {
+    o.r = read_lane(e.r, l);
+    o.u = __builtin_amdgcn_readlane(e.u, l);
+    o.i = __builtin_amdgcn_readlane(i, l);
+    o.v = (uint32_t)__builtin_amdgcn_readlane((int)e.v, l);
+    o.k = __builtin_amdgcn_readlane(e.k, l);
+    o.beg = __builtin_amdgcn_readlane(e.beg, l);
+}
+
+// The waves' candidates (lane l of each, l < 0: none) into one set of slots;
+// after the barrier each lane holds one wave's (i < 0: none).
+__device__ __forceinline__ void slot_exchange(TeamSh &sh, const TeamId &id, int &par, int l, Ent &e, int32_t &i) {
+    TeamSh::Slot *s = sh.slot[par];
+    par ^= 1;
+    if (id.lane == max(l, 0)) {
+        s[id.wid].r = e.r;
+        s[id.wid].u = e.u;
+        s[id.wid].i = l < 0 ? -1 : i;
+        s[id.wid].v = e.v;
+        s[id.wid].k = e.k;
+        s[id.wid].beg = e.beg;
     }
     __syncthreads();
-    // exclusive prefix of the bucket counts (wave 0: four buckets per lane)
+    const int w = id.lane < id.nw ? id.lane : 0;
+    e.r = s[w].r;
+    e.u = s[w].u;
+    i = id.lane < id.nw ? s[w].i : -1;
+    e.v = s[w].v;
+    e.k = s[w].k;
+    e.beg = s[w].beg;
+}
+
+// The workgroup's first entry in queue order among the lanes' candidates (i
+// < 0: none).  One barrier; set `par` of the slots is used and toggled.
+__device__ __forceinline__ bool block_pick_max(TeamSh &sh, const TeamId &id, int &par, Ent e, int32_t i, Picked &o) {
+    int l = wave_first(e.r, e.u, i);
+    if (id.nw > 1) {
+        slot_exchange(sh, id, par, l, e, i);
+        l = wave_first(e.r, e.u, i);
+    } else {
+        __syncthreads();
+    }
+    if (l < 0)
+        return false;
+    pick_lane(l, e, i, o);
+    return true;
+}
+
+__device__ __forceinline__ int wave_smallest(int32_t u, int32_t i) {
+    const int32_t lo = wave_min(i >= 0 ? u : INT32_MAX);
+    const uint64_t at = __ballot(i >= 0 && u == lo);
+    return at ? (int)__builtin_ctzll(at) : -1;
+}
+
+// The workgroup's smallest id u (i < 0: none).
+__device__ __forceinline__ bool block_pick_min(TeamSh &sh, const TeamId &id, int &par, Ent e, int32_t i, Picked &o) {
+    int l = wave_smallest(e.u, i);
+    if (id.nw > 1) {
+        slot_exchange(sh, id, par, l, e, i);
+        l = wave_smallest(e.u, i);
+    } else {
+        __syncthreads();
+    }
+    if (l < 0)
+        return false;
+    pick_lane(l, e, i, o);
+    return true;
+}
+
+// The bucketed queue: ns entries, positions before cp hold only
+// popped ones; lane l holds the starts of buckets 4l .. 4l + 3.
+struct LQ {
+    int32_t ns, cp;
+    int32_t s4[4];
+};
+
+// Start of bucket b (wave-uniform) from the lanes' registers.
+__device__ __forceinline__ int32_t lq_start(const LQ &q, int32_t b) {
+    if (b >= kBuckets)
+        return q.ns;
+    const int l = b >> 2, j = b & 3;
+    return __builtin_amdgcn_readlane(j == 0 ? q.s4[0] : j == 1 ? q.s4[1] : j == 2 ? q.s4[2] : q.s4[3], l);
+}
+
+__device__ __forceinline__ int32_t lq_bucket(const St &st, double r) {
+    return (int32_t)fmin(fmax((st.qtop - r) * st.qscale, 0.0), (double)(kBuckets - 1));
+}
+
+// Exclusive prefix of the bucket counts in sh.fill, four buckets per lane: the
+// buckets' starts, and the fill cursors at them.
+__device__ __forceinline__ void bucket_starts(TeamSh &sh, const TeamId &id) {
     if (id.wid == 0) {
-        const int32_t b0 = 4 * id.lane;
-        uint32_t c4[4];
-        uint32_t sum = 0;
+        // exclusive prefix of the bucket counts, four buckets per lane
+        const int32_t b4 = 4 * id.lane;
+        uint32_t c4[4], sum = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            c4[j] = sh.fill[b0 + j];
+            c4[j] = sh.fill[b4 + j];
             sum += c4[j];
         }
         uint32_t incl = sum;
@@ -1716,366 +2082,281 @@ __device__ void bq_build(const Tab &t, TeamSh &sh, St &st, const TeamId &id, BQ 
         uint32_t run = incl - sum;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            sh.bstart[b0 + j] = (int32_t)run;
-            sh.fill[b0 + j] = run;
+            sh.bstart[b4 + j] = (int32_t)run;
+            sh.fill[b4 + j] = run;
             run += c4[j];
         }
         if (id.lane == 63)
             sh.bstart[kBuckets] = (int32_t)incl;
     }
+}
+
+// Sort the queue into its buckets: at a call's start (CREATE: every
+// non-member with a link into c enters it, with its rank) or when the fresh
+// list has grown long (the pops still pending on it are applied first, as by
+// the next scan).  Two passes over the table: count, scatter.
+template <bool CREATE, int L>
+__device__ __forceinline__ void lq_build(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
+                                         LQ &q) {
+    double hi = -__builtin_huge_val(), lo = __builtin_huge_val();
+    st.scanned += 2 * (uint64_t)st.count;
+    for (int32_t b = id.tid; b < kBuckets; b += id.nt)
+        sh.fill[b] = 0u;
     __syncthreads();
-    for (int32_t i = id.tid; i < st.count; i += id.nt) {
-        const uint32_t v = t.DV(i);
-        if (!(v & kLive) || (v & kMember))
-            continue;
-        const uint32_t pos = atomicAdd(&sh.fill[bucket_of(t.RK(i), q)], 1u);
-        t.sq[pos] = i;
+    if (id.tid == 0)
+        sh.row.flen = 0;
+    st.flen = 0;
+    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+        uint32_t vv[kScanAhead];
+        int32_t kk[kScanAhead];
+        double rr[kScanAhead];
+#pragma unroll
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t i = min(base + x * id.nt, st.count - 1);
+            vv[x] = t.DV(i);
+            kk[x] = CREATE ? t.KV(i) : t.NODE(i);
+            rr[x] = CREATE ? 0.0 : t.RK(i);
+        }
+        if constexpr (CREATE) {
+#pragma unroll
+            for (int x = 0; x < kScanAhead; ++x)
+                rr[x] = (vv[x] & kMember) || (vv[x] & kDMask) == 0
+                            ? 0.0
+                            : block_log(t, c, 2 * (int32_t)(vv[x] & kDMask)) - st.alpha * block_log(t, c, kk[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t i = base + x * id.nt;
+            const uint32_t v = vv[x];
+            const double r = rr[x];
+            if (i >= st.count)
+                continue;
+            uint32_t nv;
+            bool in = false;
+            if constexpr (CREATE) {
+                nv = v & ~(kLive | kFresh | kTouch);
+                if (!(v & kMember) && (v & kDMask) != 0) {
+                    in = true;
+                    nv |= kLive;
+                    t.RK(i) = r;
+                    st.Rl += 1;
+                    st.Gl += 1;
+                    hi = fmax(hi, r);
+                    lo = fmin(lo, r);
+                }
+            } else {
+                nv = v & ~(kFresh | kTouch);
+                if ((v & kLive) && !(v & kMember)) {
+                    in = !((v & kFresh) && !(v & kTouch) && before(r, kk[x], st.pr, st.pu));
+                    if (!in)
+                        nv &= ~kLive;
+                }
+            }
+            if (in)
+                atomicAdd(&sh.fill[lq_bucket(st, r)], 1u);
+            if (nv != v)
+                t.DV(i) = nv;
+        }
+    }
+    if constexpr (CREATE) {
+        const double h = wave_max(hi), l = -wave_max(-lo);
+        if (id.lane == 0) {
+            sh.r[id.wid] = h;
+            sh.r2[id.wid] = l;
+        }
     }
     __syncthreads();
-    q.ns = sh.bstart[kBuckets];
+    bucket_starts(sh, id);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        q.s4[j] = sh.bstart[4 * id.lane + j];
+    q.ns = __builtin_amdgcn_readfirstlane(sh.bstart[kBuckets]);
     q.cp = 0;
-}
-
-// Rebuild the queue from every queued entry (fresh ones included), right
-// after an addition (st.pr, st.pu): the fresh-list pops still pending are
-// applied first.
-__device__ void bq_rebuild(const Tab &t, TeamSh &sh, St &st, const TeamId &id, BQ &q) {
-    double lo = __builtin_huge_val(), hi = -__builtin_huge_val();
-    st.scanned += (uint64_t)st.count;
-    for (int32_t i = id.tid; i < st.count; i += id.nt) {
-        const uint32_t v = t.DV(i);
-        if ((v & kLive) && !(v & kMember)) {
-            const double r = t.RK(i);
-            if (build_pops(v, POP_FRESH_LIST) && before(r, t.NODE(i), st.pr, st.pu))
-                continue;
-            lo = fmin(lo, r);
-            hi = fmax(hi, r);
-        }
-    }
-    double r = -__builtin_huge_val();
-    int32_t u = INT32_MAX, i = -1;
-    team_max_range(sh, id, r, u, i, lo, hi);
-    bq_build(t, sh, st, id, q, hi, lo, POP_FRESH_LIST, st.pr, st.pu);
-}
-
-// Up to kScanAhead entries of an index list per thread (positions
-// j0 + q * nt below lim), all loads issued before any is used: the index
-// loads, then the entries' fields (i < 0: no entry).
-struct Batch {
-    int32_t i[kScanAhead];
-    uint32_t v[kScanAhead];
-    double r[kScanAhead];
-    int32_t u[kScanAhead];
-    int32_t k[kScanAhead];
-};
-
-__device__ __forceinline__ void load_batch(const Tab &t, const int32_t *list, int32_t j0, int32_t lim, int32_t nt,
-                                           Batch &b) {
+    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+        uint32_t vv[kScanAhead];
+        double rr[kScanAhead];
 #pragma unroll
-    for (int q = 0; q < kScanAhead; ++q) {
-        const int32_t j = j0 + q * nt;
-        b.i[q] = j < lim ? list[j] : -1;
-    }
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t i = min(base + x * id.nt, st.count - 1);
+            vv[x] = t.DV(i);
+            rr[x] = t.RK(i);
+        }
 #pragma unroll
-    for (int q = 0; q < kScanAhead; ++q) {
-        b.v[q] = 0u;
-        b.r[q] = 0.0;
-        b.u[q] = 0;
-        b.k[q] = 0;
-        if (b.i[q] >= 0) {
-            const int32_t i = b.i[q];
-            b.v[q] = t.DV(i);
-            b.r[q] = t.RK(i);
-            b.u[q] = t.NODE(i);
-            b.k[q] = t.KV(i);
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t i = base + x * id.nt;
+            if (i < st.count && (vv[x] & (kLive | kMember)) == kLive)
+                t.sq[atomicAdd(&sh.fill[lq_bucket(st, rr[x])], 1u)] = (typename BTab<L>::Q)i;
         }
     }
+    if constexpr (CREATE) {
+        // the next call's range; a change of scale moves it a little
+        double h = sh.r[0], l = sh.r2[0];
+        for (int w = 1; w < id.nw; ++w) {
+            h = fmax(h, sh.r[w]);
+            l = fmin(l, sh.r2[w]);
+        }
+        st.nqtop = h + 0.25;
+        st.nqscale = (double)kBuckets / (h - l + 0.5);
+    }
+    __syncthreads();
 }
 
-// Switch a call from lazy pops to the bucketed queue right after an
-// addition (st.pr, st.pu): the entries the lazy scan would drop next (not
-// re-ranked, ranked above the addition) are popped, every other queued entry
-// is bucketed.
-__device__ void bq_switch(const Tab &t, TeamSh &sh, St &st, const TeamId &id, BQ &q) {
-    double lo = __builtin_huge_val(), hi = -__builtin_huge_val();
-    st.scanned += (uint64_t)st.count;
-    for (int32_t i = id.tid; i < st.count; i += id.nt) {
-        const uint32_t v = t.DV(i);
-        if (!(v & kLive) || (v & kMember))
-            continue;
-        const double r = t.RK(i);
-        if (build_pops(v, POP_LAZY_SCAN) && before(r, t.NODE(i), st.pr, st.pu))
-            continue;
-        lo = fmin(lo, r);
-        hi = fmax(hi, r);
-    }
-    double r = -__builtin_huge_val();
-    int32_t u = INT32_MAX, i = -1;
-    team_max_range(sh, id, r, u, i, lo, hi);
-    bq_build(t, sh, st, id, q, hi, lo, POP_LAZY_SCAN, st.pr, st.pu);
+// The fresh list's length from which the queue is rebuilt.  A step reads the
+// whole list and a rebuild the whole table, so the cost per addition is about
+// a count / f + b f, least at f in proportion to the root of count.
+__device__ __forceinline__ int32_t fresh_limit(int32_t count) {
+    return max(kFreshRebuild, (int32_t)(4.0f * sqrtf((float)count)));
 }
 
-// The next addition: the entry the sequential queue would add next (the
-// first improving entry in rank order), popping every queued entry ranked
-// above it.  Returns its index, or -1 when no queued entry improves (every
-// queued entry is popped then); er, eu, ev, ek get its rank, id, d|flags,
-// degree.  The fresh list's pops are applied lazily: its scan drops the
-// entries that an addition did not re-rank and that rank above it (the
-// last addition is st.pr, st.pu).  A first window of at most one entry per
-// thread keeps its entry in registers for its pops.
-__device__ int32_t bq_step(const Tab &t, TeamSh &sh, St &st, const TeamId &id, BQ &q, double &er, int32_t &eu,
-                           uint32_t &ev, int32_t &ek) {
-    const int32_t flen = min(sh.flen, t.cap);
-    st.scanned += (uint64_t)flen;
-    double fr = -__builtin_huge_val();
-    int32_t fu = INT32_MAX, fi = -1;
-    uint32_t my_fv = 0u;
-    int32_t my_fk = 0;
-    for (int32_t j = id.tid; j < flen; j += id.nt) {
-        const int32_t i = t.fr[j];
-        uint32_t v = t.DV(i);
-        if ((v & (kLive | kFresh | kMember)) != (kLive | kFresh))
-            continue;
-        const double r = t.RK(i);
-        const int32_t u = t.NODE(i);
-        const int32_t k = t.KV(i);
-        if (v & kTouch) {
-            v &= ~kTouch;
-            t.DV(i) = v;
-        } else if (before(r, u, st.pr, st.pu)) {
-            // popped before the last addition; it keeps kFresh (and its
-            // slot in the list), so that a later re-rank does not list it
-            // twice
-            t.DV(i) = v & ~kLive;
-            continue;
-        }
-        if (before(r, u, fr, fu) && improves_add(st, (int32_t)(v & kDMask), k)) {
-            fr = r;
-            fu = u;
-            fi = i;
-            my_fv = v;
-            my_fk = k;
-        }
-    }
-    const int32_t my_fi = fi;
-    int32_t my_wi = -1;
-    uint32_t my_wv = 0u;
-    int32_t my_wk = 0;
-    int32_t cp = q.cp;
+// The next addition (false: no queued entry improves): the best improving
+// entry of the fresh list and of windows of whole buckets from the queue's
+// head.  It is the queue's first improving entry once its bucket lies before
+// the window's end (every entry outside ranks strictly below it); until then
+// the window holds no improving entry and is popped whole.  Pops as in
+// bq_step: at once in the queue, by the next scan in the fresh list.
+// Both lists are read as one, two entries per thread at a time and without
+// branches up to the choice, so that the reads and the chains of dependent
+// operations of the two overlap.
+constexpr int kStepAhead = 2;
+
+template <int L>
+__device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id, LQ &q, int &par,
+                                        Picked &o) {
+    Ent b;
+    b.r = -__builtin_huge_val();
+    b.u = INT32_MAX;
+    b.v = 0u;
+    b.k = b.beg = 0;
+    int32_t bi = -1;
+    const bool zero = st.K == 0;
+    int32_t nf = min(st.flen, t.fmax);   // fresh entries in this window's scan
     int32_t win = id.nt;
-    bool first = true;
-    int32_t e = -1;
-    bool from_q = false;
     for (;;) {
-        // the window: whole buckets from cp, at most win entries unless its
-        // first bucket alone holds more
-        int32_t end = cp;
-        if (cp < q.ns) {
-            const int32_t b0 = bucket_at(sh, 0, kBuckets - 1, cp);
-            int32_t b1 = bucket_at(sh, b0, kBuckets, cp + win);
-            if (b1 <= b0)
-                b1 = b0 + 1;
-            end = sh.bstart[b1];
+        // buckets b0 (where cp lies) and b1 (the window's end): the largest
+        // that start at or before cp and cp + win
+        int32_t b0 = -1, b1 = -1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            b0 += __popcll(__ballot(q.s4[j] <= q.cp));
+            b1 += __popcll(__ballot(q.s4[j] <= q.cp + win));
         }
-        // a window of at most one entry per thread stays in registers
-        const bool cached = end - cp <= id.nt;
-        int32_t ci = -1;
-        uint32_t cv = 0u;
-        double cr = 0.0;
-        int32_t cu = 0;
-        double wr = -__builtin_huge_val(), mr = 0.0;
-        int32_t wu = INT32_MAX, wi = -1, mu = 0, mi = -1;
-        my_wi = -1;
-        st.scanned += (uint64_t)(end - cp);
-        for (int32_t j = cp + id.tid; j < end; j += id.nt) {
-            const int32_t i = t.sq[j];
-            const uint32_t v = t.DV(i);
-            if ((v & (kLive | kFresh | kMember)) != kLive)
-                continue;
-            const double r = t.RK(i);
-            const int32_t u = t.NODE(i);
-            const int32_t k = t.KV(i);
-            ci = i;
-            cv = v;
-            cr = r;
-            cu = u;
-            if (mi < 0 || pops_after(r, u, mr, mu)) {
-                mr = r;
-                mu = u;
-                mi = i;
+        b0 += q.ns <= q.cp;
+        b1 += q.ns <= q.cp + win;
+        if (b1 <= b0)
+            b1 = min(b0 + 1, kBuckets);
+        const int32_t end = lq_start(q, b1);
+        const int32_t total = nf + (end - q.cp);
+        st.scanned += (uint64_t)total;
+        Ent ee[kStepAhead];
+        int32_t ii[kStepAhead];
+        bool wi[kStepAhead];   // queued entries of the window
+        for (int32_t x0 = 0; x0 < total; x0 += kStepAhead * id.nt) {
+            bool in[kStepAhead], ff[kStepAhead];
+#pragma unroll
+            for (int y = 0; y < kStepAhead; ++y) {
+                const int32_t x = x0 + y * id.nt + id.tid;
+                in[y] = x < total;
+                ff[y] = x < nf;
+                // the fresh list lies right behind the queue
+                ii[y] = (int32_t)t.sq[in[y] ? (ff[y] ? t.cap + x : q.cp + x - nf) : 0];
             }
-            if (before(r, u, wr, wu) && improves_add(st, (int32_t)(v & kDMask), k)) {
-                wr = r;
-                wu = u;
-                wi = i;
-                my_wv = v;
-                my_wk = k;
+#pragma unroll
+            for (int y = 0; y < kStepAhead; ++y) {
+                ii[y] = in[y] ? ii[y] : 0;
+                ee[y] = ent_get(t, ii[y]);
+            }
+            int ok[kStepAhead];
+#pragma unroll
+            for (int y = 0; y < kStepAhead; ++y) {
+                const uint32_t v = ee[y].v;
+                const bool on =
+                    in[y] && (v & (kLive | kFresh | kMember)) == (ff[y] ? kLive | kFresh : kLive);
+                const bool pop = ff[y] && !(v & kTouch) && before(ee[y].r, ee[y].u, st.pr, st.pu);
+                const uint32_t nv = pop ? v & ~kLive : v & ~kTouch;   // (a popped fresh entry keeps its slot)
+                if (on && nv != v)
+                    t.DV(ii[y]) = nv;
+                wi[y] = on && !ff[y];
+                const int s = settle_add(st, (int32_t)(v & kDMask), ee[y].k);
+                ok[y] = on && !pop ? (zero ? 1 : s) : 0;
+            }
+#pragma unroll
+            for (int y = 0; y < kStepAhead; ++y) {
+                bool take = ok[y] != 0 && before(ee[y].r, ee[y].u, b.r, b.u);
+                if (take && ok[y] < 0)
+                    take = decide(st.K, st.V, st.K + 2 * (int64_t)(ee[y].v & kDMask), st.V + ee[y].k, st.alpha);
+                b.r = take ? ee[y].r : b.r;
+                b.u = take ? ee[y].u : b.u;
+                b.v = take ? ee[y].v : b.v;
+                b.k = take ? ee[y].k : b.k;
+                b.beg = take ? ee[y].beg : b.beg;
+                bi = take ? ii[y] : bi;
             }
         }
-        my_wi = wi;
-        if (!first) {
-            fr = -__builtin_huge_val();
-            fu = INT32_MAX;
-            fi = -1;
-        }
-        team_window(sh, id, fr, fu, fi, wr, wu, wi, mr, mi, mu);
-        if (first) {
-            // the fresh candidate, kept for later windows
-            er = fr;
-            eu = fu;
-            e = fi;
-            first = false;
-        }
-        const bool has_f = e >= 0 && !from_q;
+        const bool found = block_pick_max(sh, id, par, b, bi, o);
+        const int32_t bo = found ? __builtin_amdgcn_readfirstlane(lq_bucket(st, o.r)) : kBuckets;
         const bool last = end >= q.ns;
-        bool decided = false;
-        if (wi >= 0 && (!has_f || before(wr, wu, er, eu))) {
-            e = wi;
-            er = wr;
-            eu = wu;
-            from_q = true;
-            decided = true;
-        } else if (has_f && ((mi >= 0 && before(er, eu, mr, mu)) || last)) {
-            decided = true;
-        } else if (last) {
-            e = -1;
-            decided = true;
-        }
-        // pops in the window: entries ranked above the addition, or all
-        if (cached) {
-            if (ci >= 0 && ci != e && (!decided || e < 0 || before(cr, cu, er, eu)))
-                t.DV(ci) = cv & ~kLive;
+        const bool decided = found && (bo < b1 || last);
+        if (total <= kStepAhead * id.nt) {
+            // (one round: its entries are still in registers)
+            if (total > 0) {
+#pragma unroll
+                for (int y = 0; y < kStepAhead; ++y)
+                    if (wi[y] && (!decided || (ii[y] != o.i && before(ee[y].r, ee[y].u, o.r, o.u))))
+                        t.DV(ii[y]) = ee[y].v & ~kLive;
+            }
         } else {
-            for (int32_t j = cp + id.tid; j < end; j += id.nt) {
-                const int32_t i = t.sq[j];
+            for (int32_t p = q.cp + id.tid; p < end; p += id.nt) {
+                const int32_t i = t.sq[p];
                 const uint32_t v = t.DV(i);
-                if ((v & (kLive | kFresh | kMember)) != kLive || i == e)
-                    continue;
-                if (!decided || e < 0 || before(t.RK(i), t.NODE(i), er, eu))
+                if ((v & (kLive | kFresh | kMember)) == kLive &&
+                    (!decided || (i != o.i && before(t.RK(i), t.NODE(i), o.r, o.u))))
                     t.DV(i) = v & ~kLive;
             }
         }
-        if (decided)
-            break;
-        cp = end;
-        win *= 2;
-        __syncthreads();
-    }
-    // buckets before the addition's hold only popped entries now
-    q.cp = (e >= 0 && from_q) ? sh.bstart[bucket_of(er, q)] : cp;
-    // the thread that found the addition hands on its flags and degree
-    if (e >= 0 && (from_q ? my_wi == e : my_fi == e)) {
-        sh.ev = from_q ? my_wv : my_fv;
-        sh.ek = from_q ? my_wk : my_fk;
-    }
-    __syncthreads();
-    if (e >= 0) {
-        ev = sh.ev;
-        ek = sh.ek;
-    }
-    return e;
-}
-
-// Additions from the bucketed queue until no queued entry improves (true)
-// or the call must end early (false: overflow, move limit, budget).
-template <bool GLOBAL>
-__device__ bool bq_additions(const Tab &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, BQ &q,
-                             int64_t &moves) {
-    for (;;) {
-        if (sh.flen > max(512, st.count >> 5))
-            bq_rebuild(t, sh, st, id, q);
-        double br;
-        int32_t bu;
-        uint32_t v;
-        int32_t k;
-        const int32_t bi = bq_step(t, sh, st, id, q, br, bu, v, k);
-        if (bi < 0)
+        if (decided) {
+            // the buckets before the addition's hold only popped entries
+            q.cp = max(q.cp, lq_start(q, bo));
+            __syncthreads();   // the pops are in place before the row's updates
             return true;
-        // add bi; no thread reads its flags again before the row update's barriers
-        const int32_t d = (int32_t)(v & kDMask);
-        if (id.tid == 0)
-            t.DV(bi) = (v | kMember) & ~(kLive | kFresh | kTouch);
-        st.K += 2 * (int64_t)d;
-        st.V += k;
-        st.nmem += 1;
-        st.M += 1;
-        moves += 1;
-        st.pr = br;
-        st.pu = bu;
-        set_rates(st);
-        team_row<GLOBAL, ROW_ADD>(t, sh, st, c, id, bu, true);
-        if (st.ovf)
-            return false;
-        if ((int64_t)st.M > st.move_limit) {
-            st.err |= ERR_LIMIT;
-            return false;
         }
-        if ((st.M & 15) == 0 && team_over_budget(sh, id, st))
+        if (last)
             return false;
+        q.cp = end;
+        win *= 2;
+        nf = 0;
     }
 }
 
-// Removal passes of one growth call over a list of the members gathered
-// once (global tables), same order and decisions as removal_scan.  Record
-// tables of more than by_id_min entries (16 queue_min: 16,384 at the default)
-// sort the list into kBuckets ranges of node id (the queue's bucket arrays
-// are free once the additions are over), so that a search for the smallest
-// removable id above the cursor walks whole buckets from the cursor's one
-// and stops at the first that holds one; smaller tables scan their whole
-// list per search, which costs less than the sort and the extra barriers
-// there.
-template <bool GLOBAL>
-__device__ bool removal_members(const Tab &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
-                                uint32_t k_prune, int32_t by_id_min, int64_t &moves) {
-    // record tables only (their lists run to tens of thousands of members);
-    // the same in all threads
-    const bool by_id = t.hp != nullptr && st.count > by_id_min;
-    const int shift = max(0, (32 - __builtin_clz((uint32_t)max(c.n - 1, 1))) - 8);
-    int32_t ml;
-    if (by_id) {
-        for (int32_t b = id.tid; b < kBuckets; b += id.nt)
-            sh.fill[b] = 0u;
-        __syncthreads();
-        for (int32_t i = id.tid; i < st.count; i += id.nt) {
-            if (t.DV(i) & kMember)
-                atomicAdd(&sh.fill[t.NODE(i) >> shift], 1u);
-        }
-        __syncthreads();
-        if (id.wid == 0) {
-            const int32_t b0 = 4 * id.lane;
-            uint32_t c4[4];
-            uint32_t sum = 0;
+// The smallest removable id above the cursor among the entries i[] (< 0: none).
+template <int L, int N>
+__device__ __forceinline__ void removal_look(const BTab<L> &t, const St &st, const int32_t *i, int32_t cursor, Ent &b,
+                                             int32_t &bi) {
+    Ent e[N];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                c4[j] = sh.fill[b0 + j];
-                sum += c4[j];
-            }
-            uint32_t incl = sum;
+    for (int x = 0; x < N; ++x)
+        e[x] = ent_get(t, max(i[x], 0));
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t x = __shfl_up(incl, off);
-                if (id.lane >= off)
-                    incl += x;
-            }
-            uint32_t run = incl - sum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                sh.bstart[b0 + j] = (int32_t)run;
-                sh.fill[b0 + j] = run;
-                run += c4[j];
-            }
-            if (id.lane == 63)
-                sh.bstart[kBuckets] = (int32_t)incl;
+    for (int x = 0; x < N; ++x) {
+        if (i[x] < 0 || !(e[x].v & kMember) || e[x].u <= cursor || e[x].u >= b.u)
+            continue;
+        if (improves_remove(st, (int32_t)(e[x].v & kDMask), e[x].k)) {
+            b = e[x];
+            bi = i[x];
         }
-        __syncthreads();
-        for (int32_t i = id.tid; i < st.count; i += id.nt) {
-            if (t.DV(i) & kMember)
-                t.scr[atomicAdd(&sh.fill[t.NODE(i) >> shift], 1u)] = i;
-        }
-        __syncthreads();
-        ml = sh.bstart[kBuckets];
-        st.scanned += 2 * (uint64_t)st.count;
-    } else {
+    }
+}
+
+// The members gathered once (t.scr), for the removal passes of a call on
+// tables in global memory.  Wide tables of more than by_id_min entries sort
+// the list into kBuckets ranges of node id (the queue's bucket arrays are
+// free once the additions are over), so that a search for the smallest
+// removable id above the cursor walks whole buckets from the cursor's one and
+// stops at the first that holds one; smaller tables scan their whole list per
+// search, which costs less than the sort and the extra barriers there.
+template <int L>
+__device__ int32_t removal_list(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id, bool by_id, int shift) {
+    if (!by_id) {
         if (id.tid == 0)
             sh.m = 0;
         __syncthreads();
@@ -2084,205 +2365,142 @@ __device__ bool removal_members(const Tab &t, TeamSh &sh, St &st, const Ctx &c, 
                 t.scr[atomicAdd(&sh.m, 1)] = i;
         }
         __syncthreads();
-        ml = sh.m;
         st.scanned += (uint64_t)st.count;
+        return sh.m;
     }
-    for (uint32_t pass = 0; k_prune == 0 || pass < k_prune; ++pass) {
-        st.Gu += (uint64_t)st.nmem;
-        int32_t cursor = -1;
-        bool removed = false;
-        int32_t pos = 0;   // list positions before pos hold only ids at or below the cursor
-        for (;;) {
-            int32_t cu = INT32_MAX;
-            int32_t ci = -1;
-            // windows of whole buckets from pos until one holds a removable
-            // id (unsorted: one window, the whole list)
-            while (pos < ml) {
-                int32_t end = ml;
-                if (by_id) {
-                    const int32_t b0 = bucket_at(sh, 0, kBuckets - 1, pos);
-                    int32_t b1 = bucket_at(sh, b0, kBuckets, pos + kScanAhead * id.nt);
-                    if (b1 <= b0)
-                        b1 = b0 + 1;
-                    end = sh.bstart[b1];
-                }
-                st.scanned += (uint64_t)(end - pos);
-                for (int32_t j0 = pos + id.tid; j0 < end; j0 += kScanAhead * id.nt) {
-                    Batch b;
-                    load_batch(t, t.scr, j0, end, id.nt, b);
-#pragma unroll
-                    for (int x = 0; x < kScanAhead; ++x) {
-                        if (b.i[x] < 0 || !(b.v[x] & kMember))
-                            continue;
-                        const int32_t u = b.u[x];
-                        if (u <= cursor || u >= cu)
-                            continue;
-                        if (improves_remove(st, (int32_t)(b.v[x] & kDMask), b.k[x])) {
-                            cu = u;
-                            ci = b.i[x];
-                        }
-                    }
-                }
-                if (end >= ml)
-                    break;   // the last window: the pick below decides
-                const int32_t found = team_min_i32(sh, id, ci < 0 ? INT32_MAX : cu);
-                if (found != INT32_MAX)
-                    break;
-                pos = end;
-            }
-            uint32_t vm = 0;
-            int32_t km = 0;
-            team_pick_min(sh, id, t, cu, ci, vm, km);
-            if (ci < 0)
-                break;
-            const int32_t d = (int32_t)(vm & kDMask);
-            if (id.tid == 0)
-                t.DV(ci) = vm & ~kMember;
-            st.K -= 2 * (int64_t)d;
-            st.V -= km;
-            st.nmem -= 1;
-            st.M += 1;
-            moves += 1;
-            set_rates(st);
-            team_row<GLOBAL, ROW_REMOVE>(t, sh, st, c, id, cu);
-            removed = true;
-            cursor = cu;
-            pos = by_id ? sh.bstart[cu >> shift] : 0;
-            if ((int64_t)st.M > st.move_limit) {
-                st.err |= ERR_LIMIT;
-                return false;
-            }
-            if ((st.M & 15) == 0 && team_over_budget(sh, id, st))
-                return false;
-        }
-        if (!removed)
-            break;
+    for (int32_t b = id.tid; b < kBuckets; b += id.nt)
+        sh.fill[b] = 0u;
+    __syncthreads();
+    for (int32_t i = id.tid; i < st.count; i += id.nt) {
+        if (t.DV(i) & kMember)
+            atomicAdd(&sh.fill[t.NODE(i) >> shift], 1u);
     }
-    return true;
+    __syncthreads();
+    bucket_starts(sh, id);
+    __syncthreads();
+    for (int32_t i = id.tid; i < st.count; i += id.nt) {
+        if (t.DV(i) & kMember)
+            t.scr[atomicAdd(&sh.fill[t.NODE(i) >> shift], 1u)] = i;
+    }
+    __syncthreads();
+    st.scanned += 2 * (uint64_t)st.count;
+    return sh.bstart[kBuckets];
 }
 
-
-// One call of the growth function (Algorithm 1) by the whole workgroup.
-// Additions start with full-table scans and lazy pops; on a global table
-// whose entry count reaches queue_min (the count is the same in all
-// threads) the call switches to the bucketed queue for the rest of its
-// additions and to member-list removal passes.
-template <bool GLOBAL>
-__device__ int64_t team_grow(const Tab &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
-                             uint32_t k_prune, int32_t queue_min) {
+// One call of the growth function (Algorithm 1).
+template <int L>
+__device__ int64_t team_grow(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, uint32_t k_prune,
+                             int32_t by_id_min) {
     int64_t moves = 0;
-    bool creation = true;
-    bool bucketed = false;
+    int par = 0;
+    LQ q;
+    lq_build<true>(t, sh, st, c, id, q);
     for (;;) {
-        double br = -__builtin_huge_val();
-        int32_t bu = INT32_MAX;
-        int32_t bi = -1;
-        st.scanned += (uint64_t)st.count;
-        for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
-            uint32_t vv[kScanAhead];
-            double rr[kScanAhead];
-            int32_t nn[kScanAhead], kk[kScanAhead];
-#pragma unroll
-            for (int q = 0; q < kScanAhead; ++q) {
-                const int32_t i = base + q * id.nt;
-                vv[q] = 0u;
-                rr[q] = 0.0;
-                nn[q] = 0;
-                kk[q] = 0;
-                if (i < st.count) {
-                    vv[q] = t.DV(i);
-                    rr[q] = t.RK(i);
-                    nn[q] = t.NODE(i);
-                    kk[q] = t.KV(i);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < kScanAhead; ++q) {
-                const int32_t i = base + q * id.nt;
-                if (i >= st.count)
-                    continue;
-                uint32_t v = vv[q];
-                double r = rr[q];
-                if (creation) {
-                    // the queue is built from every non-member with a link into c
-                    if ((v & kMember) || (v & kDMask) == 0) {
-                        if (v & (kLive | kFresh | kTouch))
-                            t.DV(i) = v & ~(kLive | kFresh | kTouch);
-                        continue;
-                    }
-                    r = rank_of(c, (int32_t)(v & kDMask), kk[q], st.alpha);
-                    t.RK(i) = r;
-                    st.Rl += 1;
-                    st.Gl += 1;
-                    v = (v | kLive) & ~(kFresh | kTouch);
-                    t.DV(i) = v;
-                } else {
-                    if (!(v & kLive))
-                        continue;
-                    if (v & kFresh) {
-                        v &= ~kFresh;
-                        t.DV(i) = v;
-                    } else if (before(r, nn[q], st.pr, st.pu)) {
-                        t.DV(i) = v & ~kLive;      // popped and rejected last step
-                        continue;
-                    }
-                }
-                if (before(r, nn[q], br, bu) && improves_add(st, (int32_t)(v & kDMask), kk[q])) {
-                    br = r;
-                    bu = nn[q];
-                    bi = i;
-                }
-            }
-        }
-        creation = false;
-        uint32_t v = 0;
-        int32_t k = 0;
-        team_pick_max(sh, id, t, br, bu, bi, v, k);
-        if (bi < 0)
+        if (st.flen > fresh_limit(st.count))
+            lq_build<false>(t, sh, st, c, id, q);
+        Picked o;
+        if (!lq_step(t, sh, st, id, q, par, o))
             break;
-        // add the best improving node; no thread reads its flags again
-        // before the barriers of the row update below
-        const int32_t d = (int32_t)(v & kDMask);
         if (id.tid == 0)
-            t.DV(bi) = (v | kMember) & ~(kLive | kFresh);
-        st.K += 2 * (int64_t)d;
-        st.V += k;
+            t.DV(o.i) = (o.v | kMember) & ~(kLive | kFresh | kTouch);
+        st.K += 2 * (int64_t)(o.v & kDMask);
+        st.V += o.k;
         st.nmem += 1;
         st.M += 1;
         moves += 1;
-        st.pr = br;
-        st.pu = bu;
+        st.pr = o.r;
+        st.pu = o.u;
         set_rates(st);
-        team_row<GLOBAL, ROW_ADD>(t, sh, st, c, id, bu);
+        block_row<ROW_ADD>(t, sh, st, c, id, o.u, o.beg, o.k);
         if (st.ovf)
             return moves;
         if ((int64_t)st.M > st.move_limit) {
             st.err |= ERR_LIMIT;
             return moves;
         }
-        if ((st.M & 15) == 0 && team_over_budget(sh, id, st))
+        if (st.err & ERR_TIMEOUT)
             return moves;
-        if constexpr (GLOBAL) {
-            if (st.count >= queue_min) {
-                BQ q;
-                bq_switch(t, sh, st, id, q);
-                if (!bq_additions<GLOBAL>(t, sh, st, c, id, q, moves))
-                    return moves;
-                bucketed = true;
-                break;
-            }
-        }
     }
+    st.qtop = st.nqtop;
+    st.qscale = st.nqscale;
     if (moves == 0)
         return 0;
-    if constexpr (GLOBAL) {
-        if (bucketed) {
-            const int32_t by_id_min = (int32_t)min<int64_t>(16 * (int64_t)queue_min, INT32_MAX);
-            removal_members<GLOBAL>(t, sh, st, c, id, k_prune, by_id_min, moves);
-            return moves;
+    // removal passes over the members in ascending id
+    const bool by_id = L == T_WIDE && st.count > by_id_min;
+    const int shift = max(0, (32 - __builtin_clz((uint32_t)max(c.n - 1, 1))) - 8);
+    int32_t ml = 0;
+    if constexpr (L != T_LDS)
+        ml = removal_list(t, sh, st, id, by_id, shift);
+    for (uint32_t pass = 0; k_prune == 0 || pass < k_prune; ++pass) {
+        st.Gu += (uint64_t)st.nmem;
+        int32_t cursor = -1;
+        int32_t bkt = 0;   // by_id: the bucket of the cursor
+        bool removed = false;
+        for (;;) {
+            Ent b;
+            b.u = INT32_MAX;
+            b.r = 0.0;
+            b.v = 0u;
+            b.k = b.beg = 0;
+            int32_t bi = -1;
+            int32_t ii[kScanAhead];
+            if constexpr (L == T_LDS) {
+                st.scanned += (uint64_t)st.count;
+                for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+#pragma unroll
+                    for (int x = 0; x < kScanAhead; ++x)
+                        ii[x] = base + x * id.nt < st.count ? base + x * id.nt : -1;
+                    removal_look<L, kScanAhead>(t, st, ii, cursor, b, bi);
+                }
+            } else {
+                int32_t pos = by_id ? sh.bstart[bkt] : 0;
+                while (pos < ml) {
+                    int32_t end = ml;
+                    if (by_id) {
+                        const int32_t b0 = bucket_at(sh, 0, kBuckets - 1, pos);
+                        const int32_t b1 = bucket_at(sh, b0, kBuckets, pos + kScanAhead * id.nt);
+                        end = sh.bstart[max(b1, b0 + 1)];
+                    }
+                    st.scanned += (uint64_t)(end - pos);
+                    for (int32_t base = pos + id.tid; base < end; base += kScanAhead * id.nt) {
+#pragma unroll
+                        for (int x = 0; x < kScanAhead; ++x)
+                            ii[x] = base + x * id.nt < end ? t.scr[base + x * id.nt] : -1;
+                        removal_look<L, kScanAhead>(t, st, ii, cursor, b, bi);
+                    }
+                    if (end >= ml)
+                        break;   // the last window: the pick below decides
+                    if (team_min_i32(sh, id, bi < 0 ? INT32_MAX : b.u) != INT32_MAX)
+                        break;
+                    pos = end;
+                }
+            }
+            Picked o;
+            if (!block_pick_min(sh, id, par, b, bi, o))
+                break;
+            if (id.tid == 0)
+                t.DV(o.i) = o.v & ~kMember;
+            st.K -= 2 * (int64_t)(o.v & kDMask);
+            st.V -= o.k;
+            st.nmem -= 1;
+            st.M += 1;
+            moves += 1;
+            set_rates(st);
+            block_row<ROW_REMOVE>(t, sh, st, c, id, o.u, o.beg, o.k);
+            removed = true;
+            cursor = o.u;
+            if (by_id)
+                bkt = cursor >> shift;
+            if ((int64_t)st.M > st.move_limit) {
+                st.err |= ERR_LIMIT;
+                return moves;
+            }
+            if (st.err & ERR_TIMEOUT)
+                return moves;
         }
+        if (!removed)
+            break;
     }
-    removal_scan<GLOBAL>(t, sh, st, c, id, k_prune, moves);
     return moves;
 }
 
@@ -2346,8 +2564,8 @@ __device__ void team_sort(int32_t *a, int32_t m, const TeamId &id) {
 }
 
 // Delta output, one workgroup: wave_toggle_records for the workgroup.
-template <bool GLOBAL>
-__device__ bool team_toggle_records(const SweepArgs &A, const Tab &t, TeamSh &sh, St &st, const Ctx &c,
+template <class T>
+__device__ bool team_toggle_records(const SweepArgs &A, const T &t, TeamSh &sh, St &st, const Ctx &c,
                                     const TeamId &id, int32_t set, int32_t s_last) {
     const int32_t sk = delta_key_scale(A.rec, A.S, set, s_last);
     if (sk < 0) {
@@ -2363,14 +2581,14 @@ __device__ bool team_toggle_records(const SweepArgs &A, const Tab &t, TeamSh &sh
         for (int32_t base = 0; base < len; base += id.nt) {
             const bool act = base + id.tid < len;
             const int32_t u = act ? A.pool[off + base + id.tid] : 0;
-            const int32_t idx = team_ensure<GLOBAL>(t, sh, st, c, act, u);
-            if (sh.ovf) {
+            const int32_t idx = team_ensure(t, sh, st, c, id, act, u);
+            if (sh.row.ovf) {
                 st.ovf = true;
                 return true;
             }
             if (act && idx >= 0)
                 t.DV(idx) ^= (kMember | kWas);
-            st.count = min(sh.count, t.cap);
+            st.count = min(sh.row.count, t.cap);
             __syncthreads();
         }
     }
@@ -2379,7 +2597,7 @@ __device__ bool team_toggle_records(const SweepArgs &A, const Tab &t, TeamSh &sh
 
 // Sort a[0..m) (global memory) through the LDS buffer lbuf when it fits:
 // the bitonic network's rounds then wait on LDS, not on memory.
-constexpr int kLdsSort = 2048;
+constexpr int kLdsSort = 1024;
 
 __device__ void team_sort_via(int32_t *a, int32_t m, const TeamId &id, int32_t *lbuf) {
     if (m <= 1)
@@ -2397,37 +2615,27 @@ __device__ void team_sort_via(int32_t *a, int32_t m, const TeamId &id, int32_t *
     __syncthreads();
 }
 
-// lbuf: LDS sort buffer of kLdsSort entries (global tables), or nullptr.
-template <bool GLOBAL, bool PERSET>
-__device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *lbuf) {
+// lbuf: LDS sort buffer of kLdsSort entries, or nullptr (tables in LDS sort in place).
+template <bool PERSET, class T>
+__device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lbuf) {
     TeamId id;
     id.tid = (int)threadIdx.x;
     id.nt = (int)blockDim.x;
     id.lane = id.tid & 63;
     id.wid = id.tid >> 6;
     id.nw = id.nt >> 6;
-    Ctx c;
-    c.row_ptr = A.g.row_ptr;
-    c.col = A.g.col;
-    c.w = A.g.w;
-    c.kdeg = A.g.kdeg;
-    c.logtab = A.g.logtab;
-    c.logtab_last = A.g.logtab_n - 1;
-    c.n = A.g.n;
+    const Ctx c = make_ctx(A.g);
     const uint32_t n_items = A.tier == 0 ? (uint32_t)A.n_sets : A.ctl->ovf_count[A.in_from];
     for (;;) {
         __syncthreads();
         if (id.tid == 0) {
             sh.item = atomicAdd(&A.ctl->work_next[A.tier], 1u);
             sh.abort = __hip_atomic_load(A.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ERR_TIMEOUT;
-            sh.count = 0;
-            sh.ovf = 0u;
-            sh.stop = 0u;
+            sh.row.count = 0;
+            sh.row.ovf = 0u;
+            sh.row.stop = 0u;
         }
-        if constexpr (!GLOBAL) {
-            for (uint32_t i = id.tid; i <= t.hmask; i += id.nt)
-                t.hs[i] = -1;
-        }
+        team_reset(t, id);
         __syncthreads();
         const uint32_t item = sh.item;
         if (item >= n_items || sh.abort)
@@ -2464,7 +2672,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
         bool bad = false;
         bool keyed = false;   // delta output (see run_wave)
         if ((s0 > A.s_begin || A.resume) && A.rec.drem) {
-            bad = !team_toggle_records<GLOBAL>(A, t, sh, st, c, id, set, s0 - 1);
+            bad = !team_toggle_records(A, t, sh, st, c, id, set, s0 - 1);
             st.err = team_or(sh, id, st.err);
             if (!bad && !st.ovf && !st.err) {
                 if (id.tid == 0)
@@ -2491,30 +2699,8 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
             init = A.seed_nodes + A.seed_ptr[set];
             n_init = A.seed_ptr[set + 1] - A.seed_ptr[set];
         }
-        for (int32_t q = 0; q < n_init && !bad && !st.ovf; ++q) {
-            const int32_t u = init[q];
-            const int32_t idx = team_ensure<GLOBAL>(t, sh, st, c, id.tid == 0, u);
-            if (sh.ovf) {
-                st.ovf = true;
-                break;
-            }
-            if (id.tid == 0)
-                sh.bidx = idx;
-            __syncthreads();
-            const int32_t i0 = sh.bidx;
-            const uint32_t v = t.DV(i0);
-            __syncthreads();
-            if (id.tid == 0)
-                t.DV(i0) = v | kMember;
-            st.K += 2 * (int64_t)(v & kDMask);
-            st.V += c.kdeg[u];
-            st.nmem += 1;
-            st.count = min(sh.count, t.cap);
-            __syncthreads();
-            team_row<GLOBAL, ROW_INIT>(t, sh, st, c, id, u);
-            if (st.ovf)
-                break;
-        }
+        if (!bad && !st.ovf)
+            team_init(t, sh, st, c, id, init, n_init);
         st.err = team_or(sh, id, st.err);
         // seed-set gathers are the method's; a resumed set's are overhead
         if (!(s0 > A.s_begin || A.resume)) {
@@ -2541,7 +2727,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
             int64_t moved = 0;
             for (;;) {
                 calls += 1;
-                const int64_t mv = team_grow<GLOBAL>(t, sh, st, c, id, A.k_prune, A.queue_min);
+                const int64_t mv = team_grow(t, sh, st, c, id, A.k_prune, A.by_id_min);
                 st.err = team_or(sh, id, st.err);
                 moved += mv;
                 if (st.ovf || st.err || mv == 0)
@@ -2666,6 +2852,8 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
         const uint64_t inserted = team_sum(sh, id, st.inserted);
         const uint64_t cins = team_sum(sh, id, st.c_ins);
         if (id.tid == 0) {
+            if (bad || st.err || (st.ovf && !A.work_out))
+                void_records(A, set, s_at);
             if (st.ovf) {
                 if (A.work_out) {
                     const uint32_t pos = atomicAdd(&A.ctl->ovf_count[A.tier], 1u);
@@ -2677,7 +2865,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
             if (st.err)
                 atomicOr(A.err, st.err);
             if (!st.ovf) {
-                unsigned long long *sx = A.stat + kStatWords * A.tier;
+                unsigned long long *sx = A.stat + kStatWords * A.stat_slot;
                 atomicAdd(&sx[0], (unsigned long long)st.rows);
                 atomicAdd(&sx[1], (unsigned long long)st.row_len);
                 atomicAdd(&sx[2], (unsigned long long)inserted);
@@ -2685,7 +2873,7 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
                 atomicAdd(&sx[4], 1ull);
                 atomicAdd(&sx[5], (unsigned long long)st.scanned);
             }
-            unsigned long long *sa = A.stat + kStatWords * A.tier;
+            unsigned long long *sa = A.stat + kStatWords * A.stat_slot;
             atomicAdd(&sa[6], (unsigned long long)st.c_mrows);
             atomicAdd(&sa[7], (unsigned long long)st.c_mrow_len);
             if (st.emitted) {
@@ -2694,53 +2882,50 @@ __device__ void run_team(const SweepArgs &A, const Tab &t, TeamSh &sh, int32_t *
             }
             atomicAdd(&sa[10], (unsigned long long)cins);
         }
-        if constexpr (GLOBAL) {
-            // leave the slab's hash empty for the next community
-            const int32_t cnt = min(sh.count, t.cap);
-            for (int32_t i = id.tid; i < cnt; i += id.nt)
-                tab_slot_clear<GLOBAL>(t, i);
-        }
+        team_leave(t, sh, id);
     }
 }
 
-template <bool PERSET>
-__device__ __forceinline__ void team_lds_entry(const SweepArgs &A) {
-    extern __shared__ __align__(16) char smem[];
-    __shared__ TeamSh sh;
-    Tab t = carve(smem, A.cap, A.hbits);
-    run_team<false, PERSET>(A, t, sh, nullptr);
+// Fill a workgroup's copy of the first logs (run_team starts with a barrier).
+__device__ __forceinline__ void load_logs(const SweepArgs &A, double *lt) {
+    for (int32_t i = (int32_t)threadIdx.x; i < min(kBlockLogs, A.g.logtab_n); i += (int32_t)blockDim.x)
+        lt[i] = A.g.logtab[i];
 }
 
-// REC: the tables are of the record layout (cap >= kRecordMinEntries); one
-// kernel per layout, so that each is compiled with its own strides.
-template <bool PERSET, bool REC>
-__device__ __forceinline__ void team_global_entry(const SweepArgs &A) {
+template <bool PERSET, int L>
+__device__ __forceinline__ void team_entry(const SweepArgs &A) {
     __shared__ TeamSh sh;
-    __shared__ int32_t lsort[kLdsSort];
-    const int slot = blockIdx.x;
-    if (slot >= A.n_slots)
-        return;
-    Tab t = carve_global_as<REC>(A.gtab + (int64_t)slot * A.gtab_stride, A.cap, A.hbits);
-    run_team<true, PERSET>(A, t, sh, lsort);
+    double *lt;
+    if constexpr (L == T_LDS) {
+        extern __shared__ __align__(16) char smem[];
+        lt = (double *)smem;
+        const BTab<L> t = carve_lds(smem, A.cap, A.hbits);
+        load_logs(A, lt);
+        run_team<PERSET>(A, t, sh, nullptr);
+    } else {
+        __shared__ double logs[kBlockLogs];
+        __shared__ int32_t lsort[kLdsSort];
+        if ((int)blockIdx.x >= A.n_slots)
+            return;
+        const BTab<L> t = carve_slab<L>(A.gtab, A.gtab_stride, A.n_slots, blockIdx.x, logs, A.cap, A.hbits);
+        load_logs(A, logs);
+        run_team<PERSET>(A, t, sh, lsort);
+    }
 }
 
-// Register bounds: a workgroup steps through one community as a chain of
-// dependent scans, reductions and table updates, so more communities in
-// flight per CU is what hides the latency, up to the point where spilled
-// values reloaded inside the steps cost more than the extra communities
-// win.  Both kinds take at most 128 VGPRs (four waves per SIMD): LDS tables
-// of 1,024 entries allow four workgroups per CU anyway, and for the
-// global-table kernels 96 VGPRs (five waves) spilled about 130 registers
-// into scratch that the steps reload (measured: 128 is 7 % faster on the
-// 100k- and 10M-node graphs, 1 % on the 1M one; 168 is slower on the 1M
-// one).
+// Register bounds.  LDS tables leave room for at most three workgroups per
+// compute unit, so their kernel takes the 256 VGPRs of two waves per SIMD and
+// spills nothing.  On global tables three waves per SIMD (168 VGPRs, 79
+// spilled) were best at two waves per community: sweeps of the 100k-, 1M- and
+// 4M-node graphs 26, 151 and 450 ms; two (no spills) 30, 170 and 474, four 26,
+// 148 and 464.
 #define LCD_TEAM_KERNEL(w) __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(w)))
-LCD_TEAM_KERNEL(4) sweep_team_lds_kernel(SweepArgs A) { team_lds_entry<false>(A); }
-LCD_TEAM_KERNEL(4) sweep_team_global_kernel(SweepArgs A) { team_global_entry<false, false>(A); }
-LCD_TEAM_KERNEL(4) sweep_team_global_rec_kernel(SweepArgs A) { team_global_entry<false, true>(A); }
-LCD_TEAM_KERNEL(4) query_team_lds_kernel(SweepArgs A) { team_lds_entry<true>(A); }
-LCD_TEAM_KERNEL(4) query_team_global_kernel(SweepArgs A) { team_global_entry<true, false>(A); }
-LCD_TEAM_KERNEL(4) query_team_global_rec_kernel(SweepArgs A) { team_global_entry<true, true>(A); }
+LCD_TEAM_KERNEL(2) sweep_team_lds_kernel(SweepArgs A) { team_entry<false, T_LDS>(A); }
+LCD_TEAM_KERNEL(3) sweep_team_global_kernel(SweepArgs A) { team_entry<false, T_PACK>(A); }
+LCD_TEAM_KERNEL(3) sweep_team_global_rec_kernel(SweepArgs A) { team_entry<false, T_WIDE>(A); }
+LCD_TEAM_KERNEL(2) query_team_lds_kernel(SweepArgs A) { team_entry<true, T_LDS>(A); }
+LCD_TEAM_KERNEL(3) query_team_global_kernel(SweepArgs A) { team_entry<true, T_PACK>(A); }
+LCD_TEAM_KERNEL(3) query_team_global_rec_kernel(SweepArgs A) { team_entry<true, T_WIDE>(A); }
 #undef LCD_TEAM_KERNEL
 
 // ---------------------------------------------------------------------------
@@ -2759,6 +2944,23 @@ __global__ void degrees_kernel(const int32_t *row_ptr, const uint8_t *w, int32_t
     for (int32_t j = b; j < e; ++j)
         s += w[j];
     kdeg[u] = s;
+}
+
+__global__ void node_info_kernel(const int32_t *row_ptr, const int32_t *kdeg, int2 *info, int32_t n) {
+    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < n)
+        info[u] = make_int2(row_ptr[u], kdeg[u]);
+}
+
+__global__ void adj_kernel(const int32_t *row_ptr, const int32_t *col, const uint8_t *w, const int32_t *kdeg,
+                           const double *logtab, int64_t nnz, int4 *adj, double *adjl) {
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz;
+         j += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t u = col[j];
+        const int32_t k = kdeg[u];
+        adj[j] = make_int4(u, k, row_ptr[u], w ? (int32_t)w[j] : 1);
+        adjl[j] = logtab[k];
+    }
 }
 
 __global__ void logtab_kernel(double *tab, int32_t m) {
@@ -3573,6 +3775,22 @@ hipError_t launch_degrees(const int32_t *row_ptr, const uint8_t *w, int32_t *kde
     return hipGetLastError();
 }
 
+hipError_t launch_node_info(const int32_t *row_ptr, const int32_t *kdeg, int2 *info, int32_t n, hipStream_t st) {
+    if (n == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(node_info_kernel, dim3(grid_for(n, 256)), dim3(256), 0, st, row_ptr, kdeg, info, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_adj(const int32_t *row_ptr, const int32_t *col, const uint8_t *w, const int32_t *kdeg,
+                      const double *logtab, int64_t nnz, int4 *adj, double *adjl, hipStream_t st) {
+    if (nnz == 0)
+        return hipSuccess;
+    const int g = grid_for(nnz, 256) < 16384 ? grid_for(nnz, 256) : 16384;
+    hipLaunchKernelGGL(adj_kernel, dim3(g), dim3(256), 0, st, row_ptr, col, w, kdeg, logtab, nnz, adj, adjl);
+    return hipGetLastError();
+}
+
 hipError_t launch_logtab(double *tab, int32_t m, hipStream_t st) {
     hipLaunchKernelGGL(logtab_kernel, dim3(grid_for(m, 256)), dim3(256), 0, st, tab, m);
     return hipGetLastError();
@@ -3623,7 +3841,7 @@ hipError_t launch_sweep(const SweepArgs &a, int32_t blocks, int32_t waves_per_bl
     case TIER_TEAM_LDS: {
         if (waves_per_block < 1 || 64 * waves_per_block > kTeamMaxThreads)
             return hipErrorInvalidValue;
-        const size_t smem = (size_t)table_bytes(a.cap, a.hbits);
+        const size_t smem = (size_t)block_table_bytes(a.cap, a.hbits);
         hipLaunchKernelGGL(q ? query_team_lds_kernel : sweep_team_lds_kernel, grid, block, smem, st, a);
         break;
     }

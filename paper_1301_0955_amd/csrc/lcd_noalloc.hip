@@ -27,10 +27,12 @@ constexpr int32_t kNaTables = LCD_NOALLOC_TABLES;
 constexpr int64_t kNaCtl = 0;                                    // Counters
 constexpr int64_t kNaCursor = 256;                               // kCursorWords x u64
 constexpr int64_t kNaCheck = kNaCursor + 512;                    // validation verdict (u32)
-constexpr int64_t kNaWork = kNaCheck + 256;                      // 6 x kNaMaxSets int32
-constexpr int64_t kNaSlab = kNaWork + (int64_t)6 * kNaMaxSets * 4;
-constexpr int64_t kNaStride = (global_table_bytes(kNaTableCap, 15) + 255) / 256 * 256;
-constexpr int64_t kNaBytes = kNaSlab + kNaTables * kNaStride;
+constexpr int kNaQueues = 3;                                     // two overflow queues in turn, the ordered copy
+constexpr int64_t kNaWork = kNaCheck + 256;                      // kNaQueues x kNaMaxSets int32
+constexpr int64_t kNaSlab = kNaWork + (int64_t)kNaQueues * kNaMaxSets * 4;
+constexpr int kNaHashBits = 15;                                  // two slots per entry
+constexpr int64_t kNaTableBytes = team_table_bytes(kNaTableCap) + (4 << kNaHashBits);
+constexpr int64_t kNaBytes = kNaSlab + kNaTables * kNaTableBytes;
 static_assert(kCursorWords * 8 <= 512, "cursor words fit their slot");
 static_assert(((int64_t)1 << 15) >= 2 * (int64_t)kNaTableCap, "hash bits of the workgroup tier");
 static_assert(kNaBytes <= LCD_NOALLOC_SCRATCH_BYTES, "scratch layout fits the stated size");
@@ -173,7 +175,7 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     // the tier chain of lcd_sweep, cut after its first global-memory tier,
     // whose tables come from the scratch array
     TierPlan full;
-    CHK(plan_tiers(g->dev, g->n, prm, full));
+    CHK(plan_tiers(g->dev, g->n, n_sets, prm, full));
     TierPlan tp;
     for (int k = 0; k < full.n; ++k) {
         TierSpec T = full.t[k];
@@ -181,7 +183,7 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
             if (T.kind != TIER_TEAM_GLOBAL || T.cap > kNaTableCap)
                 break;
             T.cap = kNaTableCap;
-            T.hbits = 15;
+            T.hbits = kNaHashBits;
             T.slots = kNaTables;
             T.slab = 0;
             tp.t[tp.n++] = T;
@@ -191,9 +193,10 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     }
     Slab slab[2];
     slab[0].buf = base + kNaSlab;
-    slab[0].stride = kNaStride;
+    slab[0].kind = TIER_TEAM_GLOBAL;
+    slab[0].stride = team_table_bytes(kNaTableCap);
     slab[0].cap = kNaTableCap;
-    slab[0].hbits = 15;
+    slab[0].hbits = kNaHashBits;
     slab[0].slots = kNaTables;
 
     // check the inputs, then clear the queues, counters and table hashes
@@ -213,7 +216,7 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     HIPCHK(launch_zero_bytes(base + kNaCtl, sizeof(Counters), st));
     HIPCHK(launch_zero_bytes(base + kNaCursor, 8 * kCursorWords, st));
     if (tp.n > 0 && tp.t[tp.n - 1].slab >= 0)
-        HIPCHK(launch_fill_i32((int32_t *)slab[0].buf, -1, kNaStride * kNaTables / 4, st));
+        HIPCHK(launch_fill_i32((int32_t *)slab[0].buf, -1, (int64_t)kNaTables << kNaHashBits, st));
 
     SweepArgs a{};
     a.g = graph_dev(g);
@@ -227,7 +230,7 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     a.n_sets = n_sets;
     a.k_prune = prm.k_prune;
     a.max_calls = prm.grow_calls > 0 ? (uint32_t)prm.grow_calls : 0u;
-    a.queue_min = queue_min_of(prm);
+    a.by_id_min = by_id_min_of(prm);
     a.resume = 0;
     a.rec.off = rec_off;
     a.rec.cnt = rec_cnt;
@@ -245,8 +248,9 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     a.budget_ticks = prm.watchdog_ms < 0 ? 0 : g->dev.wall_khz * (int64_t)prm.watchdog_ms;
     int32_t *work[kMaxTiers - 1], *ordered[kMaxTiers - 1];
     for (int k = 0; k < kMaxTiers - 1; ++k) {
-        work[k] = (int32_t *)(base + kNaWork) + (int64_t)k * kNaMaxSets;
-        ordered[k] = (int32_t *)(base + kNaWork) + (int64_t)(3 + k) * kNaMaxSets;
+        // a tier reads one queue (or its ordered copy) and fills the other
+        work[k] = (int32_t *)(base + kNaWork) + (int64_t)(k & 1) * kNaMaxSets;
+        ordered[k] = (int32_t *)(base + kNaWork) + (int64_t)2 * kNaMaxSets;
     }
     int32_t launches = 0;
     CHK(enqueue_tiers(a, tp, 0, tp.n, tp.t[0].blocks, slab, work, ordered, st, nullptr, &launches));

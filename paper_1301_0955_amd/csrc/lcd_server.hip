@@ -131,7 +131,7 @@ struct Lane {
     uint32_t *flags = nullptr;
     Counters *ctl = nullptr;
     unsigned long long *cursor = nullptr;
-    int32_t *work[kMaxTiers - 1] = {nullptr, nullptr, nullptr};
+    int32_t *work[kMaxTiers - 1] = {};
     Slab slab[2];
     // pinned host staging
     double *h_alpha = nullptr;
@@ -265,7 +265,7 @@ lcd_status launch_lane(lcd_server *S, Lane &L) {
     for (int k = 0; k < S->tp.n; ++k)
         if (S->tp.t[k].slab >= 0 && L.slab[S->tp.t[k].slab].buf) {
             Slab &sl = L.slab[S->tp.t[k].slab];
-            CHK(ensure_slab(sl, sl.cap, sl.slots, st));
+            CHK(ensure_slab(sl, sl.kind, sl.cap, sl.slots, st));
         }
     SweepArgs a{};
     a.g = graph_dev(g);
@@ -278,7 +278,7 @@ lcd_status launch_lane(lcd_server *S, Lane &L) {
     a.seed_nodes = L.seed_nodes;
     a.n_sets = nq;
     a.k_prune = S->prm.k_prune;
-    a.queue_min = queue_min_of(S->prm);
+    a.by_id_min = by_id_min_of(S->prm);
     a.resume = 0;
     a.rec = L.rec;
     a.pool = L.pool;
@@ -626,7 +626,7 @@ lcd_status lane_init(lcd_server *S, Lane &L, int id, int32_t max_q, int64_t max_
     CHK(host_alloc(&L.h_work0, max_q));
     for (int k = 0; k < S->tp.n; ++k)
         if (S->tp.t[k].slab >= 0 && slots[S->tp.t[k].slab] > 0)
-            CHK(ensure_slab(L.slab[S->tp.t[k].slab], S->tp.t[k].cap, slots[S->tp.t[k].slab], L.st));
+            CHK(ensure_slab(L.slab[S->tp.t[k].slab], S->tp.t[k].kind, S->tp.t[k].cap, slots[S->tp.t[k].slab], L.st));
     HIPCHK(hipStreamSynchronize(L.st));
     return LCD_OK;
 }
@@ -685,7 +685,7 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
         prm.team_waves = 8;
     }
     S->prm = prm;
-    lcd_status s = plan_tiers(g->dev, g->n, prm, S->tp);
+    lcd_status s = plan_tiers(g->dev, g->n, 1, prm, S->tp);
     if (s != LCD_OK) {
         delete S;
         return s;
@@ -696,11 +696,12 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     // so a short batch can wait behind a long one.
     //  * >= 8 queues: one stage per tier (a batch lasts as long as its
     //    slowest query, so a query that fits a small table never waits for
-    //    one that needs a large table) and six lanes: one per LDS tier,
-    //    three for the 16,384-entry tier (about a third of a query stream
-    //    ends there), one for the whole-graph tier; with 10 or more queues
-    //    five lanes for the 16,384-entry tier (eight in all), so that a
-    //    query leaving an earlier stage finds a free lane sooner.
+    //    one that needs a large table; the LDS workgroup tiers are one
+    //    stage) and six lanes: one for tier 0, three for the LDS workgroup
+    //    tiers (about half of a query stream ends there), one each for the
+    //    16,384-entry and the whole-graph tier; with 10 or more queues four
+    //    lanes and two (eight in all), so that a query leaving an earlier
+    //    stage finds a free lane sooner.
     //  * fewer: tier 0, then all later tiers; four lanes, one for tier 0.
     int hw_queues = 4;
     if (const char *e = std::getenv("GPU_MAX_HW_QUEUES"))
@@ -708,15 +709,20 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     const bool per_tier = hw_queues >= 8 && S->tp.n >= 2;
     S->n_stages = 0;
     if (per_tier) {
-        for (int k = 0; k < S->tp.n && k < kMaxStages; ++k)
-            S->stages[S->n_stages++] = Stage{k, k + 1};
+        // the LDS workgroup tiers share a stage
+        for (int k = 0; k < S->tp.n; ++k) {
+            if (k > 0 && S->tp.t[k].stat == S->tp.t[k - 1].stat)
+                S->stages[S->n_stages - 1].last = k + 1;
+            else
+                S->stages[S->n_stages++] = Stage{k, k + 1};
+        }
     } else {
         S->stages[S->n_stages++] = Stage{0, 1};
         if (S->tp.n >= 2)
             S->stages[S->n_stages++] = Stage{1, S->tp.n};
     }
-    static const int kPerTierLanes[6] = {0, 1, 2, 2, 2, 3};
-    static const int kPerTierWide[8] = {0, 1, 2, 2, 2, 2, 2, 3};
+    static const int kPerTierLanes[6] = {0, 1, 1, 1, 2, 3};
+    static const int kPerTierWide[8] = {0, 1, 1, 1, 1, 2, 2, 3};
     static const int kTwoStageLanes[4] = {0, 1, 1, 1};
     const bool wide = per_tier && hw_queues >= 10;
     const int n_lanes = per_tier ? (wide ? 8 : 6) : 4;
@@ -731,7 +737,7 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     int32_t want[2] = {0, 0};
     for (int k = 0; k < S->tp.n; ++k)
         if (S->tp.t[k].slab >= 0) {
-            tb[S->tp.t[k].slab] = slab_stride(S->tp.t[k].cap);
+            tb[S->tp.t[k].slab] = slab_bytes(S->tp.t[k].kind, S->tp.t[k].cap);
             want[S->tp.t[k].slab] = S->tp.t[k].slots;
         }
     const int64_t fixed = lane_bytes(max_q, max_seed, pool_cap);
@@ -794,7 +800,7 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     // start-stage routing needs the adjacency on the host: kept for graphs
     // of up to 2^28 entries (1 GiB)
     for (int k = 0; k < S->n_stages; ++k)
-        S->stage_cap[k] = S->tp.t[S->stages[k].first].cap;
+        S->stage_cap[k] = S->tp.t[S->stages[k].last - 1].cap;
     if (S->n_stages >= 2 && g->nnz <= ((int64_t)1 << 28)) {
         try {
             S->h_row_ptr.resize((size_t)g->n + 1);
