@@ -100,18 +100,17 @@ typedef struct {
                                 stops with LCD_EDEVICE.  0 = default (20000);
                                 negative = no budget at all (tests the error path) */
     int32_t spill_mode;      /* sets whose table outgrows tier 0: 0 = workgroup tiers
-                                (one workgroup per community: LDS tables, then
-                                global-memory tables);
+                                (one workgroup per community: an LDS table if
+                                team_capacity is given, then global-memory tables);
                                 1 = one-wave global-memory tiers; 2 = one-wave
                                 global tables of 16,384 entries, then workgroups
                                 on tables that hold every node */
-    int32_t team_capacity;   /* spill_mode 0: entries of one workgroup tier with LDS
-                                tables; 0 = chosen by the number of seed sets: three
-                                tiers of LDS tables for few sets (four per compute
-                                unit at most), none for more */
+    int32_t team_capacity;   /* spill_mode 0: entries of a workgroup tier's LDS table;
+                                0 = no such tier */
     int32_t team_waves;      /* waves per community in the workgroup tiers, 1..8;
-                                0 = 2 (4 on the largest LDS tables, 8 on the tables
-                                that hold every node) */
+                                0 = 4 for few seed sets (three per compute unit) and
+                                on graphs of 4M+ nodes, else 2 (8 on the tables that
+                                hold every node) */
     int32_t grow_calls;      /* growth calls per (seed set, scale): 0 = until a call
                                 changes nothing (the default); n > 0 stops after
                                 n calls (lcd_sweep_merge makes one per round) */

@@ -78,15 +78,6 @@ lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipSt
     return LCD_OK;
 }
 
-// Entries of the largest table held in LDS (a multiple of 64) whose workgroup
-// takes at most `bytes` of LDS.
-static int32_t block_capacity(int64_t bytes) {
-    int32_t cap = 8192;
-    while (cap > 64 && block_table_bytes(cap, block_hbits(cap)) + kTeamShBytes > bytes)
-        cap -= 64;
-    return cap;
-}
-
 lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp) {
     int32_t cap = p.lds_capacity > 0 ? p.lds_capacity : 512;
     if (cap % 64 != 0 || cap < 64 || cap > 8192)
@@ -106,23 +97,12 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
                                       : (int32_t)std::max<int64_t>(1, dev.lds_cu / (wpb * tb));
     bpc = std::min(bpc, 32);
     tp.n = 0;
-    tp.t[tp.n++] = TierSpec{TIER_WAVE_LDS, cap, hbits0, wpb, dev.cus * bpc, 0, -1, 0};
+    tp.t[tp.n++] = TierSpec{TIER_WAVE_LDS, cap, hbits0, wpb, dev.cus * bpc, 0, -1};
     const int64_t need = std::max<int64_t>(64, n);
     const int32_t capn = (int32_t)((int64_t)1 << next_pow2_bits(need));
     int32_t have = cap;   // largest table so far
-    auto add_global = [&](int32_t kind, int32_t c, int32_t waves, int32_t slots, int32_t slab) {
-        tp.t[tp.n] = TierSpec{kind, c, next_pow2_bits(2 * (int64_t)c), waves, 0, slots, slab, tp.t[tp.n - 1].stat + 1};
-        tp.n += 1;
-        have = c;
-    };
     if (p.team_waves < 0 || 64 * p.team_waves > kTeamMaxThreads)
         return fail(LCD_EINVAL, "team_waves must be in [0, %d]", kTeamMaxThreads / 64);
-    // waves per community on global tables: with two, a community's step takes
-    // about 0.8 of its time with one, and six communities share a compute unit
-    // instead of twelve; the tables of twelve miss the L2 more often (sweeps of
-    // the 100k-, 1M- and 4M-node graphs: 26, 151 and 450 ms with two, 25, 148
-    // and 546 ms with one, 42, 219 and 505 ms with four)
-    const int32_t team_waves = p.team_waves > 0 ? p.team_waves : 2;
     // workgroups of a workgroup tier that stay resident on the whole chip
     auto resident = [&](int32_t kind, int32_t waves, size_t lds) -> int32_t {
         int32_t nb = 0;
@@ -130,6 +110,25 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
             nb = 1;
         return dev.cus * nb;
     };
+    auto add_global = [&](int32_t kind, int32_t c, int32_t waves, int32_t slots, int32_t slab) {
+        const int32_t blocks = kind == TIER_TEAM_GLOBAL ? resident(kind, waves, 0) : 0;
+        tp.t[tp.n] = TierSpec{kind, c, next_pow2_bits(2 * (int64_t)c), waves, blocks, slots, slab};
+        tp.n += 1;
+        have = c;
+    };
+    // waves per community on global tables.  A wide workgroup shortens a
+    // community's chain of steps (22,990 additions alone on the 4M-node graph:
+    // 272 ms with one wave, 206 with two, 168 with four), a narrow one keeps
+    // more communities in flight (16,384 sets on the 1M-node graph: 105, 109
+    // and 149 ms; 20,000 on 100k nodes: 18, 20 and 29 ms).  Four where every set
+    // is resident at four, and on graphs of millions of nodes, whose longest
+    // chains are much of a sweep (547, 398 and 380 ms); else two.
+    int32_t team_waves = p.team_waves;
+    if (team_waves == 0)
+        team_waves = n >= (4 << 20) || n_sets <= resident(TIER_TEAM_GLOBAL, 4, 0) ? 4 : 2;
+    // tables for the narrowest of them, whatever the launch, so that launches of
+    // few and of many sets share one slab
+    const int32_t team_slots = std::max(resident(TIER_TEAM_GLOBAL, 2, 0), resident(TIER_TEAM_GLOBAL, team_waves, 0));
     if (p.spill_mode == 1 || p.spill_mode == 2) {
         const int32_t c1 = std::min<int32_t>(16384, capn);
         if (c1 > have && n > have)
@@ -144,34 +143,18 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
         }
         return LCD_OK;
     }
-    // workgroup tiers.  A launch of few communities lasts as long as the
-    // longest chain of steps in it, and a step on an LDS table takes about 0.7
-    // of one on a global table: tables of the largest sizes that let three, two
-    // and one workgroup share a compute unit, then global ones.  A launch of
-    // many communities lasts as long as the chip needs for all their steps, and
-    // LDS tables leave too few in flight: all on global tables (1,000 sets: 5.5
-    // ms with the LDS tiers, 6.5 without; 20,000 sets: 55 and 26 ms).
-    struct Want { int32_t cap, waves; } want[3];
-    int n_want = 0;
     if (p.team_capacity > 0) {
         const int32_t cl = p.team_capacity;
         if (cl % 64 != 0 || cl > 8192 ||
             table_bytes(cl, next_pow2_bits(2 * (int64_t)cl)) + 1024 > dev.lds_block)
             return fail(LCD_EINVAL, "team_capacity must be a multiple of 64 whose table fits one workgroup's LDS");
-        want[n_want++] = Want{cl, 2};
-    } else if (n_sets <= 4 * dev.cus) {
-        for (int share = 3; share >= 1; --share)
-            want[n_want++] = Want{block_capacity(std::min(dev.lds_block, dev.lds_cu / share)), share == 1 ? 4 : 2};
-    }
-    for (int q = 0; q < n_want; ++q) {
-        const int32_t cl = want[q].cap;
-        if (cl <= have || n <= have)
-            continue;
-        const int32_t hb = block_hbits(cl);
-        const int32_t waves = p.team_waves > 0 ? p.team_waves : want[q].waves;
-        tp.t[tp.n++] = TierSpec{TIER_TEAM_LDS, cl, hb, waves,
-                                resident(TIER_TEAM_LDS, waves, (size_t)block_table_bytes(cl, hb)), 0, -1, 1};
-        have = cl;
+        if (cl > have && n > have) {
+            const int32_t hb = block_hbits(cl), waves = p.team_waves > 0 ? p.team_waves : 2;
+            tp.t[tp.n] = TierSpec{TIER_TEAM_LDS, cl, hb, waves,
+                                  resident(TIER_TEAM_LDS, waves, (size_t)block_table_bytes(cl, hb)), 0, -1};
+            tp.n += 1;
+            have = cl;
+        }
     }
     // graphs of millions of nodes grow communities of thousands of members
     // whose tables hold tens of thousands of entries: there the first global
@@ -179,7 +162,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
     // workgroup instead of waiting for the few whole-graph tables
     const int32_t c2 = std::min<int32_t>(n >= (4 << 20) ? 131072 : 16384, capn);
     if (c2 > have && n > have)
-        add_global(TIER_TEAM_GLOBAL, c2, team_waves, resident(TIER_TEAM_GLOBAL, team_waves, 0), 0);
+        add_global(TIER_TEAM_GLOBAL, c2, team_waves, team_slots, 0);
     if (capn > have && n > have) {
         // the whole-graph tier gets the few largest communities, whose
         // step-by-step chain is the tier's time: the widest workgroups
@@ -204,7 +187,6 @@ lcd_status enqueue_tiers(const SweepArgs &a0, const TierPlan &tp, int first, int
             HIPCHK(hipEventRecord(ev[k], st));
         SweepArgs b = a0;
         b.tier = k;
-        b.stat_slot = T.stat;
         b.kind = T.kind;
         b.in_from = k > 0 ? k - 1 : 0;
         b.work_in = k > 0 ? work[k - 1] : nullptr;
@@ -224,7 +206,7 @@ lcd_status enqueue_tiers(const SweepArgs &a0, const TierPlan &tp, int first, int
             b.gtab = sl.buf;
             b.gtab_stride = sl.stride;
             b.n_slots = sl.slots;
-            blocks = T.kind == TIER_WAVE_GLOBAL ? (sl.slots + T.waves - 1) / T.waves : sl.slots;
+            blocks = T.kind == TIER_WAVE_GLOBAL ? (sl.slots + T.waves - 1) / T.waves : std::min(T.blocks, sl.slots);
         } else {
             b.gtab = nullptr;
             b.gtab_stride = 0;
@@ -394,11 +376,11 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
     r->stats.lds_capacity = tp.t[0].cap;
     r->stats.waves_per_block = tp.t[0].waves;
     r->stats.grid_blocks = tp.t[0].blocks;
-    r->stats.tiers = tp.t[tp.n - 1].stat + 1;
+    r->stats.tiers = tp.n;
     for (int k = 0; k < tp.n; ++k) {
         // tiers that share a slot report the largest one's capacity
-        r->stats.tier_kind[tp.t[k].stat] = tp.t[k].kind;
-        r->stats.tier_capacity[tp.t[k].stat] = tp.t[k].cap;
+        r->stats.tier_kind[k] = tp.t[k].kind;
+        r->stats.tier_capacity[k] = tp.t[k].cap;
     }
     // ev[0 .. n]: before each tier and after the last; ev[kMaxTiers + 1]:
     // before the work-queue reset
@@ -449,7 +431,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
         HIPCHK(hipMemcpy(ctl.data(), r->ctl, sizeof(Counters) * r->n_ctl, hipMemcpyDeviceToHost));
         float ms_total = 0.f, ms_main = 0.f, ms_spill = 0.f;
         HIPCHK(hipEventElapsedTime(&ms_total, ev_begin, ev_end));
-        for (int k = 0; k < kStatSlots; ++k)
+        for (int k = 0; k < kMaxTiers; ++k)
             r->stats.ms_tier[k] = 0.0;
         if (timed) {
             HIPCHK(hipEventElapsedTime(&ms_main, ev[0], ev[1]));
@@ -458,7 +440,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
             for (int k = 0; k < tp.n; ++k) {
                 float x = 0.f;
                 HIPCHK(hipEventElapsedTime(&x, ev[k], ev[k + 1]));
-                r->stats.ms_tier[tp.t[k].stat] += x;
+                r->stats.ms_tier[k] += x;
             }
         }
         const uint32_t err = (uint32_t)(cur[1] & 0xffffffffu);
@@ -480,7 +462,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
         r->stats.n_spilled = sp;
         r->stats.n_spilled_big = spb;
         r->stats.pool_used = (int64_t)cur[0];
-        for (int t = 0; t < kStatSlots; ++t) {
+        for (int t = 0; t < kMaxTiers; ++t) {
             const unsigned long long *x = cur + 2 + kStatWords * t;
             r->stats.tier[t].rows_gathered = (int64_t)x[0];
             r->stats.tier[t].row_entries = (int64_t)x[1];

@@ -100,7 +100,7 @@ struct Slab {
 };
 
 // pool cursor, error word, then kStatWords statistics per tier
-constexpr int kCursorWords = 2 + kStatWords * kStatSlots;
+constexpr int kCursorWords = 2 + kStatWords * kMaxTiers;
 
 // Table entries above which a removal pass sorts its member list.
 inline int32_t by_id_min_of(const lcd_params &p) {
@@ -113,10 +113,9 @@ struct TierSpec {
     int32_t cap;       // table entries per community
     int32_t hbits;     // hash slots = 2^hbits
     int32_t waves;     // waves per workgroup
-    int32_t blocks;    // workgroups of an LDS tier (tier 0: the full-size grid)
+    int32_t blocks;    // workgroups resident (tier 0: the full-size grid); unused by wave global tiers
     int32_t slots;     // global tiers: tables wanted in the slab
     int32_t slab;      // global tiers: slab index; -1 for LDS tiers
-    int32_t stat;      // statistics slot
 };
 
 struct TierPlan {
@@ -142,11 +141,11 @@ inline int64_t slab_bytes(int32_t kind, int32_t cap) {
 
 // The tier chain for n_sets communities on a graph of n nodes: tier 0 one
 // wave per community with an LDS table (lds_capacity entries), then tiers with
-// larger tables.  spill_mode 0: workgroup tiers (LDS tables for few sets,
-// global tables of 16,384 entries, or 131,072 on graphs of millions of nodes,
-// global tables that hold every node); 1: one-wave global tiers (16,384
-// entries x 4,096 tables, then every node); 2: a one-wave global tier, then
-// workgroups.
+// larger tables.  spill_mode 0: workgroup tiers (LDS tables if team_capacity
+// is given, global tables of 16,384 entries, or 131,072 on graphs of millions
+// of nodes, global tables that hold every node); 1: one-wave global tiers
+// (16,384 entries x 4,096 tables, then every node); 2: a one-wave global
+// tier, then workgroups.
 lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp);
 
 // (Re)allocate a slab for cap entries x slots tables of a tier kind and mark

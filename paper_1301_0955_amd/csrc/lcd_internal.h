@@ -52,8 +52,7 @@ enum : uint32_t {
 
 // Work-queue state of one launch group (all tiers of one scale range),
 // zeroed before the group runs.
-constexpr int kMaxTiers = 6;    // tiers of a launch chain
-constexpr int kStatSlots = 4;   // tier statistics kept (lcd_sweep_stats): the LDS workgroup tiers share one
+constexpr int kMaxTiers = 4;    // tiers of a launch chain
 
 struct Counters {
     uint32_t work_next[kMaxTiers];    // per tier: next work item
@@ -79,7 +78,7 @@ struct SweepArgs {
     Counters *ctl;
     unsigned long long *pool_cursor;   // entries claimed in the pool (may pass pool_cap)
     uint32_t *err;                     // ERR_* bits
-    unsigned long long *stat;          // per statistics slot (kStatWords each), over the sets the tier
+    unsigned long long *stat;          // per tier (kStatWords each), over the sets the tier
                                        // finished: rows gathered, their length, entries
                                        // created, pool entries written, sets finished, table
                                        // entries scanned; over every set the tier ran, for
@@ -87,7 +86,6 @@ struct SweepArgs {
                                        // moves, their length, seed-set rows, their length,
                                        // entries created after the set's start
     int32_t tier;             // position in the launch chain
-    int32_t stat_slot;        // where the tier's statistics are counted
     int32_t in_from;          // tier > 0: the tier whose pushes this one consumes
     const int32_t *work_in;   // tier > 0: set ids pushed by that tier
     int32_t *work_out;        // sets pushed to the next tier (nullptr for the last)
@@ -132,20 +130,19 @@ constexpr int kBlockLogs = 512;
 constexpr int kRecordBytes = 32;
 constexpr int32_t kRecordMinEntries = 65536;
 constexpr int kBlockEntryBytes = 8 /*rank*/ + 4 /*node*/ + 4 /*d|flags*/ + 4 /*k*/ + 4 /*row start*/ + 2 /*queue*/;
-constexpr int kFreshMax = 512;       // fresh-list entries of an LDS table
+constexpr int kFreshMax = 320;       // fresh-list entries kept
+constexpr int kFreshMaxWide = 1024;  // ... of tables of 32-bit indices
 constexpr int kFreshRebuild = 256;   // ... from which the queue is rebuilt, at least
-constexpr int kTeamShBytes = 3072;   // LDS a workgroup uses beside its table, at most
+constexpr int kTeamShBytes = 3584;   // LDS a workgroup uses beside its table, at most
 
 __host__ __device__ constexpr int64_t block_table_bytes(int32_t cap, int32_t hbits) {
     return (int64_t)kBlockLogs * 8 + ((int64_t)1 << hbits) * 4 + (int64_t)cap * kBlockEntryBytes + kFreshMax * 2;
 }
 
-__host__ __device__ constexpr int32_t fresh_max(int32_t cap) { return kFreshMax + cap / 64; }
-
 // One workgroup table in global memory, without its hash (4 << hbits bytes).
 __host__ __device__ constexpr int64_t team_table_bytes(int32_t cap) {
     return ((int64_t)cap * (kRecordBytes + 4) +
-            ((int64_t)cap + fresh_max(cap)) * (cap >= kRecordMinEntries ? 4 : 2) + 255) & ~(int64_t)255;
+            (int64_t)cap * (cap >= kRecordMinEntries ? 4 : 2) + 255) & ~(int64_t)255;
 }
 
 hipError_t launch_degrees(const int32_t *row_ptr, const uint8_t *w, int32_t *kdeg, int32_t n,

@@ -186,8 +186,9 @@ struct St {
                                     // committed count at the last record written
     uint64_t srows, srow_len;       // seed-set rows of a set in its first tier
     double qtop, qscale;            // compact LDS tables: rank range of the queue's buckets
-    double nqtop, nqscale;          // ... of the next growth call
+    double qhi, qlo, qalpha;        // the ranks' range at the last build, and its scale
     int32_t flen;                   // ... entries on the fresh list
+    int32_t nadd, nrem;             // ... additions and removals at the scale being grown
     bool emitted;                   // a record was written in this tier
 };
 
@@ -818,7 +819,7 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
                 }
                 if (pend_err)
                     atomicOr(A.err, pend_err);
-                unsigned long long *sx = A.stat + kStatWords * A.stat_slot;
+                unsigned long long *sx = A.stat + kStatWords * A.tier;
                 for (int q = 0; q < kStatWords; ++q)
                     if (q >= 6 || !pend_ovf)
                         atomicAdd(&sx[q], (unsigned long long)pend_stat[q]);
@@ -1151,6 +1152,8 @@ constexpr int kTeamMaxWaves = 8;
 // Rank buckets of the queue of a workgroup on a global-memory table.
 constexpr int kBuckets = 256;
 
+constexpr int kMovedMax = 128;
+
 struct TeamSh {
     double r[kTeamMaxWaves];
     int32_t u[kTeamMaxWaves];
@@ -1181,9 +1184,10 @@ struct TeamSh {
         double r;
         int32_t u, i;
         uint32_t v;
-        int32_t k, beg;
+        int32_t k, beg, pos;
     } slot[2][kTeamMaxWaves];
     int32_t done;     // waves whose rows are finished (initialisation)
+    int32_t moved[kMovedMax];   // entries added at the scale being grown, see emit_moved
 };
 static_assert(sizeof(TeamSh) <= kTeamShBytes, "the tier sizes count the workgroup's own LDS");
 
@@ -1304,31 +1308,42 @@ __device__ __forceinline__ int32_t bucket_at(const TeamSh &sh, int32_t lo, int32
 // ---------------------------------------------------------------------------
 enum { T_LDS = 0, T_PACK = 1, T_WIDE = 2 };
 
+// The fresh list of a table in global memory: its entries' fields live here
+// while they are on it (the record keeps the flag kFresh and the place), so
+// that a step reads the list from LDS and a row writes it there.
+template <int N>
+struct FreshSh {
+    double r[N];
+    uint32_t v[N];
+    int32_t u[N], k[N], beg[N];
+    int32_t i[N];   // table entry; -1: it became a member
+};
+
 template <int L>
 struct BTab {
     static constexpr bool G = L != T_LDS;
+    static constexpr int FM = L == T_WIDE ? kFreshMaxWide : kFreshMax;   // fresh-list entries kept
     using Q = std::conditional_t<L == T_WIDE, uint32_t, uint16_t>;
+    using F = FreshSh<FM>;
     double *lt;        // L(x) for x < kBlockLogs (LDS)
     uint32_t *hw;      // hash slots: tag over entry index
-    Q *sq;             // queue, cap entry indices, then the fresh list
+    Q *sq;             // queue, cap entry indices; T_LDS: then the fresh list
+    F *fs;             // else: the fresh list
     double *rk;        // T_LDS: entries as arrays
     int32_t *node, *kv, *beg;
     uint32_t *dv;
-    char *rec;         // else: records {d|flags, node, degree, row start, rank, hash slot}
+    char *rec;         // else: records {rank, d|flags, fresh place, node, degree, row start, hash slot}
     int32_t *scr;      // scratch i32[cap] (emission, resume, removal): T_LDS the ranks'
                        // place, which hold nothing once a call's additions are over
     uint32_t hmask;
     int hbits, ibits;  // ibits: index bits of a hash slot, T_WIDE (16 otherwise)
     int cap;
-    int fmax;          // fresh-list entries kept
     __device__ __forceinline__ char *at(int32_t i) const { return rec + (size_t)(uint32_t)i * kRecordBytes; }
-    __device__ __forceinline__ double &RK(int32_t i) const {
-        return G ? *(double *)(at(i) + 16) : rk[i];
-    }
-    __device__ __forceinline__ uint32_t &DV(int32_t i) const { return G ? *(uint32_t *)at(i) : dv[i]; }
-    __device__ __forceinline__ int32_t &NODE(int32_t i) const { return G ? *(int32_t *)(at(i) + 4) : node[i]; }
-    __device__ __forceinline__ int32_t &KV(int32_t i) const { return G ? *(int32_t *)(at(i) + 8) : kv[i]; }
-    __device__ __forceinline__ uint32_t &SLOT(int32_t i) const { return *(uint32_t *)(at(i) + 24); }
+    __device__ __forceinline__ double &RK(int32_t i) const { return G ? *(double *)at(i) : rk[i]; }
+    __device__ __forceinline__ uint32_t &DV(int32_t i) const { return G ? *(uint32_t *)(at(i) + 8) : dv[i]; }
+    __device__ __forceinline__ int32_t &NODE(int32_t i) const { return G ? *(int32_t *)(at(i) + 16) : node[i]; }
+    __device__ __forceinline__ int32_t &KV(int32_t i) const { return G ? *(int32_t *)(at(i) + 20) : kv[i]; }
+    __device__ __forceinline__ uint32_t &SLOT(int32_t i) const { return *(uint32_t *)(at(i) + 28); }
     __device__ __forceinline__ int shift() const { return L == T_WIDE ? ibits : 16; }
 };
 
@@ -1337,34 +1352,44 @@ struct Ent {
     uint32_t v;
     int32_t u, k, beg;
     double r;
+    int32_t pos;   // tables in global memory: place on the fresh list, if kFresh is set
 };
 
 template <int L>
 __device__ __forceinline__ Ent ent_get(const BTab<L> &t, int32_t i) {
     Ent e;
     if constexpr (L != T_LDS) {
-        const char *p = t.at(i);
-        const int4 a = *(const int4 *)p;
-        e.v = (uint32_t)a.x;
-        e.u = a.y;
-        e.k = a.z;
-        e.beg = a.w;
-        e.r = *(const double *)(p + 16);
+        const int4 *p = (const int4 *)t.at(i);
+        const int4 a = p[0], b = p[1];
+        e.r = __hiloint2double(a.y, a.x);
+        e.v = (uint32_t)a.z;
+        e.pos = a.w;
+        e.u = b.x;
+        e.k = b.y;
+        e.beg = b.z;
     } else {
         e.v = t.dv[i];
         e.u = t.node[i];
         e.k = t.kv[i];
         e.beg = t.beg[i];
         e.r = t.rk[i];
+        e.pos = -1;
     }
     return e;
+}
+
+// A record's first half.
+template <int L>
+__device__ __forceinline__ void ent_put(const BTab<L> &t, int32_t i, double r, uint32_t v, int32_t pos) {
+    *(int4 *)t.at(i) = make_int4(__double2loint(r), __double2hiint(r), (int32_t)v, pos);
 }
 
 // A new entry with d = 0 (its rank follows with its first re-rank).
 template <int L>
 __device__ __forceinline__ void ent_new(const BTab<L> &t, int32_t i, int32_t u, int32_t k, int32_t beg) {
     if constexpr (L != T_LDS) {
-        *(int4 *)t.at(i) = make_int4(0, u, k, beg);
+        ent_put(t, i, 0.0, 0u, -1);
+        *(int4 *)(t.at(i) + 16) = make_int4(u, k, beg, -1);
     } else {
         t.dv[i] = 0u;
         t.node[i] = u;
@@ -1389,7 +1414,7 @@ __device__ __forceinline__ BTab<T_LDS> carve_lds(char *lds, int cap, int hbits) 
     t.hbits = hbits;
     t.ibits = 16;
     t.cap = cap;
-    t.fmax = kFreshMax;
+    t.fs = nullptr;
     return t;
 }
 
@@ -1397,7 +1422,7 @@ __device__ __forceinline__ BTab<T_LDS> carve_lds(char *lds, int cap, int hbits) 
 // fill empties them.
 template <int L>
 __device__ __forceinline__ BTab<L> carve_slab(char *slab, int64_t stride, int32_t n_slots, int slot, double *lt,
-                                              int cap, int hbits) {
+                                              typename BTab<L>::F *fs, int cap, int hbits) {
     BTab<L> t;
     t.lt = lt;
     t.hw = (uint32_t *)(slab + ((size_t)slot << (hbits + 2)));
@@ -1412,7 +1437,7 @@ __device__ __forceinline__ BTab<L> carve_slab(char *slab, int64_t stride, int32_
     t.hbits = hbits;
     t.ibits = 33 - __builtin_clz((uint32_t)cap - 1);   // an index and the claim bit
     t.cap = cap;
-    t.fmax = fresh_max(cap);
+    t.fs = fs;
     return t;
 }
 
@@ -1448,23 +1473,9 @@ __device__ __forceinline__ uint32_t group_of(const BTab<L> &t, uint32_t h) {
     return (h >> (32 - t.hbits)) & ~3u;
 }
 
-// A group.  Global slots change by compare-and-swap in the L2, so they are read
-// from there.
-template <int L>
-__device__ __forceinline__ uint4 group_get(const BTab<L> &t, uint32_t p) {
-    if constexpr (L != T_LDS) {
-        const uint64_t *q = (const uint64_t *)(t.hw + p);
-        const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
-    } else {
-        return *(const uint4 *)(t.hw + p);
-    }
-}
-
 template <int L>
 __device__ __forceinline__ void slot_put(const BTab<L> &t, uint32_t p, uint32_t v) {
-    __hip_atomic_store(t.hw + p, v, __ATOMIC_RELAXED, L != T_LDS ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_store(t.hw + p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Before a hash slot is written that another wave may follow, and after one
@@ -1509,7 +1520,7 @@ __device__ __forceinline__ void block_find(const BTab<L> &t, int32_t u, int32_t 
     idx = -1;
     slot = kNoSlot;
     for (uint32_t it = 0; it <= t.hmask; it += 4) {
-        const uint4 g = group_get(t, p);
+        const uint4 g = *(const uint4 *)(t.hw + p);
         const uint32_t room = group_empty(g);
         uint32_t m = group_tagged(g, h, t.shift()) & ~room;
         slot_acquire<L>();
@@ -1536,8 +1547,13 @@ __device__ __forceinline__ uint32_t block_claim(const BTab<L> &t, uint32_t p, ui
     if (p == kNoSlot)
         return kNoSlot;
     for (uint32_t it = 0; it <= t.hmask; ++it) {
-        if (atomicCAS(&t.hw[p], kNoSlot, v) == kNoSlot)
+        if (atomicCAS(&t.hw[p], kNoSlot, v) == kNoSlot) {
+            // the swap is done in the L2; a store also goes through the L1,
+            // from which groups are read
+            if constexpr (L != T_LDS)
+                slot_put(t, p, v);
             return p;
+        }
         p = (p + 1) & t.hmask;
     }
     return kNoSlot;
@@ -1682,26 +1698,46 @@ __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, 
         } else {
             const bool fresh = act && idx < 0;
             block_add(t, sh, st, id, fresh, e.x, e.y, e.z, slot, solo, idx);
+            // a non-member neighbour is (re)queued with its new rank: on the
+            // fresh list already, or to be listed (in the queue unless
+            // popped: queue entries at once, fresh ones by the next scan)
             bool list = false;
+            uint32_t v = 0u;
+            double r = 0.0;
             if (act && idx >= 0) {
-                const uint32_t v = fresh ? 0u : a.v;
+                const bool here = L != T_LDS && !fresh && (a.v & kFresh) && (uint32_t)a.pos < (uint32_t)BTab<L>::FM;
+                v = fresh ? 0u : a.v;
+                r = a.r;
+                if constexpr (L != T_LDS) {
+                    if (here) {
+                        v = t.fs->v[a.pos];
+                        r = t.fs->r[a.pos];
+                    }
+                }
                 const int32_t d = (int32_t)(v & kDMask) + e.w;
                 if (v & kMember) {
                     t.DV(idx) = (v & ~kDMask) | (uint32_t)d;
                 } else {
-                    // in the queue unless popped (queue entries at once, fresh
-                    // ones by the next scan, see team_row)
-                    const bool popped = !(v & kLive) || ((v & kFresh) && before(a.r, e.x, st.pr, st.pu));
+                    const bool popped = !(v & kLive) || ((v & kFresh) && before(r, e.x, st.pr, st.pu));
                     if (popped)
                         st.Gl += 1;
                     list = !(v & kFresh);
-                    t.RK(idx) = block_log(t, c, 2 * d) - st.alpha * x.lk;
+                    r = block_log(t, c, 2 * d) - st.alpha * x.lk;
                     st.Rl += 1;
-                    t.DV(idx) = (v & kWas) | (uint32_t)d | kLive | kFresh | kTouch;
+                    v = (v & kWas) | (uint32_t)d | kLive | kFresh | kTouch;
+                    if constexpr (L == T_LDS) {
+                        t.RK(idx) = r;
+                        t.DV(idx) = v;
+                    } else if (here) {
+                        t.fs->v[a.pos] = v;
+                        t.fs->r[a.pos] = r;
+                    } else if (!list) {
+                        ent_put(t, idx, r, v, BTab<L>::FM);   // past the list's end
+                    }
                 }
             }
-            // the fresh list; entries past its end are found by the rebuild
-            // that its length then asks for
+            // entries past the list's end are found by the rebuild that its
+            // length then asks for
             const uint64_t m = __ballot(list);
             if (m) {
                 int32_t at = st.flen;
@@ -1715,8 +1751,20 @@ __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, 
                     at = __builtin_amdgcn_readlane(at, lead);
                 }
                 at += __popcll(m & lanes_below(id.lane));
-                if (list && at < t.fmax)
-                    t.sq[t.cap + at] = (typename BTab<L>::Q)idx;
+                if constexpr (L == T_LDS) {
+                    if (list && at < BTab<L>::FM)
+                        t.sq[t.cap + at] = (uint16_t)idx;
+                } else if (list) {
+                    ent_put(t, idx, r, v, min(at, BTab<L>::FM));
+                    if (at < BTab<L>::FM) {
+                        t.fs->r[at] = r;
+                        t.fs->v[at] = v;
+                        t.fs->u[at] = e.x;
+                        t.fs->k[at] = e.y;
+                        t.fs->beg[at] = e.z;
+                        t.fs->i[at] = idx;
+                    }
+                }
             }
         }
     }
@@ -1808,7 +1856,7 @@ __device__ void block_edges(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, 
             uint32_t from = 0;   // slots of the group already known to be others'
             uint32_t it = 0;
             for (; it <= t.hmask; ++it) {
-                const uint4 g = group_get(t, p);
+                const uint4 g = *(const uint4 *)(t.hw + p);
                 uint32_t room = group_empty(g) & ~from;
                 uint32_t m = group_tagged(g, h, t.shift()) & ~group_empty(g);
                 slot_acquire<L>();
@@ -1932,10 +1980,11 @@ __device__ void team_init(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, co
     st.K = (int64_t)team_sum(sh, id, K);
     st.V = (int64_t)team_sum(sh, id, V);
     st.nmem = n_init;
-    // the first call's buckets: ranks lie in [-L(kmax), L(2 kmax)] at alpha <= 1
-    // (a rank outside goes to the first or last bucket)
-    st.qtop = c.logtab[c.logtab_last];
-    st.qscale = (double)kBuckets / (2.0 * st.qtop + 1.0);
+    // the first call's buckets: ranks lie in [-alpha L(kmax), L(2 kmax)] (a rank
+    // outside the range goes to the first or last bucket)
+    st.qhi = c.logtab[c.logtab_last];
+    st.qlo = 0.0;
+    st.qalpha = 0.0;
     // rows were counted per wave
     st.rows = team_sum(sh, id, id.lane == 0 ? st.rows : 0);
     st.row_len = team_sum(sh, id, id.lane == 0 ? st.row_len : 0);
@@ -1969,6 +2018,7 @@ struct Picked {
     int32_t u, i;
     uint32_t v;
     int32_t k, beg;
+    int32_t pos;   // place on the fresh list, or -1
 };
 
 // Lane l's candidate in every lane (scalar registers).
@@ -1979,11 +2029,13 @@ __device__ __forceinline__ void pick_lane(int l, const Ent &e, int32_t i, Picked
     o.v = (uint32_t)__builtin_amdgcn_readlane((int)e.v, l);
     o.k = __builtin_amdgcn_readlane(e.k, l);
     o.beg = __builtin_amdgcn_readlane(e.beg, l);
+    o.pos = __builtin_amdgcn_readlane(e.pos, l);
 }
 
-// The waves' candidates (lane l of each, l < 0: none) into one set of slots;
-// after the barrier each lane holds one wave's (i < 0: none).
-__device__ __forceinline__ void slot_exchange(TeamSh &sh, const TeamId &id, int &par, int l, Ent &e, int32_t &i) {
+// The waves' candidates (lane l of each, l < 0: none) into one set of slots,
+// read after the barrier.
+__device__ __forceinline__ const TeamSh::Slot *slot_put(TeamSh &sh, const TeamId &id, int &par, int l, const Ent &e,
+                                                        int32_t i) {
     TeamSh::Slot *s = sh.slot[par];
     par ^= 1;
     if (id.lane == max(l, 0)) {
@@ -1993,31 +2045,45 @@ __device__ __forceinline__ void slot_exchange(TeamSh &sh, const TeamId &id, int 
         s[id.wid].v = e.v;
         s[id.wid].k = e.k;
         s[id.wid].beg = e.beg;
+        s[id.wid].pos = e.pos;
     }
     __syncthreads();
-    const int w = id.lane < id.nw ? id.lane : 0;
-    e.r = s[w].r;
-    e.u = s[w].u;
-    i = id.lane < id.nw ? s[w].i : -1;
-    e.v = s[w].v;
-    e.k = s[w].k;
-    e.beg = s[w].beg;
+    return s;
+}
+
+// Slot w's candidate (false: none), in scalar registers.
+__device__ __forceinline__ bool slot_take(const TeamSh::Slot *s, int w, Picked &o) {
+    w = __builtin_amdgcn_readfirstlane(w);
+    o.i = __builtin_amdgcn_readfirstlane(s[w].i);
+    o.r = read_lane(s[w].r, 0);
+    o.u = __builtin_amdgcn_readfirstlane(s[w].u);
+    o.v = (uint32_t)__builtin_amdgcn_readfirstlane((int)s[w].v);
+    o.k = __builtin_amdgcn_readfirstlane(s[w].k);
+    o.beg = __builtin_amdgcn_readfirstlane(s[w].beg);
+    o.pos = __builtin_amdgcn_readfirstlane(s[w].pos);
+    return o.i >= 0;
 }
 
 // The workgroup's first entry in queue order among the lanes' candidates (i
-// < 0: none).  One barrier; set `par` of the slots is used and toggled.
+// < 0: none).  One barrier; set `par` of the slots is used and toggled.  Two
+// waves compare their slots, more of them reduce over the lanes again.
 __device__ __forceinline__ bool block_pick_max(TeamSh &sh, const TeamId &id, int &par, Ent e, int32_t i, Picked &o) {
     int l = wave_first(e.r, e.u, i);
-    if (id.nw > 1) {
-        slot_exchange(sh, id, par, l, e, i);
-        l = wave_first(e.r, e.u, i);
-    } else {
+    if (id.nw == 1) {
         __syncthreads();
+        if (l < 0)
+            return false;
+        pick_lane(l, e, i, o);
+        return true;
     }
-    if (l < 0)
-        return false;
-    pick_lane(l, e, i, o);
-    return true;
+    const TeamSh::Slot *s = slot_put(sh, id, par, l, e, i);
+    if (id.nw == 2) {
+        l = s[1].i >= 0 && (s[0].i < 0 || before(s[1].r, s[1].u, s[0].r, s[0].u)) ? 1 : 0;
+    } else {
+        const int w = id.lane < id.nw ? id.lane : 0;
+        l = max(wave_first(s[w].r, s[w].u, id.lane < id.nw ? s[w].i : -1), 0);
+    }
+    return slot_take(s, l, o);
 }
 
 __device__ __forceinline__ int wave_smallest(int32_t u, int32_t i) {
@@ -2029,16 +2095,17 @@ __device__ __forceinline__ int wave_smallest(int32_t u, int32_t i) {
 // The workgroup's smallest id u (i < 0: none).
 __device__ __forceinline__ bool block_pick_min(TeamSh &sh, const TeamId &id, int &par, Ent e, int32_t i, Picked &o) {
     int l = wave_smallest(e.u, i);
-    if (id.nw > 1) {
-        slot_exchange(sh, id, par, l, e, i);
-        l = wave_smallest(e.u, i);
-    } else {
+    if (id.nw == 1) {
         __syncthreads();
+        if (l < 0)
+            return false;
+        pick_lane(l, e, i, o);
+        return true;
     }
-    if (l < 0)
-        return false;
-    pick_lane(l, e, i, o);
-    return true;
+    const TeamSh::Slot *s = slot_put(sh, id, par, l, e, i);
+    const int w = id.lane < id.nw ? id.lane : 0;
+    l = max(wave_smallest(s[w].u, id.lane < id.nw ? s[w].i : -1), 0);
+    return slot_take(s, l, o);
 }
 
 // The bucketed queue: ns entries, positions before cp hold only
@@ -2057,7 +2124,7 @@ __device__ __forceinline__ int32_t lq_start(const LQ &q, int32_t b) {
 }
 
 __device__ __forceinline__ int32_t lq_bucket(const St &st, double r) {
-    return (int32_t)fmin(fmax((st.qtop - r) * st.qscale, 0.0), (double)(kBuckets - 1));
+    return (int32_t)fmin(fmax((st.qtop - r) * st.qscale, 0.0), (double)(kBuckets - 2));
 }
 
 // Exclusive prefix of the bucket counts in sh.fill, four buckets per lane: the
@@ -2091,6 +2158,26 @@ __device__ __forceinline__ void bucket_starts(TeamSh &sh, const TeamId &id) {
     }
 }
 
+// Write the fresh list back into the records, its pending pops applied, and
+// empty it (a barrier at the end; T_LDS: nothing to do).
+template <int L>
+__device__ __forceinline__ void fresh_flush(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id) {
+    if constexpr (L != T_LDS) {
+        const int32_t nf = min(st.flen, BTab<L>::FM);
+        for (int32_t f = id.tid; f < nf; f += id.nt) {
+            const int32_t i = t.fs->i[f];
+            if (i < 0)
+                continue;
+            uint32_t v = t.fs->v[f];
+            const double r = t.fs->r[f];
+            if (!(v & kTouch) && before(r, t.fs->u[f], st.pr, st.pu))
+                v &= ~kLive;
+            ent_put(t, i, r, v & ~(kFresh | kTouch), -1);
+        }
+        __syncthreads();
+    }
+}
+
 // Sort the queue into its buckets: at a call's start (CREATE: every
 // non-member with a link into c enters it, with its rank) or when the fresh
 // list has grown long (the pops still pending on it are applied first, as by
@@ -2102,19 +2189,32 @@ __device__ __forceinline__ void lq_build(const BTab<L> &t, TeamSh &sh, St &st, c
     st.scanned += 2 * (uint64_t)st.count;
     for (int32_t b = id.tid; b < kBuckets; b += id.nt)
         sh.fill[b] = 0u;
+    if constexpr (CREATE) {
+        // the ranks' range of the last build, moved by the change of scale
+        st.qtop = st.qhi + fmax(st.qalpha - st.alpha, 0.0) * c.logtab[c.logtab_last] + 0.25;
+        st.qscale = (double)(kBuckets - 1) /
+                    (st.qtop - (st.qlo + fmin(st.qalpha - st.alpha, 0.0) * c.logtab[c.logtab_last]) + 0.25);
+    } else {
+        fresh_flush(t, sh, st, id);
+    }
     __syncthreads();
     if (id.tid == 0)
         sh.row.flen = 0;
     st.flen = 0;
-    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+    // tables in global memory: the buckets of a thread's entries, a byte each
+    // (kBuckets - 1: not queued), go to the scratch, so that the second pass
+    // reads one word for kScanAhead records
+    uint32_t *packed = (uint32_t *)t.scr + id.tid;
+    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt, packed += id.nt) {
         uint32_t vv[kScanAhead];
         int32_t kk[kScanAhead];
         double rr[kScanAhead];
+        uint32_t pk = 0u;
 #pragma unroll
         for (int x = 0; x < kScanAhead; ++x) {
             const int32_t i = min(base + x * id.nt, st.count - 1);
             vv[x] = t.DV(i);
-            kk[x] = CREATE ? t.KV(i) : t.NODE(i);
+            kk[x] = CREATE ? t.KV(i) : L == T_LDS ? t.NODE(i) : 0;
             rr[x] = CREATE ? 0.0 : t.RK(i);
         }
         if constexpr (CREATE) {
@@ -2129,34 +2229,34 @@ __device__ __forceinline__ void lq_build(const BTab<L> &t, TeamSh &sh, St &st, c
             const int32_t i = base + x * id.nt;
             const uint32_t v = vv[x];
             const double r = rr[x];
-            if (i >= st.count)
-                continue;
             uint32_t nv;
             bool in = false;
             if constexpr (CREATE) {
-                nv = v & ~(kLive | kFresh | kTouch);
-                if (!(v & kMember) && (v & kDMask) != 0) {
-                    in = true;
-                    nv |= kLive;
-                    t.RK(i) = r;
-                    st.Rl += 1;
-                    st.Gl += 1;
+                in = i < st.count && !(v & kMember) && (v & kDMask) != 0;
+                nv = (v & ~(kLive | kFresh | kTouch)) | (in ? kLive : 0u);
+                if (in) {
+                    if constexpr (L == T_LDS)
+                        t.RK(i) = r;
+                    else
+                        ent_put(t, i, r, nv, -1);
                     hi = fmax(hi, r);
                     lo = fmin(lo, r);
                 }
             } else {
-                nv = v & ~(kFresh | kTouch);
-                if ((v & kLive) && !(v & kMember)) {
-                    in = !((v & kFresh) && !(v & kTouch) && before(r, kk[x], st.pr, st.pu));
-                    if (!in)
-                        nv &= ~kLive;
-                }
+                in = i < st.count && (v & kLive) && !(v & kMember);
+                if (in && (v & kFresh) && !(v & kTouch))
+                    in = !before(r, L == T_LDS ? kk[x] : t.NODE(i), st.pr, st.pu);
+                nv = v & ~(kFresh | kTouch | (in ? 0u : kLive));
             }
+            const int32_t b = lq_bucket(st, r);
             if (in)
-                atomicAdd(&sh.fill[lq_bucket(st, r)], 1u);
-            if (nv != v)
+                atomicAdd(&sh.fill[b], 1u);
+            if (i < st.count && nv != v && !(CREATE && L != T_LDS && in))
                 t.DV(i) = nv;
+            pk |= (uint32_t)(in ? b : kBuckets - 1) << (8 * x);
         }
+        if constexpr (L != T_LDS)
+            *packed = pk;
     }
     if constexpr (CREATE) {
         const double h = wave_max(hi), l = -wave_max(-lo);
@@ -2173,40 +2273,88 @@ __device__ __forceinline__ void lq_build(const BTab<L> &t, TeamSh &sh, St &st, c
         q.s4[j] = sh.bstart[4 * id.lane + j];
     q.ns = __builtin_amdgcn_readfirstlane(sh.bstart[kBuckets]);
     q.cp = 0;
-    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
-        uint32_t vv[kScanAhead];
-        double rr[kScanAhead];
+    if constexpr (L == T_LDS) {
+        for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+            uint32_t vv[kScanAhead];
+            double rr[kScanAhead];
 #pragma unroll
-        for (int x = 0; x < kScanAhead; ++x) {
-            const int32_t i = min(base + x * id.nt, st.count - 1);
-            vv[x] = t.DV(i);
-            rr[x] = t.RK(i);
+            for (int x = 0; x < kScanAhead; ++x) {
+                const int32_t i = min(base + x * id.nt, st.count - 1);
+                vv[x] = t.DV(i);
+                rr[x] = t.RK(i);
+            }
+#pragma unroll
+            for (int x = 0; x < kScanAhead; ++x) {
+                const int32_t i = base + x * id.nt;
+                if (i < st.count && (vv[x] & (kLive | kMember)) == kLive)
+                    t.sq[atomicAdd(&sh.fill[lq_bucket(st, rr[x])], 1u)] = (uint16_t)i;
+            }
         }
+    } else {
+        packed = (uint32_t *)t.scr + id.tid;
+        for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt, packed += id.nt) {
+            const uint32_t pk = *packed;
 #pragma unroll
-        for (int x = 0; x < kScanAhead; ++x) {
-            const int32_t i = base + x * id.nt;
-            if (i < st.count && (vv[x] & (kLive | kMember)) == kLive)
-                t.sq[atomicAdd(&sh.fill[lq_bucket(st, rr[x])], 1u)] = (typename BTab<L>::Q)i;
+            for (int x = 0; x < kScanAhead; ++x) {
+                const uint32_t b = (pk >> (8 * x)) & 255u;
+                if (b != kBuckets - 1)
+                    t.sq[atomicAdd(&sh.fill[b], 1u)] = (typename BTab<L>::Q)(base + x * id.nt);
+            }
         }
     }
     if constexpr (CREATE) {
-        // the next call's range; a change of scale moves it a little
         double h = sh.r[0], l = sh.r2[0];
         for (int w = 1; w < id.nw; ++w) {
             h = fmax(h, sh.r[w]);
             l = fmin(l, sh.r2[w]);
         }
-        st.nqtop = h + 0.25;
-        st.nqscale = (double)kBuckets / (h - l + 0.5);
+        st.qhi = h;
+        st.qlo = l;
+        st.qalpha = st.alpha;
     }
     __syncthreads();
+}
+
+// Whether any entry of the queue that a call starts with improves.  Most
+// calls add nothing (at least one per scale): for those the queue need not
+// be built, only counted.
+template <int L>
+__device__ __forceinline__ bool any_improves(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id) {
+    bool any = false;
+    const bool zero = st.K == 0;
+    st.scanned += (uint64_t)st.count;
+    for (int32_t base = id.tid; base < st.count; base += kScanAhead * id.nt) {
+        uint32_t vv[kScanAhead];
+        int32_t kk[kScanAhead];
+#pragma unroll
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t i = min(base + x * id.nt, st.count - 1);
+            vv[x] = t.DV(i);
+            kk[x] = t.KV(i);
+        }
+#pragma unroll
+        for (int x = 0; x < kScanAhead; ++x) {
+            const int32_t d = (int32_t)(vv[x] & kDMask);
+            const bool in = base + x * id.nt < st.count && !(vv[x] & kMember) && d != 0;
+            st.Rl += in ? 1 : 0;
+            st.Gl += in ? 1 : 0;
+            int s = zero ? 1 : settle_add(st, d, kk[x]);
+            if (in && !any && s < 0)
+                s = decide(st.K, st.V, st.K + 2 * (int64_t)d, st.V + kk[x], st.alpha) ? 1 : 0;
+            any = any || (in && s > 0);
+        }
+    }
+    if (id.nw == 1)
+        return __ballot(any) != 0;
+    return team_or(sh, id, any ? 1u : 0u) != 0;
 }
 
 // The fresh list's length from which the queue is rebuilt.  A step reads the
 // whole list and a rebuild the whole table, so the cost per addition is about
 // a count / f + b f, least at f in proportion to the root of count.
+template <int L>
 __device__ __forceinline__ int32_t fresh_limit(int32_t count) {
-    return max(kFreshRebuild, (int32_t)(4.0f * sqrtf((float)count)));
+    return min(max(kFreshRebuild, (int32_t)(4.0f * sqrtf((float)count))), BTab<L>::FM - 64);
 }
 
 // The next addition (false: no queued entry improves): the best improving
@@ -2220,111 +2368,191 @@ __device__ __forceinline__ int32_t fresh_limit(int32_t count) {
 // operations of the two overlap.
 constexpr int kStepAhead = 2;
 
+// One candidate of a step: entry e (on: it is queued; ff: on the fresh list).
+// True when it has to be written back as v; cand: +1 improves, -1 undecided.
+__device__ __forceinline__ bool step_look(const St &st, const Ent &e, bool on, bool ff, bool zero, uint32_t &v,
+                                          int &cand) {
+    const bool pop = ff && !(e.v & kTouch) && before(e.r, e.u, st.pr, st.pu);
+    v = pop ? e.v & ~kLive : e.v & ~kTouch;   // (a popped fresh entry keeps its place)
+    const int s = settle_add(st, (int32_t)(e.v & kDMask), e.k);
+    cand = on && !pop ? (zero ? 1 : s) : 0;
+    return on && v != e.v;
+}
+
+__device__ __forceinline__ void step_take(const St &st, const Ent &e, int32_t i, int cand, Ent &b, int32_t &bi) {
+    bool take = cand != 0 && before(e.r, e.u, b.r, b.u);
+    if (take && cand < 0)
+        take = decide(st.K, st.V, st.K + 2 * (int64_t)(e.v & kDMask), st.V + e.k, st.alpha);
+    b.r = take ? e.r : b.r;
+    b.u = take ? e.u : b.u;
+    b.v = take ? e.v : b.v;
+    b.k = take ? e.k : b.k;
+    b.beg = take ? e.beg : b.beg;
+    b.pos = take ? e.pos : b.pos;
+    bi = take ? i : bi;
+}
+
 template <int L>
 __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id, LQ &q, int &par,
                                         Picked &o) {
+    // entries in flight per thread: LDS tables two, to overlap the round trips;
+    // else one (a window is one entry per thread, and registers are short)
+    constexpr int A = L == T_LDS ? kStepAhead : 1;
     Ent b;
     b.r = -__builtin_huge_val();
     b.u = INT32_MAX;
     b.v = 0u;
     b.k = b.beg = 0;
+    b.pos = -1;
     int32_t bi = -1;
     const bool zero = st.K == 0;
-    int32_t nf = min(st.flen, t.fmax);   // fresh entries in this window's scan
+    int32_t nf = min(st.flen, BTab<L>::FM);   // fresh entries in this window's scan
     int32_t win = id.nt;
+    int32_t at = q.cp;    // the window's start; the ones before it hold no improving entry
     for (;;) {
-        // buckets b0 (where cp lies) and b1 (the window's end): the largest
-        // that start at or before cp and cp + win
+        // buckets b0 (where the window starts) and b1 (its end): the largest
+        // that start at or before those positions
         int32_t b0 = -1, b1 = -1;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            b0 += __popcll(__ballot(q.s4[j] <= q.cp));
-            b1 += __popcll(__ballot(q.s4[j] <= q.cp + win));
+            b0 += __popcll(__ballot(q.s4[j] <= at));
+            b1 += __popcll(__ballot(q.s4[j] <= at + win));
         }
-        b0 += q.ns <= q.cp;
-        b1 += q.ns <= q.cp + win;
+        b0 += q.ns <= at;
+        b1 += q.ns <= at + win;
         if (b1 <= b0)
             b1 = min(b0 + 1, kBuckets);
         const int32_t end = lq_start(q, b1);
-        const int32_t total = nf + (end - q.cp);
+        const int32_t total = nf + (end - at);
         st.scanned += (uint64_t)total;
-        Ent ee[kStepAhead];
-        int32_t ii[kStepAhead];
-        bool wi[kStepAhead];   // queued entries of the window
-        for (int32_t x0 = 0; x0 < total; x0 += kStepAhead * id.nt) {
-            bool in[kStepAhead], ff[kStepAhead];
+        // one: its entries stay in registers for their pops
+        bool one;
+        Ent ee[A];
+        int32_t ii[A];
+        bool wi[A];   // queued entries of the window
+        uint32_t nv;
+        int ok[A];
+        if constexpr (L == T_LDS) {
+            one = at == q.cp && total <= A * id.nt;
+            for (int32_t x0 = 0; x0 < total; x0 += A * id.nt) {
+                bool in[A], ff[A];
 #pragma unroll
-            for (int y = 0; y < kStepAhead; ++y) {
-                const int32_t x = x0 + y * id.nt + id.tid;
-                in[y] = x < total;
-                ff[y] = x < nf;
-                // the fresh list lies right behind the queue
-                ii[y] = (int32_t)t.sq[in[y] ? (ff[y] ? t.cap + x : q.cp + x - nf) : 0];
+                for (int y = 0; y < A; ++y) {
+                    const int32_t x = x0 + y * id.nt + id.tid;
+                    in[y] = x < total;
+                    ff[y] = x < nf;
+                    // the fresh list lies right behind the queue
+                    ii[y] = (int32_t)t.sq[in[y] ? (ff[y] ? t.cap + x : at + x - nf) : 0];
+                }
+#pragma unroll
+                for (int y = 0; y < A; ++y) {
+                    ii[y] = in[y] ? ii[y] : 0;
+                    ee[y] = ent_get(t, ii[y]);
+                }
+#pragma unroll
+                for (int y = 0; y < A; ++y) {
+                    const bool on =
+                        in[y] && (ee[y].v & (kLive | kFresh | kMember)) == (ff[y] ? kLive | kFresh : kLive);
+                    wi[y] = on && !ff[y];
+                    if (step_look(st, ee[y], on, ff[y], zero, nv, ok[y]))
+                        t.DV(ii[y]) = nv;
+                }
+#pragma unroll
+                for (int y = 0; y < A; ++y)
+                    step_take(st, ee[y], ii[y], ok[y], b, bi);
             }
+        } else {
+            // the window's first entry of each thread is in flight while the
+            // fresh list is looked at
+            one = at == q.cp && end - at <= A * id.nt;
+            bool in[A];
+            const auto load = [&](int32_t x0) {
 #pragma unroll
-            for (int y = 0; y < kStepAhead; ++y) {
-                ii[y] = in[y] ? ii[y] : 0;
-                ee[y] = ent_get(t, ii[y]);
+                for (int y = 0; y < A; ++y) {
+                    const int32_t x = x0 + y * id.nt;
+                    in[y] = x < end;
+                    ii[y] = (int32_t)t.sq[in[y] ? x : 0];
+                }
+#pragma unroll
+                for (int y = 0; y < A; ++y) {
+                    ii[y] = in[y] ? ii[y] : 0;
+                    ee[y] = ent_get(t, ii[y]);
+                }
+            };
+            int32_t x0 = at + id.tid;
+            load(x0);
+            for (int32_t f0 = id.tid; f0 < nf; f0 += A * id.nt) {
+                Ent g[A];
+                int32_t gi[A];
+#pragma unroll
+                for (int y = 0; y < A; ++y) {
+                    const int32_t f = f0 + y * id.nt, p = min(f, BTab<L>::FM - 1);
+                    g[y].r = t.fs->r[p];
+                    g[y].v = t.fs->v[p];
+                    g[y].u = t.fs->u[p];
+                    g[y].k = t.fs->k[p];
+                    g[y].beg = t.fs->beg[p];
+                    g[y].pos = p;
+                    gi[y] = f < nf ? t.fs->i[p] : -1;
+                }
+#pragma unroll
+                for (int y = 0; y < A; ++y)
+                    if (step_look(st, g[y], gi[y] >= 0 && (g[y].v & kLive), true, zero, nv, ok[y]))
+                        t.fs->v[g[y].pos] = nv;
+#pragma unroll
+                for (int y = 0; y < A; ++y)
+                    step_take(st, g[y], gi[y], ok[y], b, bi);
             }
-            int ok[kStepAhead];
+            for (;;) {
 #pragma unroll
-            for (int y = 0; y < kStepAhead; ++y) {
-                const uint32_t v = ee[y].v;
-                const bool on =
-                    in[y] && (v & (kLive | kFresh | kMember)) == (ff[y] ? kLive | kFresh : kLive);
-                const bool pop = ff[y] && !(v & kTouch) && before(ee[y].r, ee[y].u, st.pr, st.pu);
-                const uint32_t nv = pop ? v & ~kLive : v & ~kTouch;   // (a popped fresh entry keeps its slot)
-                if (on && nv != v)
-                    t.DV(ii[y]) = nv;
-                wi[y] = on && !ff[y];
-                const int s = settle_add(st, (int32_t)(v & kDMask), ee[y].k);
-                ok[y] = on && !pop ? (zero ? 1 : s) : 0;
-            }
+                for (int y = 0; y < A; ++y) {
+                    wi[y] = in[y] && (ee[y].v & (kLive | kFresh | kMember)) == kLive;
+                    step_look(st, ee[y], wi[y], false, zero, nv, ok[y]);
+                    ee[y].pos = -1;
+                }
 #pragma unroll
-            for (int y = 0; y < kStepAhead; ++y) {
-                bool take = ok[y] != 0 && before(ee[y].r, ee[y].u, b.r, b.u);
-                if (take && ok[y] < 0)
-                    take = decide(st.K, st.V, st.K + 2 * (int64_t)(ee[y].v & kDMask), st.V + ee[y].k, st.alpha);
-                b.r = take ? ee[y].r : b.r;
-                b.u = take ? ee[y].u : b.u;
-                b.v = take ? ee[y].v : b.v;
-                b.k = take ? ee[y].k : b.k;
-                b.beg = take ? ee[y].beg : b.beg;
-                bi = take ? ii[y] : bi;
+                for (int y = 0; y < A; ++y)
+                    step_take(st, ee[y], ii[y], ok[y], b, bi);
+                x0 += A * id.nt;
+                if (x0 - id.tid >= end)
+                    break;
+                load(x0);
             }
         }
         const bool found = block_pick_max(sh, id, par, b, bi, o);
         const int32_t bo = found ? __builtin_amdgcn_readfirstlane(lq_bucket(st, o.r)) : kBuckets;
         const bool last = end >= q.ns;
         const bool decided = found && (bo < b1 || last);
-        if (total <= kStepAhead * id.nt) {
-            // (one round: its entries are still in registers)
+        if (!decided) {
+            // (nothing reads a call's flags once no entry improves)
+            if (last)
+                return false;
+            at = end;
+            win *= 8;
+            nf = 0;
+            continue;
+        }
+        // pop what ranks above the addition
+        if (one) {
             if (total > 0) {
 #pragma unroll
-                for (int y = 0; y < kStepAhead; ++y)
-                    if (wi[y] && (!decided || (ii[y] != o.i && before(ee[y].r, ee[y].u, o.r, o.u))))
+                for (int y = 0; y < A; ++y)
+                    if (wi[y] && ii[y] != o.i && before(ee[y].r, ee[y].u, o.r, o.u))
                         t.DV(ii[y]) = ee[y].v & ~kLive;
             }
         } else {
             for (int32_t p = q.cp + id.tid; p < end; p += id.nt) {
                 const int32_t i = t.sq[p];
                 const uint32_t v = t.DV(i);
-                if ((v & (kLive | kFresh | kMember)) == kLive &&
-                    (!decided || (i != o.i && before(t.RK(i), t.NODE(i), o.r, o.u))))
+                if ((v & (kLive | kFresh | kMember)) == kLive && i != o.i &&
+                    before(t.RK(i), t.NODE(i), o.r, o.u))
                     t.DV(i) = v & ~kLive;
             }
         }
-        if (decided) {
-            // the buckets before the addition's hold only popped entries
-            q.cp = max(q.cp, lq_start(q, bo));
-            __syncthreads();   // the pops are in place before the row's updates
-            return true;
-        }
-        if (last)
-            return false;
-        q.cp = end;
-        win *= 2;
-        nf = 0;
+        // the buckets before the addition's hold only popped entries
+        q.cp = max(q.cp, lq_start(q, bo));
+        __syncthreads();   // the pops are in place before the row's updates
+        return true;
     }
 }
 
@@ -2393,16 +2621,24 @@ __device__ int64_t team_grow(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c,
                              int32_t by_id_min) {
     int64_t moves = 0;
     int par = 0;
+    if (!any_improves(t, sh, st, id))
+        return 0;
     LQ q;
     lq_build<true>(t, sh, st, c, id, q);
     for (;;) {
-        if (st.flen > fresh_limit(st.count))
+        if (st.flen > fresh_limit<L>(st.count))
             lq_build<false>(t, sh, st, c, id, q);
         Picked o;
         if (!lq_step(t, sh, st, id, q, par, o))
             break;
-        if (id.tid == 0)
+        if (id.tid == 0) {
             t.DV(o.i) = (o.v | kMember) & ~(kLive | kFresh | kTouch);
+            if (L != T_LDS && o.pos >= 0)
+                t.fs->i[o.pos] = -1;
+            if (st.nadd < kMovedMax)
+                sh.moved[st.nadd] = o.i;
+        }
+        st.nadd += 1;
         st.K += 2 * (int64_t)(o.v & kDMask);
         st.V += o.k;
         st.nmem += 1;
@@ -2421,8 +2657,7 @@ __device__ int64_t team_grow(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c,
         if (st.err & ERR_TIMEOUT)
             return moves;
     }
-    st.qtop = st.nqtop;
-    st.qscale = st.nqscale;
+    fresh_flush(t, sh, st, id);
     if (moves == 0)
         return 0;
     // removal passes over the members in ascending id
@@ -2480,6 +2715,7 @@ __device__ int64_t team_grow(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c,
                 break;
             if (id.tid == 0)
                 t.DV(o.i) = o.v & ~kMember;
+            st.nrem += 1;
             st.K -= 2 * (int64_t)(o.v & kDMask);
             st.V -= o.k;
             st.nmem -= 1;
@@ -2597,7 +2833,7 @@ __device__ bool team_toggle_records(const SweepArgs &A, const T &t, TeamSh &sh, 
 
 // Sort a[0..m) (global memory) through the LDS buffer lbuf when it fits:
 // the bitonic network's rounds then wait on LDS, not on memory.
-constexpr int kLdsSort = 1024;
+constexpr int kLdsSort = (int)(sizeof(FreshSh<kFreshMax>) / 4);
 
 __device__ void team_sort_via(int32_t *a, int32_t m, const TeamId &id, int32_t *lbuf) {
     if (m <= 1)
@@ -2613,6 +2849,64 @@ __device__ void team_sort_via(int32_t *a, int32_t m, const TeamId &id, int32_t *
     for (int32_t i = id.tid; i < m; i += id.nt)
         a[i] = lbuf[i];
     __syncthreads();
+}
+
+// The ids added at a scale that removed none, ascending, in sh.resv[0 .. na)
+// (na = st.nadd <= kMovedMax): by counting the smaller ones.  Delta output:
+// their entries are marked as emitted.
+template <class T>
+__device__ void moved_ids(const T &t, TeamSh &sh, const TeamId &id, int32_t na, bool mark) {
+    const int32_t i = id.tid < na ? sh.moved[id.tid] : 0;
+    const int32_t j = id.tid + id.nt < na ? sh.moved[id.tid + id.nt] : 0;   // (na <= 2 * 64)
+    const int32_t u = t.NODE(i), w = t.NODE(j);
+    __syncthreads();
+    if (id.tid < na) {
+        sh.moved[id.tid] = u;
+        if (mark)
+            t.DV(i) |= kWas;
+    }
+    if (id.tid + id.nt < na) {
+        sh.moved[id.tid + id.nt] = w;
+        if (mark)
+            t.DV(j) |= kWas;
+    }
+    __syncthreads();
+    int32_t ru = 0, rw = 0;
+    for (int32_t q = 0; q < na; ++q) {
+        const int32_t x = sh.moved[q];
+        ru += x < u;
+        rw += x < w;
+    }
+    if (id.tid < na)
+        sh.resv[ru] = u;
+    if (id.tid + id.nt < na)
+        sh.resv[rw] = w;
+    __syncthreads();
+}
+
+// How many of the ascending a[0 .. n) are below x (n <= 2^8 - 1).
+__device__ __forceinline__ int32_t lower_count(const int32_t *a, int32_t n, int32_t x) {
+    int32_t lo = 0;
+#pragma unroll
+    for (int step = 128; step >= 1; step >>= 1)
+        if (lo + step <= n && a[lo + step - 1] < x)
+            lo += step;
+    return lo;
+}
+
+// Merge the ascending list from[0 .. n) with the ascending ids sh.resv[0 .. na),
+// none in common, into to[0 .. n + na).
+__device__ void merge_moved(TeamSh &sh, const TeamId &id, const int32_t *from, int32_t n, int32_t na, int32_t *to) {
+    for (int32_t i = id.tid; i < n; i += id.nt) {
+        const int32_t x = from[i], y = i > 0 ? from[i - 1] : -1;
+        const int32_t a = i > 0 ? lower_count(sh.resv, na, y) : 0, b = lower_count(sh.resv, na, x);
+        to[i + b] = x;
+        for (int32_t q = a; q < b; ++q)   // the ids between y and x
+            to[i + q] = sh.resv[q];
+        if (i == n - 1)
+            for (int32_t q = b; q < na; ++q)
+                to[n + q] = sh.resv[q];
+    }
 }
 
 // lbuf: LDS sort buffer of kLdsSort entries, or nullptr (tables in LDS sort in place).
@@ -2712,6 +3006,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
 
         int64_t last_off = -1;
         int32_t last_cnt = 0;
+        bool listed = false;   // pool[last_off ..) holds the members at the last emission, ascending
         int32_t s_at = s0;   // the scale being grown (where an overflow happened)
         for (int32_t s = s0; s < A.s_end && !st.ovf && !bad && !st.err; ++s) {
             s_at = s;
@@ -2725,6 +3020,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
             st.M = 0;
             uint64_t calls = 0;
             int64_t moved = 0;
+            st.nadd = st.nrem = 0;
             for (;;) {
                 calls += 1;
                 const int64_t mv = team_grow(t, sh, st, c, id, A.k_prune, A.by_id_min);
@@ -2749,12 +3045,15 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
             int32_t dadd = 0, drem = 0;
             if ((s == s0 || moved > 0) && keyed) {
                 // delta output (see run_wave)
+                const bool few = s > s0 && st.nrem == 0 && st.nadd <= kMovedMax;
                 if (id.tid == 0) {
-                    sh.m = 0;
+                    sh.m = few ? st.nadd : 0;
                     sh.m2 = 0;
                 }
                 __syncthreads();
-                for (int32_t i = id.tid; i < st.count; i += id.nt) {
+                if (few)
+                    moved_ids(t, sh, id, st.nadd, true);
+                else for (int32_t i = id.tid; i < st.count; i += id.nt) {
                     const uint32_t v = t.DV(i);
                     const bool add = (v & kMember) && !(v & kWas);
                     const bool rem = (v & kWas) && !(v & kMember);
@@ -2767,7 +3066,8 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
                 }
                 __syncthreads();
                 const int32_t na = sh.m, nr = sh.m2;
-                team_sort_via(t.scr, na, id, lbuf);
+                if (!few)
+                    team_sort_via(t.scr, na, id, lbuf);
                 team_sort_via(t.scr + (t.cap - nr), nr, id, lbuf);
                 if (id.tid == 0)
                     sh.off = atomicAdd(A.pool_cursor, (unsigned long long)(na + nr));
@@ -2775,7 +3075,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
                 const unsigned long long off = sh.off;
                 if ((int64_t)off + na + nr <= A.pool_cap) {
                     for (int32_t i = id.tid; i < na; i += id.nt)
-                        A.pool[off + i] = t.scr[i];
+                        A.pool[off + i] = few ? sh.resv[i] : t.scr[i];
                     for (int32_t i = id.tid; i < nr; i += id.nt)
                         A.pool[off + na + i] = t.scr[t.cap - nr + i];
                 }
@@ -2784,6 +3084,21 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
                 dadd = na;
                 drem = nr;
                 st.written += (uint64_t)(na + nr);
+                __syncthreads();
+            } else if (moved > 0 && listed && last_cnt > 0 && st.nrem == 0 && st.nadd <= kMovedMax && !A.rec.drem) {
+                // the last list and the ids added since
+                const int32_t na = st.nadd, m = last_cnt + na;
+                moved_ids(t, sh, id, na, false);
+                if (id.tid == 0)
+                    sh.off = atomicAdd(A.pool_cursor, (unsigned long long)m);
+                __syncthreads();
+                const unsigned long long off = sh.off;
+                listed = (int64_t)off + m <= A.pool_cap;
+                if (listed)
+                    merge_moved(sh, id, A.pool + last_off, last_cnt, na, A.pool + off);
+                last_off = (int64_t)off;
+                last_cnt = m;
+                st.written += (uint64_t)m;
                 __syncthreads();
             } else if (s == s0 || moved > 0) {
                 if (id.tid == 0)
@@ -2810,6 +3125,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
                     for (int32_t i = id.tid; i < m; i += id.nt)
                         A.pool[off + i] = t.scr[i];
                 }
+                listed = (int64_t)off + m <= A.pool_cap;
                 last_off = (int64_t)off;
                 last_cnt = m;
                 dadd = m;
@@ -2865,7 +3181,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
             if (st.err)
                 atomicOr(A.err, st.err);
             if (!st.ovf) {
-                unsigned long long *sx = A.stat + kStatWords * A.stat_slot;
+                unsigned long long *sx = A.stat + kStatWords * A.tier;
                 atomicAdd(&sx[0], (unsigned long long)st.rows);
                 atomicAdd(&sx[1], (unsigned long long)st.row_len);
                 atomicAdd(&sx[2], (unsigned long long)inserted);
@@ -2873,7 +3189,7 @@ __device__ void run_team(const SweepArgs &A, const T &t, TeamSh &sh, int32_t *lb
                 atomicAdd(&sx[4], 1ull);
                 atomicAdd(&sx[5], (unsigned long long)st.scanned);
             }
-            unsigned long long *sa = A.stat + kStatWords * A.stat_slot;
+            unsigned long long *sa = A.stat + kStatWords * A.tier;
             atomicAdd(&sa[6], (unsigned long long)st.c_mrows);
             atomicAdd(&sa[7], (unsigned long long)st.c_mrow_len);
             if (st.emitted) {
@@ -2904,12 +3220,13 @@ __device__ __forceinline__ void team_entry(const SweepArgs &A) {
         run_team<PERSET>(A, t, sh, nullptr);
     } else {
         __shared__ double logs[kBlockLogs];
-        __shared__ int32_t lsort[kLdsSort];
+        __shared__ typename BTab<L>::F fresh;   // between growth calls: sort buffer
         if ((int)blockIdx.x >= A.n_slots)
             return;
-        const BTab<L> t = carve_slab<L>(A.gtab, A.gtab_stride, A.n_slots, blockIdx.x, logs, A.cap, A.hbits);
+        const BTab<L> t = carve_slab<L>(A.gtab, A.gtab_stride, A.n_slots, blockIdx.x, logs, &fresh, A.cap,
+                                        A.hbits);
         load_logs(A, logs);
-        run_team<PERSET>(A, t, sh, lsort);
+        run_team<PERSET>(A, t, sh, (int32_t *)&fresh);
     }
 }
 

@@ -682,7 +682,7 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     // sets; a query stream wants most queries done by tier 0
     if (params_are_auto(prm)) {
         prm.lds_capacity = 1024;
-        prm.team_waves = 8;
+        prm.team_waves = 4;
     }
     S->prm = prm;
     lcd_status s = plan_tiers(g->dev, g->n, 1, prm, S->tp);
@@ -696,12 +696,10 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     // so a short batch can wait behind a long one.
     //  * >= 8 queues: one stage per tier (a batch lasts as long as its
     //    slowest query, so a query that fits a small table never waits for
-    //    one that needs a large table; the LDS workgroup tiers are one
-    //    stage) and six lanes: one for tier 0, three for the LDS workgroup
-    //    tiers (about half of a query stream ends there), one each for the
-    //    16,384-entry and the whole-graph tier; with 10 or more queues four
-    //    lanes and two (eight in all), so that a query leaving an earlier
-    //    stage finds a free lane sooner.
+    //    one that needs a large table) and six lanes: one for tier 0, one for
+    //    the whole-graph tier, the rest for the tier between them, where most
+    //    of the queries that outgrow tier 0 end; with 10 or more queues eight
+    //    lanes, so that a query leaving tier 0 finds a free one sooner.
     //  * fewer: tier 0, then all later tiers; four lanes, one for tier 0.
     int hw_queues = 4;
     if (const char *e = std::getenv("GPU_MAX_HW_QUEUES"))
@@ -709,26 +707,22 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     const bool per_tier = hw_queues >= 8 && S->tp.n >= 2;
     S->n_stages = 0;
     if (per_tier) {
-        // the LDS workgroup tiers share a stage
-        for (int k = 0; k < S->tp.n; ++k) {
-            if (k > 0 && S->tp.t[k].stat == S->tp.t[k - 1].stat)
-                S->stages[S->n_stages - 1].last = k + 1;
-            else
-                S->stages[S->n_stages++] = Stage{k, k + 1};
-        }
+        for (int k = 0; k < S->tp.n; ++k)
+            S->stages[S->n_stages++] = Stage{k, k + 1};
     } else {
         S->stages[S->n_stages++] = Stage{0, 1};
         if (S->tp.n >= 2)
             S->stages[S->n_stages++] = Stage{1, S->tp.n};
     }
-    static const int kPerTierLanes[6] = {0, 1, 1, 1, 2, 3};
-    static const int kPerTierWide[8] = {0, 1, 1, 1, 1, 2, 2, 3};
+    // (the four tiers of an explicit team_capacity: a lane for its LDS tables)
+    static const int kPerTierLanes[2][6] = {{0, 1, 1, 1, 1, 2}, {0, 1, 2, 2, 2, 3}};
+    static const int kPerTierWide[2][8] = {{0, 1, 1, 1, 1, 1, 1, 2}, {0, 1, 2, 2, 2, 2, 2, 3}};
     static const int kTwoStageLanes[4] = {0, 1, 1, 1};
     const bool wide = per_tier && hw_queues >= 10;
     const int n_lanes = per_tier ? (wide ? 8 : 6) : 4;
     int lane_stage[kMaxLanes] = {0};
     for (int i = 0; i < n_lanes; ++i)
-        lane_stage[i] = std::min(per_tier ? (wide ? kPerTierWide[i] : kPerTierLanes[i]) : kTwoStageLanes[i],
+        lane_stage[i] = std::min(per_tier ? (wide ? kPerTierWide[S->n_stages > 3][i] : kPerTierLanes[S->n_stages > 3][i]) : kTwoStageLanes[i],
                                  S->n_stages - 1);
     const int32_t max_q = std::max<int32_t>(1, std::min<int32_t>(1024, max_slots));
     const int64_t max_seed = std::max<int64_t>(65536, (int64_t)g->n);

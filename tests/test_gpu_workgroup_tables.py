@@ -1,7 +1,6 @@
 """Workgroup tables against the oracle where their layouts can go wrong: the
-smallest LDS table, sizes beside a power of two (the hash's load), the three
-LDS tiers of a launch of few sets, global tables of 16-bit and of 32-bit
-indices, resumed sets, removal passes, one wave to eight; heavy weights (d
+smallest LDS table, sizes beside a power of two (the hash's load), launches
+of few and of many sets, global tables of 16-bit indices, resumed sets, removal passes, one wave to eight; heavy weights (d
 and degree in the hundreds of thousands), ranks of both signs and far beyond
 the bucket range.  Members, K, V and counters bit for bit, f within 1e-12."""
 import numpy as np
@@ -36,7 +35,7 @@ def case():
 
 
 @pytest.mark.parametrize("kw", [
-    dict(lds_capacity=64),                                     # the three LDS tiers, then global
+    dict(lds_capacity=64),
     dict(lds_capacity=64, team_capacity=128, team_waves=1),    # 16-bit global tables, resumed sets
     dict(lds_capacity=64, team_capacity=192, team_waves=8, output_mode=1),
     dict(lds_capacity=64, team_capacity=1088, team_waves=3),
@@ -63,8 +62,8 @@ def test_workgroup_tables_match_oracle(L, case, kw):
     res.free()
 
 
-def test_many_sets_on_global_tables_match_few_on_lds_tables(L, case):
-    """The set count chooses the tiers; the records of a set do not depend on it."""
+def test_many_sets_match_few(L, case):
+    """The set count chooses the waves; the records of a set do not depend on it."""
     g, sc, sp, sn, ref = case
     n = sp.size - 1
     reps = 1 + 4 * 256 // n + 1
