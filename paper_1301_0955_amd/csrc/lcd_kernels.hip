@@ -283,11 +283,39 @@ __device__ __forceinline__ void tab_slot_clear(const Tab &t, int32_t i) {
     }
 }
 
-// Dense index of u for every active lane, inserting absent ids.  All active
+// A directed entry: neighbour, its degree, its row start, the edge's weight,
+// the log of the degree.
+struct Edge {
+    int4 e;
+    double lk;
+};
+
+__device__ __forceinline__ Edge edge_at(const Ctx &c, int32_t j) {
+    Edge x;
+    if (c.adj) {
+        x.e = c.adj[j];
+        x.lk = c.adjl[j];
+        return x;
+    }
+    const int32_t u = c.col[j];
+    const int2 in = c.info[u];
+    x.e = make_int4(u, in.y, in.x, c.w ? (int32_t)c.w[j] : 1);
+    x.lk = c.logtab[min(in.y, c.logtab_last)];
+    return x;
+}
+
+__device__ __forceinline__ Edge no_edge() {
+    Edge x;
+    x.e = make_int4(0, 0, 0, 0);
+    x.lk = 0.0;
+    return x;
+}
+
+// Dense index of u (of degree k) for every active lane, inserting absent ids.  All active
 // ids of one call are distinct.  Returns -1 for inactive lanes, and for all
 // lanes when the table would overflow (st.ovf is then set).
 template <bool GLOBAL>
-__device__ int32_t tab_ensure(const Tab &t, St &st, const Ctx &c, bool act, int32_t u, int lane) {
+__device__ int32_t tab_ensure(const Tab &t, St &st, bool act, int32_t u, int32_t k, int lane) {
     int32_t idx = act ? tab_find<GLOBAL>(t, u, st.err) : -1;
     bool need = act && idx < 0;
     uint64_t m = __ballot(need);
@@ -302,7 +330,7 @@ __device__ int32_t tab_ensure(const Tab &t, St &st, const Ctx &c, bool act, int3
     if (need) {
         idx = st.count + __popcll(m & lanes_below(lane));
         t.NODE(idx) = u;
-        t.KV(idx) = c.kdeg[u];
+        t.KV(idx) = k;
         t.DV(idx) = 0u;
         tab_slot_insert<GLOBAL>(t, u, idx, st.err);
     }
@@ -329,15 +357,15 @@ __device__ void row_update(const Tab &t, St &st, const Ctx &c, int32_t n, int la
     for (int32_t base = beg; base < end; base += 64) {
         const int32_t j = base + lane;
         const bool act = j < end;
-        const int32_t u = act ? c.col[j] : 0;
-        const int32_t wt = act ? (c.w ? (int32_t)c.w[j] : 1) : 0;
+        const Edge x = act ? edge_at(c, j) : no_edge();
+        const int32_t u = x.e.x, wt = x.e.w;
         int32_t idx;
         if constexpr (MODE == ROW_REMOVE) {
             idx = act ? tab_find<GLOBAL>(t, u, st.err) : -1;
             if (act && idx < 0)
                 st.err |= ERR_MISSING;
         } else {
-            idx = tab_ensure<GLOBAL>(t, st, c, act, u, lane);
+            idx = tab_ensure<GLOBAL>(t, st, act, u, x.e.y, lane);
             if (st.ovf)
                 return;
         }
@@ -359,8 +387,7 @@ __device__ void row_update(const Tab &t, St &st, const Ctx &c, int32_t n, int la
                     const bool queued = (v & kLive) && !before(t.RK(idx), u, st.pr, st.pu);
                     if (!queued)
                         st.Gl += 1;
-                    const int32_t k = t.KV(idx);
-                    t.RK(idx) = rank_of(c, d, k, st.alpha);
+                    t.RK(idx) = c.logtab[min(2 * d, c.logtab_last)] - st.alpha * x.lk;
                     st.Rl += 1;
                     t.DV(idx) = (v & kWas) | (uint32_t)d | kLive | kFresh;
                 }
@@ -548,12 +575,46 @@ __device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
     return v;
 }
 
+// Whether any entry of the queue that a call starts with improves.  Most
+// calls add nothing (at least one per scale), and for those the ranks need
+// not be computed, only counted.
+template <bool GLOBAL>
+__device__ __forceinline__ bool wave_any_improves(const Tab &t, St &st, int lane) {
+    bool any = false;
+    const bool zero = st.K == 0;
+    st.scanned += (uint64_t)st.count;
+    for (int32_t base = 0; base < st.count; base += 128) {
+        uint32_t vv[2];
+        int32_t kk[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int32_t i = min(base + 64 * x + lane, st.count - 1);
+            vv[x] = t.DV(i);
+            kk[x] = t.KV(i);
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int32_t d = (int32_t)(vv[x] & kDMask);
+            const bool in = base + 64 * x + lane < st.count && !(vv[x] & kMember) && d != 0;
+            st.Rl += in ? 1 : 0;
+            st.Gl += in ? 1 : 0;
+            int s = zero ? 1 : settle_add(st, d, kk[x]);
+            if (in && !any && s < 0)
+                s = decide(st.K, st.V, st.K + 2 * (int64_t)d, st.V + kk[x], st.alpha) ? 1 : 0;
+            any = any || (in && s > 0);
+        }
+    }
+    return __ballot(any) != 0;
+}
+
 // One call of the growth function (Algorithm 1) at st.alpha.
 // Returns the number of moves; stops early on table overflow.
 template <bool GLOBAL>
 __device__ int64_t grow(const Tab &t, St &st, const Ctx &c, uint32_t k_prune, int lane) {
     int64_t moves = 0;
     bool creation = true;
+    if (!wave_any_improves<GLOBAL>(t, st, lane))
+        return 0;
     for (;;) {
         double br = -__builtin_huge_val();
         int32_t bu = INT32_MAX;
@@ -572,8 +633,6 @@ __device__ int64_t grow(const Tab &t, St &st, const Ctx &c, uint32_t k_prune, in
                 const int32_t d = (int32_t)(v & kDMask);
                 r = rank_of(c, d, t.KV(i), st.alpha);
                 t.RK(i) = r;
-                st.Rl += 1;
-                st.Gl += 1;
                 v = (v | kLive) & ~kFresh;
                 t.DV(i) = v;
             } else {
@@ -779,7 +838,7 @@ __device__ bool wave_toggle_records(const SweepArgs &A, const Tab &t, St &st, co
         for (int32_t base = 0; base < len; base += 64) {
             const bool act = base + lane < len;
             const int32_t u = act ? A.pool[off + base + lane] : 0;
-            const int32_t idx = tab_ensure<GLOBAL>(t, st, c, act, u, lane);
+            const int32_t idx = tab_ensure<GLOBAL>(t, st, act, u, act ? c.kdeg[u] : 0, lane);
             if (st.ovf)
                 return true;
             if (act && idx >= 0)
@@ -906,7 +965,7 @@ __device__ void run_wave(const SweepArgs &A, const Tab &t, int lane) {
         }
         for (int32_t q = 0; q < n_init && !bad && !st.ovf; ++q) {
             const int32_t u = init[q];
-            const int32_t idx = tab_ensure<GLOBAL>(t, st, c, lane == 0, u, lane);
+            const int32_t idx = tab_ensure<GLOBAL>(t, st, lane == 0, u, c.kdeg[u], lane);
             if (st.ovf)
                 break;
             const int32_t i0 = __shfl(idx, 0);
@@ -1566,34 +1625,6 @@ __device__ __forceinline__ double block_log(const BTab<L> &t, const Ctx &c, int3
     if (x < kBlockLogs)
         return lds_get(&t.lt[x]);
     return c.logtab[min(x, c.logtab_last)];
-}
-
-// A directed entry: neighbour, its degree, its row start, the edge's weight,
-// the log of the degree.
-struct Edge {
-    int4 e;
-    double lk;
-};
-
-__device__ __forceinline__ Edge edge_at(const Ctx &c, int32_t j) {
-    Edge x;
-    if (c.adj) {
-        x.e = c.adj[j];
-        x.lk = c.adjl[j];
-        return x;
-    }
-    const int32_t u = c.col[j];
-    const int2 in = c.info[u];
-    x.e = make_int4(u, in.y, in.x, c.w ? (int32_t)c.w[j] : 1);
-    x.lk = c.logtab[min(in.y, c.logtab_last)];
-    return x;
-}
-
-__device__ __forceinline__ Edge no_edge() {
-    Edge x;
-    x.e = make_int4(0, 0, 0, 0);
-    x.lk = 0.0;
-    return x;
 }
 
 // Create the entries of the lanes that need one (ids distinct in the
