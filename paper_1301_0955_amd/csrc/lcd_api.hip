@@ -554,100 +554,21 @@ lcd_status lcd_device_info(int32_t *compute_units, int64_t *lds_per_cu, int64_t 
 
 namespace {
 
-// Validate a host CSR and make it resident (the body of lcd_graph_upload).
-lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
-                       const std::vector<int32_t> &cl, const uint8_t *wp, hipStream_t st,
-                       lcd_graph **out) {
-    const bool has_w = wp != nullptr;
-    const uint8_t *w = wp;
-    std::vector<uint8_t> ww;
-    if (has_w)
-        ww.assign(wp, wp + nnz);
-    // --- validation ---
+// Make a CSR resident and validate it there (the body of lcd_graph_upload).
+// rp: host; cl, w: host or device by `kind`.
+lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *cl, const uint8_t *w,
+                       hipMemcpyKind kind, hipStream_t st, lcd_graph **out) {
     if (rp[0] != 0 || rp[n] != nnz)
         return fail(LCD_EINVAL, "row_ptr must start at 0 and end at nnz");
     for (int32_t u = 0; u < n; ++u)
         if (rp[u + 1] < rp[u])
             return fail(LCD_EINVAL, "row_ptr decreases at node %d", u);
-    // rows are checked in parallel blocks; the first failing row of the
-    // lowest block is reported
-    struct RowCheck {
-        int32_t row = -1;
-        int code = 0;
-        int32_t v = 0;
-        int64_t maxk = 0, vol = 0;
-    };
-    auto check_rows = [&](int32_t u0, int32_t u1, RowCheck &rc) {
-        for (int32_t u = u0; u < u1; ++u) {
-            const int32_t b = rp[u], e = rp[u + 1];
-            int64_t k = 0;
-            for (int32_t j = b; j < e; ++j) {
-                const int32_t v = cl[j];
-                int code = 0;
-                if (v < 0 || v >= n)
-                    code = 1;
-                else if (v == u)
-                    code = 2;
-                else if (j > b && cl[j - 1] >= v)
-                    code = 3;
-                else if ((w ? (int)ww[j] : 1) < 1)
-                    code = 4;
-                else {
-                    // symmetry: u must appear in row v with the same weight
-                    const int32_t *rb = cl.data() + rp[v];
-                    const int32_t *re = cl.data() + rp[v + 1];
-                    const int32_t *it = std::lower_bound(rb, re, u);
-                    if (it == re || *it != u)
-                        code = 5;
-                    else if (w && ww[it - cl.data()] != ww[j])
-                        code = 6;
-                }
-                if (code) {
-                    rc.row = u;
-                    rc.code = code;
-                    rc.v = v;
-                    return;
-                }
-                k += w ? (int)ww[j] : 1;
-            }
-            rc.maxk = std::max(rc.maxk, k);
-            rc.vol += k;
-        }
-    };
-    const int32_t nthr = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, (int64_t)n / 65536));
-    std::vector<RowCheck> rcs((size_t)nthr);
-    {
-        std::vector<std::thread> th;
-        for (int32_t t = 0; t < nthr; ++t) {
-            const int32_t u0 = (int32_t)((int64_t)n * t / nthr), u1 = (int32_t)((int64_t)n * (t + 1) / nthr);
-            th.emplace_back(check_rows, u0, u1, std::ref(rcs[(size_t)t]));
-        }
-        for (auto &x : th)
-            x.join();
-    }
-    int64_t maxk = 0, vol = 0;
-    for (const RowCheck &rc : rcs) {
-        if (rc.code) {
-            const int32_t u = rc.row, v = rc.v;
-            switch (rc.code) {
-            case 1: return fail(LCD_EINVAL, "neighbour id %d of node %d out of range", v, u);
-            case 2: return fail(LCD_EINVAL, "self-loop at node %d", u);
-            case 3: return fail(LCD_EINVAL, "row %d is not strictly ascending", u);
-            case 4: return fail(LCD_EINVAL, "zero weight on edge %d-%d", u, v);
-            case 5: return fail(LCD_EINVAL, "edge %d-%d has no reverse entry", u, v);
-            default: return fail(LCD_EINVAL, "edge %d-%d has unequal weights", u, v);
-            }
-        }
-        maxk = std::max(maxk, rc.maxk);
-        vol += rc.vol;
-    }
-    if (maxk >= ((int64_t)1 << 27))
-        return fail(LCD_EINVAL, "weighted degree %lld exceeds 2^27", (long long)maxk);
-    // --- device copies ---
     lcd_graph *g = new (std::nothrow) lcd_graph();
     if (!g)
         return fail(LCD_ENOMEM, "host allocation failed");
+    GraphCheck *d_chk = nullptr;
     auto bail = [&](lcd_status s) {
+        dev_free(d_chk);
         dev_free(g->row_ptr);
         dev_free(g->col);
         dev_free(g->w);
@@ -664,17 +585,51 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
         return bail(s);
     g->n = n;
     g->nnz = nnz;
-    g->maxk = maxk;
-    g->volume = vol;
     g->device = g->dev.device;
-    g->logtab_n = (int32_t)(2 * maxk + 2);
     if ((s = dev_alloc(&g->row_ptr, (size_t)n + 1)) != LCD_OK ||
         (s = dev_alloc(&g->col, (size_t)nnz)) != LCD_OK ||
         (s = dev_alloc(&g->kdeg, (size_t)std::max(n, 1))) != LCD_OK ||
-        (s = dev_alloc(&g->logtab, (size_t)g->logtab_n)) != LCD_OK ||
-        (s = dev_alloc(&g->info, (size_t)std::max(n, 1))) != LCD_OK)
+        (s = dev_alloc(&g->info, (size_t)std::max(n, 1))) != LCD_OK || (s = dev_alloc(&d_chk, 1)) != LCD_OK)
         return bail(s);
     if (w && (s = dev_alloc(&g->w, (size_t)nnz)) != LCD_OK)
+        return bail(s);
+    GraphCheck chk{~0ull, 0, 0};
+    hipError_t e = hipMemcpyAsync(g->row_ptr, rp, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(d_chk, &chk, sizeof(chk), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && nnz)
+        e = hipMemcpyAsync(g->col, cl, sizeof(int32_t) * (size_t)nnz, kind, st);
+    if (e == hipSuccess && w && nnz)
+        e = hipMemcpyAsync(g->w, w, (size_t)nnz, kind, st);
+    if (e == hipSuccess)
+        e = launch_check_graph(g->row_ptr, g->col, g->w, g->kdeg, n, nnz, d_chk, st);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&chk, d_chk, sizeof(chk), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(st);
+    int32_t v = 0;
+    const int64_t bad = (int64_t)(chk.bad >> 3);
+    if (e == hipSuccess && chk.bad != ~0ull)
+        e = hipMemcpy(&v, g->col + bad, sizeof(v), hipMemcpyDeviceToHost);
+    if (e != hipSuccess)
+        return bail(fail(LCD_EDEVICE, "graph upload: %s", hipGetErrorString(e)));
+    if (chk.bad != ~0ull) {
+        const int32_t u = (int32_t)(std::upper_bound(rp, rp + n + 1, (int32_t)bad) - rp) - 1;
+        switch ((int)(chk.bad & 7)) {
+        case 1: return bail(fail(LCD_EINVAL, "neighbour id %d of node %d out of range", v, u));
+        case 2: return bail(fail(LCD_EINVAL, "self-loop at node %d", u));
+        case 3: return bail(fail(LCD_EINVAL, "row %d is not strictly ascending", u));
+        case 4: return bail(fail(LCD_EINVAL, "zero weight on edge %d-%d", u, v));
+        case 5: return bail(fail(LCD_EINVAL, "edge %d-%d has no reverse entry", u, v));
+        default: return bail(fail(LCD_EINVAL, "edge %d-%d has unequal weights", u, v));
+        }
+    }
+    if (chk.maxk >= (1ull << 27))
+        return bail(fail(LCD_EINVAL, "weighted degree %lld exceeds 2^27", (long long)chk.maxk));
+    g->maxk = (int64_t)chk.maxk;
+    g->volume = (int64_t)chk.volume;
+    g->logtab_n = (int32_t)(2 * g->maxk + 2);
+    if ((s = dev_alloc(&g->logtab, (size_t)g->logtab_n)) != LCD_OK)
         return bail(s);
     // the adjacency records (24 bytes per directed entry) shorten a step on
     // LDS tables; a graph that would give them more than an eighth of the
@@ -685,16 +640,6 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
         dev_free(g->adj);
         dev_free(g->adjl);
     }
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(g->row_ptr, rp.data(), sizeof(int32_t) * ((size_t)n + 1),
-                           hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && nnz)
-        e = hipMemcpyAsync(g->col, cl.data(), sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && w && nnz)
-        e = hipMemcpyAsync(g->w, ww.data(), (size_t)nnz, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess)
-        e = launch_degrees(g->row_ptr, g->w, g->kdeg, n, st);
     if (e == hipSuccess)
         e = launch_node_info(g->row_ptr, g->kdeg, g->info, n, st);
     if (e == hipSuccess)
@@ -705,6 +650,7 @@ lcd_status build_graph(int32_t n, int64_t nnz, const std::vector<int32_t> &rp,
         e = hipStreamSynchronize(st);
     if (e != hipSuccess)
         return bail(fail(LCD_EDEVICE, "graph upload: %s", hipGetErrorString(e)));
+    dev_free(d_chk);
     *out = g;
     return LCD_OK;
 }
@@ -723,13 +669,13 @@ lcd_status lcd_graph_upload(int32_t n, int64_t nnz, const int32_t *row_ptr, cons
     if (mem_kind != LCD_MEM_HOST && mem_kind != LCD_MEM_DEVICE)
         return fail(LCD_EINVAL, "unknown mem_kind %d", mem_kind);
     hipStream_t st = (hipStream_t)stream;
-    std::vector<int32_t> rp, cl;
-    std::vector<uint8_t> ww;
+    if (!row_ptr || (nnz && !col))
+        return fail(LCD_EINVAL, "null input array");
+    if (mem_kind == LCD_MEM_HOST)
+        return build_graph(n, nnz, row_ptr, col, w, hipMemcpyHostToDevice, st, out);
+    std::vector<int32_t> rp;
     CHK(fetch(rp, row_ptr, (size_t)n + 1, mem_kind, st));
-    CHK(fetch(cl, col, (size_t)nnz, mem_kind, st));
-    if (w)
-        CHK(fetch(ww, w, (size_t)nnz, mem_kind, st));
-    return build_graph(n, nnz, rp, cl, w ? ww.data() : nullptr, st, out);
+    return build_graph(n, nnz, rp.data(), col, w, hipMemcpyDeviceToDevice, st, out);
 }
 
 lcd_status lcd_graph_upload_batch(int32_t n_graphs, const int64_t *node_off, const int64_t *edge_off,
@@ -782,7 +728,7 @@ lcd_status lcd_graph_upload_batch(int32_t n_graphs, const int64_t *node_off, con
     }
     rp[N] = (int32_t)E;
     lcd_graph *g = nullptr;
-    CHK(build_graph((int32_t)N, E, rp, cl, w ? lw.data() : nullptr, st, &g));
+    CHK(build_graph((int32_t)N, E, rp.data(), cl.data(), w ? lw.data() : nullptr, hipMemcpyHostToDevice, st, &g));
     g->node_off = no;
     g->edge_off = eo;
     *out = g;

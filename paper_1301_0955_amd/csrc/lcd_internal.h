@@ -145,8 +145,14 @@ __host__ __device__ constexpr int64_t team_table_bytes(int32_t cap) {
             (int64_t)cap * (cap >= kRecordMinEntries ? 4 : 2) + 255) & ~(int64_t)255;
 }
 
-hipError_t launch_degrees(const int32_t *row_ptr, const uint8_t *w, int32_t *kdeg, int32_t n,
-                          hipStream_t st);
+// What the device finds in an uploaded graph; bad: see check_graph_kernel, all
+// ones if the graph is sound.
+struct GraphCheck {
+    uint64_t bad, maxk, volume;
+};
+// Degrees and check (*chk = {all ones, 0, 0} before).
+hipError_t launch_check_graph(const int32_t *row_ptr, const int32_t *col, const uint8_t *w, int32_t *kdeg, int32_t n,
+                              int64_t nnz, GraphCheck *chk, hipStream_t st);
 hipError_t launch_node_info(const int32_t *row_ptr, const int32_t *kdeg, int2 *info, int32_t n, hipStream_t st);
 hipError_t launch_adj(const int32_t *row_ptr, const int32_t *col, const uint8_t *w, const int32_t *kdeg,
                       const double *logtab, int64_t nnz, int4 *adj, double *adjl, hipStream_t st);
