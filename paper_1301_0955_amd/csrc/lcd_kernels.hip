@@ -4162,23 +4162,26 @@ __global__ void __launch_bounds__(1024) nmi_mean_kernel(const double *term, int3
 // Checks a cover given as CSR: offsets from 0 to total, non-decreasing;
 // every community strictly ascending with ids in [0, n).  Any breach sets
 // *bad.
-__global__ void cover_check_kernel(const int32_t *ptr, const int32_t *mem, int32_t k, int64_t total, int32_t n,
-                                   uint32_t *bad) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < k; j += stride) {
+// One wave per community: a thread per community read its list entry by
+// entry, 150 us for 50,000 nodes.
+__global__ void __launch_bounds__(256) cover_check_kernel(const int32_t *ptr, const int32_t *mem, int32_t k,
+                                                          int64_t total, int32_t n, uint32_t *bad) {
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    bool breach = false;
+    for (int64_t j = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); j < k; j += waves) {
         const int32_t a = ptr[j], b = ptr[j + 1];
         if (b < a || a < 0 || (int64_t)b > total || (j == 0 && a != 0) || (j == k - 1 && (int64_t)b != total)) {
-            atomicOr(bad, 1u);
+            breach = true;
             continue;
         }
-        for (int32_t q = a; q < b; ++q) {
+        for (int32_t q = a + lane; q < b; q += 64) {
             const int32_t v = mem[q];
-            if (v < 0 || v >= n || (q > a && v <= mem[q - 1])) {
-                atomicOr(bad, 1u);
-                break;
-            }
+            breach = breach || v < 0 || v >= n || (q > a && v <= mem[q - 1]);
         }
     }
+    if (breach)
+        atomicOr(bad, 1u);
 }
 
 // Means of the p - 1 consecutive pair values of each window of p scales.
@@ -4519,7 +4522,7 @@ hipError_t launch_cover_check(const int32_t *ptr, const int32_t *mem, int32_t k,
     hipError_t e = launch_zero_bytes(bad, 4, st);
     if (e != hipSuccess || k == 0)
         return e;
-    hipLaunchKernelGGL(cover_check_kernel, dim3(grid_for(k, 256) < 4096 ? grid_for(k, 256) : 4096), dim3(256), 0, st,
+    hipLaunchKernelGGL(cover_check_kernel, dim3(grid_for(k, 4) < 4096 ? grid_for(k, 4) : 4096), dim3(256), 0, st,
                        ptr, mem, k, total, n, bad);
     return hipGetLastError();
 }
