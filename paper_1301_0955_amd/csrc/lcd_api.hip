@@ -928,23 +928,6 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     const int32_t n = g->n;
     if (n > 0 && !perm)
         return fail(LCD_EINVAL, "null input array");
-    // the permutation is checked on the host: in place when it is host
-    // memory, from a copy when it is device memory
-    std::vector<int32_t> ph;
-    const int32_t *hp = perm;
-    if (mem_kind == LCD_MEM_DEVICE) {
-        CHK(fetch(ph, perm, (size_t)n, mem_kind, st));
-        hp = ph.data();
-    }
-    {
-        std::vector<uint64_t> seen(((size_t)std::max(n, 1) + 63) / 64, 0);
-        for (int32_t i = 0; i < n; ++i) {
-            const int32_t v = hp[i];
-            if (v < 0 || v >= n || (seen[v >> 6] >> (v & 63) & 1u))
-                return fail(LCD_EINVAL, "perm is not a permutation of the node ids (entry %d)", i);
-            seen[v >> 6] |= (uint64_t)1 << (v & 63);
-        }
-    }
     *n_seeds = 0;
     if (n == 0)
         return LCD_OK;
@@ -955,7 +938,7 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     // round counters
     auto al = [](int64_t x) { return (x + 255) / 256 * 256; };
     const int64_t n4 = al(4 * (int64_t)n), n1 = al((int64_t)n);
-    const int64_t ws = 5 * n4 + al(4 * ((int64_t)nb + 1)) + 4 * n1 + al(4 * (int64_t)kSeedBatch);
+    const int64_t ws = 5 * n4 + al(4 * ((int64_t)nb + 1)) + 4 * n1 + al(4 * ((int64_t)kSeedBatch + 1));
     lcd_graph *gw = const_cast<lcd_graph *>(g);
     if (gw->seed_ws_bytes < ws) {
         dev_free(gw->seed_ws);
@@ -975,10 +958,12 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     uint8_t *act = sel + n1;
     uint8_t *near = act + n1;
     unsigned *cnt = (unsigned *)(near + n1);
+    unsigned *bad = cnt + kSeedBatch;
+    int32_t *key = at;   // free until the seeds are collected
     hipError_t e = hipMemcpyAsync(d_perm, perm, sizeof(int32_t) * (size_t)n,
                                   mem_kind == LCD_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
-        e = launch_seed_init(g->row_ptr, d_perm, n, pos, stt, act, st);
+        e = launch_seed_init(g->row_ptr, d_perm, n, pos, stt, act, key, bad, st);
     // each round settles at least the first undecided candidate in visiting
     // order, so at most n rounds run; usually a few dozen.  Rounds are queued
     // in batches (4, 8, ... up to kSeedBatch): round k of a batch counts the
@@ -988,16 +973,21 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     bool settled = false;
     for (int32_t batch = 4; e == hipSuccess && !settled && rounds <= (int64_t)n;
          batch = std::min(2 * batch, kSeedBatch)) {
-        unsigned undecided = 0;
+        unsigned undecided = 0, h_bad = ~0u;
         e = launch_zero_bytes(cnt, 4 * (int64_t)batch, st);
         for (int32_t k = 0; k < batch && e == hipSuccess; ++k)
-            e = launch_seed_round(rule, g->row_ptr, g->col, pos, stt, sel, act, near, flag, n,
+            e = launch_seed_round(rule, g->row_ptr, g->col, pos, stt, sel, act, near, flag, key, n,
                                   k > 0 ? cnt + (k - 1) : nullptr, cnt + k, st);
         rounds += batch;
         if (e == hipSuccess)
             e = hipMemcpyAsync(&undecided, cnt + (batch - 1), sizeof(unsigned), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess && rounds == batch)
+            e = hipMemcpyAsync(&h_bad, bad, sizeof(unsigned), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess)
             e = hipStreamSynchronize(st);
+        // (the rounds index nothing by an entry of perm)
+        if (e == hipSuccess && h_bad != ~0u)
+            return fail(LCD_EINVAL, "perm is not a permutation of the node ids (entry %u)", h_bad);
         settled = e == hipSuccess && undecided == 0;
     }
     int32_t total = 0;

@@ -3652,12 +3652,30 @@ __global__ void overlap_count_kernel(const int32_t *members, int64_t total, int3
 // st: 0 undecided candidate, 1 seed, 2 not a seed.
 // ---------------------------------------------------------------------------
 
-__global__ void seed_init_kernel(const int32_t *row_ptr, const int32_t *perm, int32_t n, int32_t *pos,
-                                 uint8_t *st, uint8_t *act) {
+// Positions of the nodes in perm (pos: INT32_MAX before), the first entry out
+// of range or that a later pass finds repeated in *bad.
+__global__ void seed_perm_kernel(const int32_t *perm, int32_t n, int32_t *pos, unsigned *bad) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        pos[perm[i]] = (int32_t)i;
-        st[i] = (row_ptr[i + 1] - row_ptr[i]) >= 2 ? 0 : 2;
+        const int32_t v = perm[i];
+        if (v < 0 || v >= n)
+            atomicMin(bad, (unsigned)i);
+        else
+            atomicMin(&pos[v], (int32_t)i);
+    }
+}
+
+// key[v]: the position of an undecided candidate, INT32_MAX of any other node.
+__global__ void seed_init_kernel(const int32_t *row_ptr, const int32_t *perm, int32_t n, const int32_t *pos,
+                                 uint8_t *st, uint8_t *act, int32_t *key, unsigned *bad) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t v = perm[i];
+        if (v >= 0 && v < n && pos[v] != (int32_t)i)
+            atomicMin(bad, (unsigned)i);   // repeated: an earlier entry holds it
+        const bool cand = row_ptr[i + 1] - row_ptr[i] >= 2;
+        st[i] = cand ? 0 : 2;
+        key[i] = cand ? pos[i] : INT32_MAX;
         act[i] = 1;
     }
 }
@@ -3673,9 +3691,8 @@ __global__ void seed_init_kernel(const int32_t *row_ptr, const int32_t *perm, in
 // every two-hop path.  Candidates never become undecided again, so a node
 // whose closed neighbourhood holds none keeps m1 = INT32_MAX for good and
 // is skipped from then on (act[v] = 0).
-__global__ void seed_min1_kernel(const int32_t *row_ptr, const int32_t *col, const int32_t *pos,
-                                 const uint8_t *st, uint8_t *act, int32_t n, int32_t *m1, const unsigned *prev,
-                                 unsigned *undecided) {
+__global__ void seed_min1_kernel(const int32_t *row_ptr, const int32_t *col, const int32_t *key, uint8_t *act,
+                                 int32_t n, int32_t *m1, const unsigned *prev, unsigned *undecided) {
     if (prev && *prev == 0u)
         return;
     unsigned cnt = 0;
@@ -3683,15 +3700,22 @@ __global__ void seed_min1_kernel(const int32_t *row_ptr, const int32_t *col, con
          v += (int64_t)gridDim.x * blockDim.x) {
         if (!act[v])
             continue;
-        int32_t m = INT32_MAX;
-        if (st[v] == 0) {
+        int32_t m = key[v];
+        if (m != INT32_MAX)
             cnt += 1;
-            m = pos[v];
-        }
-        for (int32_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j) {
-            const int32_t u = col[j];
-            if (st[u] == 0)
-                m = min(m, pos[u]);
+        // four neighbours at a time: their reads are in flight together
+        const int32_t end = row_ptr[v + 1];
+        for (int32_t j = row_ptr[v]; j < end; j += 4) {
+            int32_t u[4], x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                u[q] = col[min(j + q, end - 1)];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                x[q] = key[u[q]];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                m = min(m, x[q]);
         }
         m1[v] = m;
         if (m == INT32_MAX)
@@ -3726,7 +3750,8 @@ __global__ void seed_min2_kernel(const int32_t *row_ptr, const int32_t *col, con
 // own thread only, and every other write is the same value from whichever
 // thread makes it.
 __global__ void seed_apply1_kernel(const int32_t *row_ptr, const int32_t *col, const int32_t *pos,
-                                   const int32_t *m1, uint8_t *st, int32_t n, const unsigned *undecided) {
+                                   const int32_t *m1, uint8_t *st, int32_t *key, int32_t n,
+                                   const unsigned *undecided) {
     if (*undecided == 0u)
         return;   // the round found nothing to decide
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
@@ -3734,10 +3759,13 @@ __global__ void seed_apply1_kernel(const int32_t *row_ptr, const int32_t *col, c
         if (st[v] != 0 || m1[v] != pos[v])
             continue;
         st[v] = 1;
+        key[v] = INT32_MAX;
         for (int32_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j) {
             const int32_t u = col[j];
-            if (st[u] == 0)
+            if (st[u] == 0) {
                 st[u] = 2;
+                key[u] = INT32_MAX;
+            }
         }
     }
 }
@@ -3766,7 +3794,8 @@ __global__ void seed_near_kernel(const int32_t *row_ptr, const int32_t *col, con
 }
 
 __global__ void seed_apply2_kernel(const int32_t *row_ptr, const int32_t *col, const uint8_t *sel,
-                                   const uint8_t *near, uint8_t *st, int32_t n, const unsigned *undecided) {
+                                   const uint8_t *near, uint8_t *st, int32_t *key, int32_t n,
+                                   const unsigned *undecided) {
     if (*undecided == 0u)
         return;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n;
@@ -3775,13 +3804,16 @@ __global__ void seed_apply2_kernel(const int32_t *row_ptr, const int32_t *col, c
             continue;
         if (sel[v]) {
             st[v] = 1;
+            key[v] = INT32_MAX;
             continue;
         }
         uint8_t x = near[v];
         for (int32_t j = row_ptr[v]; j < row_ptr[v + 1] && !x; ++j)
             x = near[col[j]];
-        if (x)
+        if (x) {
             st[v] = 2;
+            key[v] = INT32_MAX;
+        }
     }
 }
 
@@ -4482,29 +4514,36 @@ hipError_t launch_exclusive_scan(const int32_t *in, int64_t n, int32_t *out, int
     return hipGetLastError();
 }
 
-hipError_t launch_seed_init(const int32_t *row_ptr, const int32_t *perm, int32_t n, int32_t *pos,
-                            uint8_t *st, uint8_t *act, hipStream_t s) {
+hipError_t launch_seed_init(const int32_t *row_ptr, const int32_t *perm, int32_t n, int32_t *pos, uint8_t *st,
+                            uint8_t *act, int32_t *key, unsigned *bad, hipStream_t s) {
     if (n == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(seed_init_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, row_ptr, perm, n, pos, st, act);
+    hipError_t e = launch_fill_i32(pos, INT32_MAX, n, s);
+    if (e == hipSuccess)
+        e = launch_fill_i32((int32_t *)bad, -1, 1, s);
+    if (e != hipSuccess)
+        return e;
+    const dim3 g(grid_for(n, 256)), b(256);
+    hipLaunchKernelGGL(seed_perm_kernel, g, b, 0, s, perm, n, pos, bad);
+    hipLaunchKernelGGL(seed_init_kernel, g, b, 0, s, row_ptr, perm, n, pos, st, act, key, bad);
     return hipGetLastError();
 }
 
 hipError_t launch_seed_round(int32_t rule, const int32_t *row_ptr, const int32_t *col, const int32_t *pos,
-                             uint8_t *st, uint8_t *sel, uint8_t *act, uint8_t *near, int32_t *m1, int32_t n,
+                             uint8_t *st, uint8_t *sel, uint8_t *act, uint8_t *near, int32_t *m1, int32_t *key, int32_t n,
                              const unsigned *prev, unsigned *undecided, hipStream_t s) {
     if (n == 0)
         return hipSuccess;
     if (rule != 1 && rule != 2)
         return hipErrorInvalidValue;
     const dim3 g(grid_for(n, 256)), b(256);
-    hipLaunchKernelGGL(seed_min1_kernel, g, b, 0, s, row_ptr, col, pos, st, act, n, m1, prev, undecided);
+    hipLaunchKernelGGL(seed_min1_kernel, g, b, 0, s, row_ptr, col, key, act, n, m1, prev, undecided);
     if (rule == 1) {
-        hipLaunchKernelGGL(seed_apply1_kernel, g, b, 0, s, row_ptr, col, pos, m1, st, n, undecided);
+        hipLaunchKernelGGL(seed_apply1_kernel, g, b, 0, s, row_ptr, col, pos, m1, st, key, n, undecided);
     } else {
         hipLaunchKernelGGL(seed_min2_kernel, g, b, 0, s, row_ptr, col, pos, st, m1, sel, n, undecided);
         hipLaunchKernelGGL(seed_near_kernel, g, b, 0, s, row_ptr, col, sel, act, n, near, undecided);
-        hipLaunchKernelGGL(seed_apply2_kernel, g, b, 0, s, row_ptr, col, sel, near, st, n, undecided);
+        hipLaunchKernelGGL(seed_apply2_kernel, g, b, 0, s, row_ptr, col, sel, near, st, key, n, undecided);
     }
     return hipGetLastError();
 }
