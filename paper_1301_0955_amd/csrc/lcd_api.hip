@@ -859,12 +859,13 @@ lcd_status lcd_sweep(const lcd_graph *g, const double *scales, int32_t n_scales,
     // a graph's first sweep has no size of an earlier one to go by, and a pool
     // that is too small costs a second sweep, often a third; an allocation of
     // gigabytes costs 0.6 ms
-    const int64_t per = g->pool_hint > 0 ? 32 : std::max(32, std::min(512, g->n));
-    int64_t est = std::max<int64_t>(1 << 16, (int64_t)n_sets * (n_scales / 4 + 2) * per);
-    if (per > 32) {
+    const int64_t least = std::max<int64_t>(1 << 16, (int64_t)n_sets * (n_scales / 4 + 2) * 32);
+    int64_t est = least;
+    if (g->pool_hint == 0) {
         size_t free_b = 0, total_b = 0;
         HIPCHK(hipMemGetInfo(&free_b, &total_b));
-        est = std::min<int64_t>(est, std::max<int64_t>((int64_t)(free_b / 64), (int64_t)n_sets * (n_scales / 4 + 2) * 32));
+        est = std::max(least, std::min<int64_t>((int64_t)n_sets * (n_scales / 2 + 2) * std::min(512, g->n),
+                                                (int64_t)(free_b / 64)));
     }
     est = std::max(est, g->pool_hint + g->pool_hint / 16);
     if (prm.pool_hint > 0)
