@@ -1570,10 +1570,12 @@ __device__ __forceinline__ uint32_t group_tagged(const uint4 &g, uint32_t h, int
 }
 
 // The entry of u and its fields, or idx = -1 and the first empty slot of its
-// probe (kNoSlot: none left).  Slots of an id's probe fill in order and are
+// probe (kNoSlot: none left).  Entries from `count` on are being created by
+// other waves: they are other ids', and their fields are not read.  Slots of an id's probe fill in order and are
 // never emptied, so a lookup ends at the first empty one.
 template <int L>
-__device__ __forceinline__ void block_find(const BTab<L> &t, int32_t u, int32_t &idx, uint32_t &slot, Ent &e) {
+__device__ __forceinline__ void block_find(const BTab<L> &t, int32_t u, int32_t count, int32_t &idx, uint32_t &slot,
+                                           Ent &e) {
     const uint32_t h = hash_mul(u);
     uint32_t p = group_of(t, h);
     idx = -1;
@@ -1582,13 +1584,14 @@ __device__ __forceinline__ void block_find(const BTab<L> &t, int32_t u, int32_t 
         const uint4 g = *(const uint4 *)(t.hw + p);
         const uint32_t room = group_empty(g);
         uint32_t m = group_tagged(g, h, t.shift()) & ~room;
-        slot_acquire<L>();
         while (m) {
             const int32_t i = (int32_t)(slot_of(g, __builtin_ctz(m)) & index_mask(t));
-            e = ent_get(t, i);
-            if (e.u == u) {
-                idx = i;
-                return;
+            if (i < count) {
+                e = ent_get(t, i);
+                if (e.u == u) {
+                    idx = i;
+                    return;
+                }
             }
             m &= m - 1;
         }
@@ -1628,14 +1631,15 @@ __device__ __forceinline__ double block_log(const BTab<L> &t, const Ctx &c, int3
 }
 
 // Create the entries of the lanes that need one (ids distinct in the
-// workgroup, slot from block_find): index, fields with d = 0, then the hash
-// slot, so that another wave's lookup sees no slot or a whole entry.  solo:
-// only this wave adds entries before the next barrier.  A full table sets
-// sh.row.ovf (idx stays -1).
+// workgroup, slot from block_find): index, fields with d = 0, and the swap of
+// their hash slot, whose result is left in `old` for block_added.  solo: only
+// this wave adds entries before the next barrier.  A full table sets sh.ovf
+// (idx stays -1).
 template <int L>
 __device__ __forceinline__ void block_add(const BTab<L> &t, TeamSh &sh, St &st, const TeamId &id, bool need,
                                           int32_t u, int32_t k, int32_t beg, uint32_t slot, bool solo,
-                                          int32_t &idx) {
+                                          int32_t &idx, uint32_t &old) {
+    old = kNoSlot;
     const uint64_t m = __ballot(need);
     if (m == 0)
         return;
@@ -1655,16 +1659,25 @@ __device__ __forceinline__ void block_add(const BTab<L> &t, TeamSh &sh, St &st, 
             sh.row.ovf = 1u;
         } else {
             idx = at;
+            if (slot != kNoSlot)
+                old = atomicCAS(&t.hw[slot], kNoSlot, (hash_mul(u) << t.shift()) | (uint32_t)at);
             ent_new(t, at, u, k, beg);
             st.inserted += 1;
         }
     }
-    if (solo)
-        lds_order();
-    else
-        slot_release<L>();
+}
+
+// The end of block_add, once the swap's result is there (what a row does with
+// the entries in between hides its trip to the L2): a lost slot is sought on.
+template <int L>
+__device__ __forceinline__ void block_added(const BTab<L> &t, St &st, bool need, int32_t u, uint32_t slot, int32_t idx,
+                                            uint32_t old) {
     if (need && idx >= 0) {
-        slot = block_claim(t, slot, (hash_mul(u) << t.shift()) | (uint32_t)idx);
+        const uint32_t v = (hash_mul(u) << t.shift()) | (uint32_t)idx;
+        if (slot == kNoSlot || old != kNoSlot)
+            slot = block_claim(t, slot, v);
+        else if constexpr (L != T_LDS)
+            slot_put(t, slot, v);
         if (slot == kNoSlot)
             st.err |= ERR_PROBE;
         if constexpr (L != T_LDS)
@@ -1681,11 +1694,15 @@ __device__ int32_t team_ensure(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &
     int32_t idx = -1;
     uint32_t slot = kNoSlot;
     Ent e;
+    const int32_t count = min(sh.row.count, t.cap);
+    __syncthreads();   // read by all before one is added
     if (act)
-        block_find(t, u, idx, slot, e);
+        block_find(t, u, count, idx, slot, e);
     const bool need = act && idx < 0;
     const int2 in = need ? c.info[u] : make_int2(0, 0);
-    block_add(t, sh, st, id, need, u, in.y, in.x, slot, false, idx);
+    uint32_t old;
+    block_add(t, sh, st, id, need, u, in.y, in.x, slot, false, idx, old);
+    block_added(t, st, need, u, slot, idx, old);
     __syncthreads();
     return idx;
 }
@@ -1718,7 +1735,7 @@ __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, 
         a.v = 0u;
         a.r = 0.0;
         if (act)
-            block_find(t, e.x, idx, slot, a);
+            block_find(t, e.x, st.count, idx, slot, a);
         if constexpr (MODE == ROW_REMOVE) {
             if (act) {
                 if (idx < 0)
@@ -1728,7 +1745,8 @@ __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, 
             }
         } else {
             const bool fresh = act && idx < 0;
-            block_add(t, sh, st, id, fresh, e.x, e.y, e.z, slot, solo, idx);
+            uint32_t old;
+            block_add(t, sh, st, id, fresh, e.x, e.y, e.z, slot, solo, idx, old);
             // a non-member neighbour is (re)queued with its new rank: on the
             // fresh list already, or to be listed (in the queue unless
             // popped: queue entries at once, fresh ones by the next scan)
@@ -1797,6 +1815,7 @@ __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, 
                     }
                 }
             }
+            block_added(t, st, fresh, e.x, slot, idx, old);
         }
     }
     if (id.tid == 0 && (st.M & 15) == 0 && wall_clock64() - st.t0 > st.budget)
@@ -2143,6 +2162,7 @@ __device__ __forceinline__ bool block_pick_min(TeamSh &sh, const TeamId &id, int
 // popped ones; lane l holds the starts of buckets 4l .. 4l + 3.
 struct LQ {
     int32_t ns, cp;
+    int32_t pre;      // tables in global memory: this thread's entry of the window at cp
     int32_t s4[4];
 };
 
@@ -2207,6 +2227,14 @@ __device__ __forceinline__ void fresh_flush(const BTab<L> &t, TeamSh &sh, St &st
         }
         __syncthreads();
     }
+}
+
+// The queue does not change between builds: a thread's entry of the next
+// window is read as soon as cp is known, so that its trip lies behind the row.
+template <int L>
+__device__ __forceinline__ void lq_ahead(const BTab<L> &t, const TeamId &id, LQ &q) {
+    if constexpr (L != T_LDS)
+        q.pre = q.cp + id.tid < q.ns ? (int32_t)t.sq[q.cp + id.tid] : 0;
 }
 
 // Sort the queue into its buckets: at a call's start (CREATE: every
@@ -2344,6 +2372,7 @@ __device__ __forceinline__ void lq_build(const BTab<L> &t, TeamSh &sh, St &st, c
         st.qalpha = st.alpha;
     }
     __syncthreads();
+    lq_ahead(t, id, q);
 }
 
 // Whether any entry of the queue that a call starts with improves.  Most
@@ -2497,12 +2526,12 @@ __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, co
             // fresh list is looked at
             one = at == q.cp && end - at <= A * id.nt;
             bool in[A];
-            const auto load = [&](int32_t x0) {
+            const auto load = [&](int32_t x0, bool ahead) {
 #pragma unroll
                 for (int y = 0; y < A; ++y) {
                     const int32_t x = x0 + y * id.nt;
                     in[y] = x < end;
-                    ii[y] = (int32_t)t.sq[in[y] ? x : 0];
+                    ii[y] = ahead && y == 0 ? q.pre : (int32_t)t.sq[in[y] ? x : 0];
                 }
 #pragma unroll
                 for (int y = 0; y < A; ++y) {
@@ -2511,7 +2540,7 @@ __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, co
                 }
             };
             int32_t x0 = at + id.tid;
-            load(x0);
+            load(x0, at == q.cp);
             for (int32_t f0 = id.tid; f0 < nf; f0 += A * id.nt) {
                 Ent g[A];
                 int32_t gi[A];
@@ -2547,7 +2576,7 @@ __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, co
                 x0 += A * id.nt;
                 if (x0 - id.tid >= end)
                     break;
-                load(x0);
+                load(x0, false);
             }
         }
         const bool found = block_pick_max(sh, id, par, b, bi, o);
@@ -2582,6 +2611,7 @@ __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, co
         }
         // the buckets before the addition's hold only popped entries
         q.cp = max(q.cp, lq_start(q, bo));
+        lq_ahead(t, id, q);
         __syncthreads();   // the pops are in place before the row's updates
         return true;
     }
