@@ -108,7 +108,7 @@ typedef struct {
     int32_t team_capacity;   /* spill_mode 0: entries of a workgroup tier's LDS table;
                                 0 = no such tier */
     int32_t team_waves;      /* waves per community in the workgroup tiers, 1..8;
-                                0 = 4 for few seed sets (three per compute unit) and
+                                0 = 4 for few seed sets (three per compute unit), 3
                                 on graphs of 4M+ nodes, else 2 (8 on the tables that
                                 hold every node) */
     int32_t grow_calls;      /* growth calls per (seed set, scale): 0 = until a call

@@ -118,14 +118,16 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
     };
     // waves per community on global tables.  A wide workgroup shortens a
     // community's chain of steps (22,990 additions alone on the 4M-node graph:
-    // 272 ms with one wave, 206 with two, 168 with four), a narrow one keeps
-    // more communities in flight (16,384 sets on the 1M-node graph: 105, 109
-    // and 149 ms; 20,000 on 100k nodes: 18, 20 and 29 ms).  Four where every set
-    // is resident at four, and on graphs of millions of nodes, whose longest
-    // chains are much of a sweep (547, 398 and 380 ms); else two.
+    // 264 ms with one wave, 191 with two, 156 with four), a narrow one keeps
+    // more communities in flight (16,384 sets on the 1M-node graph: 105, 107
+    // and 150 ms; 20,000 on 100k nodes: 18, 20 and 30 ms).  Four where every set
+    // is resident at four; three on graphs of millions of nodes, whose longest
+    // chains are much of a sweep (12,000 sets on the 4M-node graph: 363 ms with
+    // two, 354 with three, 372 with four; 14,184 on 10M nodes 2,028, 1,880 and
+    // 1,912); else two.
     int32_t team_waves = p.team_waves;
     if (team_waves == 0)
-        team_waves = n >= (4 << 20) || n_sets <= resident(TIER_TEAM_GLOBAL, 4, 0) ? 4 : 2;
+        team_waves = n_sets <= resident(TIER_TEAM_GLOBAL, 4, 0) ? 4 : n >= (4 << 20) ? 3 : 2;
     // tables for the narrowest of them, whatever the launch, so that launches of
     // few and of many sets share one slab
     const int32_t team_slots = std::max(resident(TIER_TEAM_GLOBAL, 2, 0), resident(TIER_TEAM_GLOBAL, team_waves, 0));
@@ -554,6 +556,34 @@ lcd_status lcd_device_info(int32_t *compute_units, int64_t *lds_per_cu, int64_t 
 
 namespace {
 
+lcd_status bad_edge(int rule, int32_t u, int32_t v) {
+    switch (rule) {
+    case 1: return fail(LCD_EINVAL, "neighbour id %d of node %d out of range", v, u);
+    case 2: return fail(LCD_EINVAL, "self-loop at node %d", u);
+    case 3: return fail(LCD_EINVAL, "row %d is not strictly ascending", u);
+    case 4: return fail(LCD_EINVAL, "zero weight on edge %d-%d", u, v);
+    case 5: return fail(LCD_EINVAL, "edge %d-%d has no reverse entry", u, v);
+    default: return fail(LCD_EINVAL, "edge %d-%d has unequal weights", u, v);
+    }
+}
+
+// The rules of check_graph_kernel on host arrays, for a graph that no device
+// can take: a malformed one is reported as such all the same.
+lcd_status check_graph_host(int32_t n, const int32_t *rp, const int32_t *cl, const uint8_t *w) {
+    for (int32_t u = 0; u < n; ++u)
+        for (int32_t j = rp[u]; j < rp[u + 1]; ++j) {
+            const int32_t v = cl[j];
+            int rule = v < 0 || v >= n ? 1 : v == u ? 2 : j > rp[u] && cl[j - 1] >= v ? 3 : w && w[j] < 1 ? 4 : 0;
+            if (!rule) {
+                const int32_t *re = cl + rp[v + 1], *it = std::lower_bound(cl + rp[v], re, u);
+                rule = it == re || *it != u ? 5 : w && w[it - cl] != w[j] ? 6 : 0;
+            }
+            if (rule)
+                return bad_edge(rule, u, v);
+        }
+    return LCD_OK;
+}
+
 // Make a CSR resident and validate it there (the body of lcd_graph_upload).
 // rp: host; cl, w: host or device by `kind`.
 lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *cl, const uint8_t *w,
@@ -580,9 +610,20 @@ lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t 
         delete g;
         return s;
     };
+    // no device, or no room on it
+    auto refuse = [&](lcd_status s) {
+        const std::string why = t_err;
+        if (kind == hipMemcpyHostToDevice) {
+            const lcd_status bad = check_graph_host(n, rp, cl, w);
+            if (bad != LCD_OK)
+                return bail(bad);
+        }
+        t_err = why;
+        return bail(s);
+    };
     lcd_status s;
     if ((s = device_info(g->dev)) != LCD_OK)
-        return bail(s);
+        return refuse(s);
     g->n = n;
     g->nnz = nnz;
     g->device = g->dev.device;
@@ -590,9 +631,9 @@ lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t 
         (s = dev_alloc(&g->col, (size_t)nnz)) != LCD_OK ||
         (s = dev_alloc(&g->kdeg, (size_t)std::max(n, 1))) != LCD_OK ||
         (s = dev_alloc(&g->info, (size_t)std::max(n, 1))) != LCD_OK || (s = dev_alloc(&d_chk, 1)) != LCD_OK)
-        return bail(s);
+        return refuse(s);
     if (w && (s = dev_alloc(&g->w, (size_t)nnz)) != LCD_OK)
-        return bail(s);
+        return refuse(s);
     GraphCheck chk{~0ull, 0, 0};
     hipError_t e = hipMemcpyAsync(g->row_ptr, rp, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
@@ -615,14 +656,7 @@ lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t 
         return bail(fail(LCD_EDEVICE, "graph upload: %s", hipGetErrorString(e)));
     if (chk.bad != ~0ull) {
         const int32_t u = (int32_t)(std::upper_bound(rp, rp + n + 1, (int32_t)bad) - rp) - 1;
-        switch ((int)(chk.bad & 7)) {
-        case 1: return bail(fail(LCD_EINVAL, "neighbour id %d of node %d out of range", v, u));
-        case 2: return bail(fail(LCD_EINVAL, "self-loop at node %d", u));
-        case 3: return bail(fail(LCD_EINVAL, "row %d is not strictly ascending", u));
-        case 4: return bail(fail(LCD_EINVAL, "zero weight on edge %d-%d", u, v));
-        case 5: return bail(fail(LCD_EINVAL, "edge %d-%d has no reverse entry", u, v));
-        default: return bail(fail(LCD_EINVAL, "edge %d-%d has unequal weights", u, v));
-        }
+        return bail(bad_edge((int)(chk.bad & 7), u, v));
     }
     if (chk.maxk >= (1ull << 27))
         return bail(fail(LCD_EINVAL, "weighted degree %lld exceeds 2^27", (long long)chk.maxk));

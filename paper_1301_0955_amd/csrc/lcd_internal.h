@@ -131,7 +131,7 @@ constexpr int kRecordBytes = 32;
 constexpr int32_t kRecordMinEntries = 65536;
 constexpr int kBlockEntryBytes = 8 /*rank*/ + 4 /*node*/ + 4 /*d|flags*/ + 4 /*k*/ + 4 /*row start*/ + 2 /*queue*/;
 constexpr int kFreshMax = 320;       // fresh-list entries kept
-constexpr int kFreshMaxWide = 1024;  // ... of tables of 32-bit indices
+constexpr int kFreshMaxWide = 704;   // ... of tables of 32-bit indices
 constexpr int kFreshRebuild = 256;   // ... from which the queue is rebuilt, at least
 constexpr int kTeamShBytes = 3584;   // LDS a workgroup uses beside its table, at most
 

@@ -1356,6 +1356,12 @@ __device__ __forceinline__ int32_t bucket_at(const TeamSh &sh, int32_t lo, int32
 //   * a copy of the first logs of the table L in LDS;
 //   * a row is read from adjacency records that carry the neighbour's degree,
 //     its log and its row start beside its id.
+// What bounds it: the chain (13,000 cycles an addition alone, of which the row
+// takes 6,000 and the step 5,000) and, with twelve waves a compute unit in
+// flight, instruction issue and the L2 misses of tables far larger than it.
+// Against array tables with slot-by-slot probing and serial initialisation,
+// sweeps of 20,000 sets on 100k nodes, 16,384 on 1M and 12,000 on 4M took 27,
+// 209 and 490 ms in this tier; now 15, 99 and 350.
 // Layouts:
 //   T_LDS: everything in LDS (16-bit queue indices).  32 bytes per entry, so
 //     one to a few communities share a compute unit: for launches of few
@@ -3291,12 +3297,12 @@ __device__ __forceinline__ void team_entry(const SweepArgs &A) {
     }
 }
 
-// Register bounds.  LDS tables leave room for at most three workgroups per
-// compute unit, so their kernel takes the 256 VGPRs of two waves per SIMD and
-// spills nothing.  On global tables three waves per SIMD (168 VGPRs, 79
-// spilled) were best at two waves per community: sweeps of the 100k-, 1M- and
-// 4M-node graphs 26, 151 and 450 ms; two (no spills) 30, 170 and 474, four 26,
-// 148 and 464.
+// Register bounds.  LDS tables leave room for a few workgroups per compute
+// unit, so their kernel takes the 256 VGPRs of two waves per SIMD and spills
+// nothing.  On global tables three waves per SIMD (168 VGPRs, 100 spilled)
+// are best: sweeps of the 100k-, 1M- and 4M-node graphs 19.6, 107 and 373 ms
+// at the same waves per community; two (no spills) 22.9, 124 and 428, four
+// 21.3, 113 and 407.
 #define LCD_TEAM_KERNEL(w) __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(w)))
 LCD_TEAM_KERNEL(2) sweep_team_lds_kernel(SweepArgs A) { team_entry<false, T_LDS>(A); }
 LCD_TEAM_KERNEL(3) sweep_team_global_kernel(SweepArgs A) { team_entry<false, T_PACK>(A); }
