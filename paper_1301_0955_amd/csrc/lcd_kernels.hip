@@ -3347,7 +3347,7 @@ __global__ void __launch_bounds__(256) degrees_kernel(const int32_t *row_ptr, co
 // << 3 | rule): id in range, no self-loop, rows strictly ascending, weights
 // at least 1, a reverse entry of the same weight.  Bound by the dependent
 // reads of two binary searches an entry, independent between entries: 0.1 ms
-// for 2M entries, where one host thread took 12.
+// for 3M entries, where one host thread took 17.
 __global__ void __launch_bounds__(256) check_graph_kernel(const int32_t *row_ptr, const int32_t *col, const uint8_t *w,
                                                           int32_t n, int64_t nnz, GraphCheck *chk) {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
@@ -3442,7 +3442,8 @@ __global__ void fill_i32_kernel(int32_t *p, int32_t v, int64_t n) {
 // before it sizes or gathers anything.  The counts lie S apart, a cache line
 // or more each: workgroup b sums all before its chunk by itself, with every
 // read independent, instead of waiting for the others (20,000 sets, 32
-// scales: one workgroup took 46 us a scale, 20 take 7).
+// scales: one workgroup took 46 us a scale, 20 take 19, the misses of the
+// counts' lines; scanning by wave shuffles instead of LDS steps changed nothing).
 __global__ void __launch_bounds__(1024) scale_scan_kernel(const int32_t *cnt, int32_t S, int32_t s,
                                                           int32_t n_sets, int32_t chunk, int32_t *comm_ptr,
                                                           long long *total) {
