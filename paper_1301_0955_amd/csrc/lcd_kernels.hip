@@ -3346,8 +3346,9 @@ __global__ void __launch_bounds__(256) degrees_kernel(const int32_t *row_ptr, co
 // The first directed entry that breaks a rule of the input (chk->bad: entry
 // << 3 | rule): id in range, no self-loop, rows strictly ascending, weights
 // at least 1, a reverse entry of the same weight.  Bound by the dependent
-// reads of two binary searches an entry, independent between entries: 0.1 ms
-// for 3M entries, where one host thread took 17.
+// reads of two binary searches an entry, independent between entries: 40 us
+// for 60,000 nodes, 0.75 ms for 1,000,000 of mean degree 18 (the upload of a
+// 10,000,000-node graph, checked by host threads, took 4.7 s; now 0.7).
 __global__ void __launch_bounds__(256) check_graph_kernel(const int32_t *row_ptr, const int32_t *col, const uint8_t *w,
                                                           int32_t n, int64_t nnz, GraphCheck *chk) {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
