@@ -173,14 +173,15 @@ extern "C" lcd_status lcd_sweep_into(const lcd_graph *g, const double *scales, i
     hipStream_t st = (hipStream_t)stream;
 
     // the tier chain of lcd_sweep, cut after its first global-memory tier,
-    // whose tables come from the scratch array
+    // whose tables come from the scratch array: kNaTableCap entries, whatever
+    // the plan gives that tier (more on graphs of millions of nodes)
     TierPlan full;
     CHK(plan_tiers(g->dev, g->n, n_sets, prm, full));
     TierPlan tp;
     for (int k = 0; k < full.n; ++k) {
         TierSpec T = full.t[k];
         if (T.slab >= 0) {
-            if (T.kind != TIER_TEAM_GLOBAL || T.cap > kNaTableCap)
+            if (T.kind != TIER_TEAM_GLOBAL)
                 break;
             T.cap = kNaTableCap;
             T.hbits = kNaHashBits;
