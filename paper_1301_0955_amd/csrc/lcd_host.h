@@ -124,8 +124,11 @@ struct TierPlan {
 };
 
 // Hash bits of a table indexed in LDS: at least 4/3 slots per entry (groups
-// of four slots keep the probes short at that load), two groups at least.
-inline int32_t block_hbits(int32_t cap) { return std::max(3, next_pow2_bits(((int64_t)cap * 4 + 2) / 3)); }
+// of four slots keep the probes short at that load), and a slot for every
+// claim in flight beside a full table (block_edges).
+inline int32_t block_hbits(int32_t cap) {
+    return next_pow2_bits(std::max(((int64_t)cap * 4 + 2) / 3, (int64_t)cap + kMaxClaims));
+}
 
 // Bytes between the tables of a slab, and of a table in all (a workgroup
 // table's hash lies apart, see carve_slab in the kernels).

@@ -127,6 +127,7 @@ __host__ __device__ constexpr int64_t table_bytes(int32_t cap, int32_t hbits) {
 // global memory an entry is a 32-byte record, with scratch i32[cap] beside,
 // and tables from kRecordMinEntries entries on have 32-bit indices.
 constexpr int kBlockLogs = 512;
+constexpr int kMaxClaims = 256;      // ids a workgroup brings in at once when a community starts
 constexpr int kRecordBytes = 32;
 constexpr int32_t kRecordMinEntries = 65536;
 constexpr int kBlockEntryBytes = 8 /*rank*/ + 4 /*node*/ + 4 /*d|flags*/ + 4 /*k*/ + 4 /*row start*/ + 2 /*queue*/;

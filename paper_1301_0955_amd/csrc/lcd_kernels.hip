@@ -1234,7 +1234,7 @@ struct TeamSh {
             int32_t bstart[kBuckets + 1];   // queue positions of each bucket
             uint32_t fill[kBuckets];        // bucket counts, then fill cursors
         };
-        int32_t resv[2 * kBuckets];     // (id, entry) of a claiming thread (initialisation)
+        int32_t resv[2 * kMaxClaims];   // (id, entry) of a claiming thread (initialisation)
     };
     double r2[kTeamMaxWaves];
     // the waves' candidates, two sets used in turn (a
@@ -1859,7 +1859,7 @@ __device__ __forceinline__ void match_slot(const BTab<L> &t, TeamSh &sh, uint32_
 template <int L>
 __device__ void block_edges(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
                             const int32_t *init, int32_t n_init) {
-    const int32_t lanes = min(64, kBuckets / id.nw);   // claims in flight per wave
+    const int32_t lanes = min(64, kMaxClaims / id.nw);   // claims in flight per wave
     const int32_t q1 = (int32_t)((int64_t)n_init * (id.wid + 1) / id.nw);
     int32_t q = (int32_t)((int64_t)n_init * id.wid / id.nw);   // next member of this wave
     int32_t beg = 0, incl = 0, len = 0, total = 0, at = 0;     // the block of members in hand
