@@ -963,9 +963,10 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     const int32_t n = g->n;
     if (n > 0 && !perm)
         return fail(LCD_EINVAL, "null input array");
-    *n_seeds = 0;
-    if (n == 0)
+    if (n == 0) {
+        *n_seeds = 0;
         return LCD_OK;
+    }
     const int nb = (int)(((int64_t)n + 1023) / 1024);
     // one device workspace per graph, allocated on the first call: perm,
     // pos, flag (also the round's one-hop minima), at, block sums, out
@@ -978,7 +979,11 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
     if (gw->seed_ws_bytes < ws) {
         dev_free(gw->seed_ws);
         gw->seed_ws_bytes = 0;
-        CHK(dev_alloc(&gw->seed_ws, (size_t)ws));
+        const lcd_status s = dev_alloc(&gw->seed_ws, (size_t)ws);
+        if (s != LCD_OK) {
+            *n_seeds = 0;
+            return s;
+        }
         gw->seed_ws_bytes = ws;
     }
     char *p = gw->seed_ws;
@@ -1020,11 +1025,13 @@ lcd_status lcd_seeds(const lcd_graph *g, int32_t rule, const int32_t *perm, int3
             e = hipMemcpyAsync(&h_bad, bad, sizeof(unsigned), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess)
             e = hipStreamSynchronize(st);
-        // (the rounds index nothing by an entry of perm)
+        // (the rounds index nothing by an entry of perm; a refused one leaves
+        // the caller's count as it was)
         if (e == hipSuccess && h_bad != ~0u)
             return fail(LCD_EINVAL, "perm is not a permutation of the node ids (entry %u)", h_bad);
         settled = e == hipSuccess && undecided == 0;
     }
+    *n_seeds = 0;
     int32_t total = 0;
     if (e == hipSuccess)
         e = launch_seed_collect(d_perm, stt, n, flag, at, bs, out, st);
