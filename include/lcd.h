@@ -578,7 +578,9 @@ typedef struct {
  * Create a server on the current device (the graph's device).
  *   mem_budget  device bytes the server may allocate (0 = 1 GiB); it must
  *               not exceed the free device memory (LCD_ENOMEM) and must
- *               cover the lanes, each able to hold any single query
+ *               cover the lanes, each able to hold any single query (a
+ *               budget that falls short of that by at most half is served
+ *               by fewer lanes)
  * Lanes are HIP streams; HIP spreads a process's streams over
  * GPU_MAX_HW_QUEUES hardware queues (4 unless set before the HIP runtime
  * starts).  With 8 or more the server runs one stage per table tier on six

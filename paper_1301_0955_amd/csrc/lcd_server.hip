@@ -719,7 +719,7 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
     static const int kPerTierWide[2][8] = {{0, 1, 1, 1, 1, 1, 1, 2}, {0, 1, 2, 2, 2, 2, 2, 3}};
     static const int kTwoStageLanes[4] = {0, 1, 1, 1};
     const bool wide = per_tier && hw_queues >= 10;
-    const int n_lanes = per_tier ? (wide ? 8 : 6) : 4;
+    int n_lanes = per_tier ? (wide ? 8 : 6) : 4;
     int lane_stage[kMaxLanes] = {0};
     for (int i = 0; i < n_lanes; ++i)
         lane_stage[i] = std::min(per_tier ? (wide ? kPerTierWide[S->n_stages > 3][i] : kPerTierLanes[S->n_stages > 3][i]) : kTwoStageLanes[i],
@@ -743,20 +743,39 @@ lcd_status lcd_server_create(const lcd_graph *g, int64_t mem_budget, int32_t max
                 return true;
         return false;
     };
-    int64_t need_min = n_lanes * fixed;
+    int64_t lane_min[kMaxStages] = {0}, need_min = 0, fewest = 0;
+    int count[kMaxStages] = {0};
+    for (int st = 0; st < S->n_stages; ++st) {
+        lane_min[st] = fixed;
+        for (int sl = 0; sl < 2; ++sl)
+            lane_min[st] += stage_uses(st, sl) ? tb[sl] : 0;
+        fewest += lane_min[st];
+    }
+    for (int i = 0; i < n_lanes; ++i) {
+        need_min += lane_min[lane_stage[i]];
+        count[lane_stage[i]] += 1;
+    }
+    // a budget that falls short of that, by at most half, is served by fewer
+    // lanes of the stages that have several
+    fewest = std::max(fewest, need_min / 2);
+    if (mem_budget < fewest) {
+        delete S;
+        return fail(LCD_ENOMEM, "mem_budget %lld is below the %lld bytes the lanes need on this graph",
+                    (long long)mem_budget, (long long)fewest);
+    }
+    while (need_min > mem_budget) {
+        const int st = (int)(std::max_element(count, count + S->n_stages) - count);
+        const int at = (int)(std::find(lane_stage, lane_stage + n_lanes, st) - lane_stage);
+        std::copy(lane_stage + at + 1, lane_stage + n_lanes, lane_stage + at);
+        n_lanes -= 1;
+        count[st] -= 1;
+        need_min -= lane_min[st];
+    }
     int users[2] = {0, 0};
     for (int i = 0; i < n_lanes; ++i)
         for (int sl = 0; sl < 2; ++sl)
-            if (tb[sl] && stage_uses(lane_stage[i], sl)) {
-                need_min += tb[sl];
-                users[sl] += 1;
-            }
+            users[sl] += tb[sl] && stage_uses(lane_stage[i], sl) ? 1 : 0;
     const int64_t left_all = mem_budget - need_min;
-    if (left_all < 0) {
-        delete S;
-        return fail(LCD_ENOMEM, "mem_budget %lld is below the %lld bytes the lanes need on this graph",
-                    (long long)mem_budget, (long long)need_min);
-    }
     int32_t slots[2] = {0, 0};
     {
         const int64_t half = left_all / 2;
