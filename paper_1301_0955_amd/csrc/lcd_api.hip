@@ -58,22 +58,25 @@ lcd_status device_info(DevInfo &d) {
     return LCD_OK;
 }
 
+// A slab that holds more tables than asked for is kept: launches of few and of
+// many sets, which run on workgroups of different widths, then share one.
 lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipStream_t st) {
-    const int32_t hbits = next_pow2_bits(2 * (int64_t)cap);
-    const int64_t bytes = slab_bytes(kind, cap) * slots;
-    if (sl.buf && sl.kind == kind && sl.cap == cap && sl.slots == slots && !sl.dirty)
+    const bool fits = sl.buf && sl.kind == kind && sl.cap == cap && sl.slots >= slots;
+    if (fits && !sl.dirty)
         return LCD_OK;
-    if (!(sl.buf && sl.kind == kind && sl.cap == cap && sl.slots == slots)) {
+    if (!fits) {
         dev_free(sl.buf);
-        CHK(dev_alloc(&sl.buf, (size_t)bytes));
+        CHK(dev_alloc(&sl.buf, (size_t)(slab_bytes(kind, cap) * slots)));
+        sl.kind = kind;
+        sl.stride = slab_stride(kind, cap);
+        sl.cap = cap;
+        sl.hbits = next_pow2_bits(2 * (int64_t)cap);
+        sl.slots = slots;
     }
-    sl.kind = kind;
-    sl.stride = slab_stride(kind, cap);
-    sl.cap = cap;
-    sl.hbits = hbits;
-    sl.slots = slots;
     // all-ones bytes: every hash slot empty; the rest of a table needs no init
-    HIPCHK(launch_fill_i32((int32_t *)sl.buf, -1, kind == TIER_TEAM_GLOBAL ? (int64_t)slots << hbits : bytes / 4, st));
+    HIPCHK(launch_fill_i32((int32_t *)sl.buf, -1,
+                           kind == TIER_TEAM_GLOBAL ? (int64_t)sl.slots << sl.hbits
+                                                    : slab_bytes(kind, cap) * sl.slots / 4, st));
     sl.dirty = false;
     return LCD_OK;
 }
@@ -104,18 +107,23 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
     if (p.team_waves < 0 || 64 * p.team_waves > kTeamMaxThreads)
         return fail(LCD_EINVAL, "team_waves must be in [0, %d]", kTeamMaxThreads / 64);
     // workgroups of a workgroup tier that stay resident on the whole chip
-    auto resident = [&](int32_t kind, int32_t waves, size_t lds) -> int32_t {
+    auto resident = [&](int32_t kind, int32_t c, int32_t waves, size_t lds) -> int32_t {
         int32_t nb = 0;
-        if (tier_blocks_per_cu(kind, waves, lds, &nb) != hipSuccess || nb < 1)
+        if (tier_blocks_per_cu(kind, c, waves, lds, &nb) != hipSuccess || nb < 1)
             nb = 1;
         return dev.cus * nb;
     };
     auto add_global = [&](int32_t kind, int32_t c, int32_t waves, int32_t slots, int32_t slab) {
-        const int32_t blocks = kind == TIER_TEAM_GLOBAL ? resident(kind, waves, 0) : 0;
+        const int32_t blocks = kind == TIER_TEAM_GLOBAL ? resident(kind, c, waves, 0) : 0;
         tp.t[tp.n] = TierSpec{kind, c, next_pow2_bits(2 * (int64_t)c), waves, blocks, slots, slab};
         tp.n += 1;
         have = c;
     };
+    // graphs of millions of nodes grow communities of thousands of members
+    // whose tables hold tens of thousands of entries: there the first global
+    // tier takes 131,072 entries, so that such sets run one per resident
+    // workgroup instead of waiting for the few whole-graph tables
+    const int32_t c2 = std::min<int32_t>(n >= (4 << 20) ? 131072 : 16384, capn);
     // waves per community on global tables.  A wide workgroup shortens a
     // community's chain of steps (22,990 additions alone on the 4M-node graph:
     // 264 ms with one wave, 191 with two, 156 with four), a narrow one keeps
@@ -127,10 +135,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
     // 1,912); else two.
     int32_t team_waves = p.team_waves;
     if (team_waves == 0)
-        team_waves = n_sets <= resident(TIER_TEAM_GLOBAL, 4, 0) ? 4 : n >= (4 << 20) ? 3 : 2;
-    // tables for the narrowest of them, whatever the launch, so that launches of
-    // few and of many sets share one slab
-    const int32_t team_slots = std::max(resident(TIER_TEAM_GLOBAL, 2, 0), resident(TIER_TEAM_GLOBAL, team_waves, 0));
+        team_waves = n_sets <= resident(TIER_TEAM_GLOBAL, c2, 4, 0) ? 4 : n >= (4 << 20) ? 3 : 2;
     if (p.spill_mode == 1 || p.spill_mode == 2) {
         const int32_t c1 = std::min<int32_t>(16384, capn);
         if (c1 > have && n > have)
@@ -141,7 +146,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
                 add_global(TIER_WAVE_GLOBAL, capn, 4, (int32_t)std::max<int64_t>(4, std::min<int64_t>(256, slots)), 1);
             else
                 add_global(TIER_TEAM_GLOBAL, capn, team_waves,
-                           (int32_t)std::max<int64_t>(4, std::min<int64_t>(resident(TIER_TEAM_GLOBAL, team_waves, 0), slots)), 1);
+                           (int32_t)std::max<int64_t>(4, std::min<int64_t>(resident(TIER_TEAM_GLOBAL, capn, team_waves, 0), slots)), 1);
         }
         return LCD_OK;
     }
@@ -153,25 +158,21 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
         if (cl > have && n > have) {
             const int32_t hb = block_hbits(cl), waves = p.team_waves > 0 ? p.team_waves : 2;
             tp.t[tp.n] = TierSpec{TIER_TEAM_LDS, cl, hb, waves,
-                                  resident(TIER_TEAM_LDS, waves, (size_t)block_table_bytes(cl, hb)), 0, -1};
+                                  resident(TIER_TEAM_LDS, cl, waves, (size_t)block_table_bytes(cl, hb)), 0, -1};
             tp.n += 1;
             have = cl;
         }
     }
-    // graphs of millions of nodes grow communities of thousands of members
-    // whose tables hold tens of thousands of entries: there the first global
-    // tier takes 131,072 entries, so that such sets run one per resident
-    // workgroup instead of waiting for the few whole-graph tables
-    const int32_t c2 = std::min<int32_t>(n >= (4 << 20) ? 131072 : 16384, capn);
+    // a table for every workgroup that the launch keeps resident
     if (c2 > have && n > have)
-        add_global(TIER_TEAM_GLOBAL, c2, team_waves, team_slots, 0);
+        add_global(TIER_TEAM_GLOBAL, c2, team_waves, resident(TIER_TEAM_GLOBAL, c2, team_waves, 0), 0);
     if (capn > have && n > have) {
         // the whole-graph tier gets the few largest communities, whose
         // step-by-step chain is the tier's time: the widest workgroups
         const int32_t wide = kTeamMaxThreads / 64;
         int64_t slots = ((int64_t)4 << 30) / slab_bytes(TIER_TEAM_GLOBAL, capn);
         add_global(TIER_TEAM_GLOBAL, capn, wide,
-                   (int32_t)std::max<int64_t>(4, std::min<int64_t>(resident(TIER_TEAM_GLOBAL, wide, 0), slots)), 1);
+                   (int32_t)std::max<int64_t>(4, std::min<int64_t>(resident(TIER_TEAM_GLOBAL, capn, wide, 0), slots)), 1);
     }
     return LCD_OK;
 }

@@ -152,7 +152,8 @@ inline int64_t slab_bytes(int32_t kind, int32_t cap) {
 lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp);
 
 // (Re)allocate a slab for cap entries x slots tables of a tier kind and mark
-// every hash slot empty; a clean slab of the same shape is kept as it is.
+// every hash slot empty; a clean slab of that shape with as many tables or
+// more is kept as it is.
 lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipStream_t st);
 
 // Enqueue one launch group on st: tiers first .. last-1 of tp in order, tier

@@ -163,9 +163,9 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t st);
 hipError_t launch_zero_bytes(void *p, int64_t bytes, hipStream_t st);
 hipError_t launch_sweep(const SweepArgs &a, int32_t blocks, int32_t waves_per_block,
                         hipStream_t st);
-// Resident workgroups per compute unit of a tier kernel (TIER_* kind) at the
-// given waves per workgroup and dynamic LDS bytes.
-hipError_t tier_blocks_per_cu(int32_t kind, int32_t waves, size_t lds_bytes, int32_t *out);
+// Resident workgroups per compute unit of a tier's kernel (TIER_* kind, table
+// entries) at the given waves per workgroup and dynamic LDS bytes.
+hipError_t tier_blocks_per_cu(int32_t kind, int32_t cap, int32_t waves, size_t lds_bytes, int32_t *out);
 // readout
 // comm_ptr[0..n_sets] (int32, wraps past 2^31 - 1) and the exact total in *total
 hipError_t launch_scale_scan(const Records &rec, int32_t S, int32_t s, int32_t n_sets,

@@ -4428,13 +4428,16 @@ hipError_t launch_sweep(const SweepArgs &a, int32_t blocks, int32_t waves_per_bl
     return hipGetLastError();
 }
 
-hipError_t tier_blocks_per_cu(int32_t kind, int32_t waves, size_t lds_bytes, int32_t *out) {
+hipError_t tier_blocks_per_cu(int32_t kind, int32_t cap, int32_t waves, size_t lds_bytes, int32_t *out) {
     const void *f = nullptr;
     switch (kind) {
     case TIER_WAVE_LDS: f = reinterpret_cast<const void *>(&sweep_lds_kernel); break;
     case TIER_WAVE_GLOBAL: f = reinterpret_cast<const void *>(&sweep_global_kernel); break;
     case TIER_TEAM_LDS: f = reinterpret_cast<const void *>(&sweep_team_lds_kernel); break;
-    case TIER_TEAM_GLOBAL: f = reinterpret_cast<const void *>(&sweep_team_global_kernel); break;
+    case TIER_TEAM_GLOBAL:
+        f = cap >= kRecordMinEntries ? reinterpret_cast<const void *>(&sweep_team_global_rec_kernel)
+                                     : reinterpret_cast<const void *>(&sweep_team_global_kernel);
+        break;
     default: return hipErrorInvalidValue;
     }
     int nb = 0;
