@@ -61,7 +61,7 @@ lcd_status device_info(DevInfo &d) {
 // A slab that holds more tables than asked for is kept: launches of few and of
 // many sets, which run on workgroups of different widths, then share one.
 lcd_status ensure_slab(Slab &sl, int32_t kind, int32_t cap, int32_t slots, hipStream_t st) {
-    const bool fits = sl.buf && sl.kind == kind && sl.cap == cap && sl.slots >= slots;
+    const bool fits = slab_fits(sl, kind, cap, slots);
     if (fits && !sl.dirty)
         return LCD_OK;
     if (!fits) {
@@ -277,6 +277,22 @@ lcd_status prepare_slabs(lcd_graph *g, const TierPlan &tp, hipStream_t st) {
     for (int k = 0; k < tp.n; ++k)
         if (tp.t[k].slab >= 0)
             CHK(ensure_slab(g->slab[tp.t[k].slab], tp.t[k].kind, tp.t[k].cap, tp.t[k].slots, st));
+    return LCD_OK;
+}
+
+// Bytes that prepare_slabs would still take for a sweep of n_sets sets.
+lcd_status slabs_wanted(const lcd_graph *g, int32_t n_sets, const lcd_params &prm, int64_t &bytes) {
+    TierPlan tp;
+    CHK(plan_tiers(g->dev, g->n, n_sets, prm, tp));
+    bytes = 0;
+    for (int k = 0; k < tp.n; ++k) {
+        const TierSpec &T = tp.t[k];
+        if (T.slab < 0)
+            continue;
+        const Slab &sl = g->slab[T.slab];
+        if (!slab_fits(sl, T.kind, T.cap, T.slots))
+            bytes += slab_bytes(T.kind, T.cap) * T.slots - (sl.buf ? slab_bytes(sl.kind, sl.cap) * sl.slots : 0);
+    }
     return LCD_OK;
 }
 
@@ -891,34 +907,42 @@ lcd_status lcd_sweep(const lcd_graph *g, const double *scales, int32_t n_scales,
     r->n_seed_nodes = total;
     const size_t R = (size_t)n_sets * (size_t)n_scales;
     r->n_ctl = prm.mode == LCD_PER_SCALE_LOOP ? n_scales : 1;
+    lcd_status s = LCD_OK;
     // a graph's first sweep has no size of an earlier one to go by, and a pool
     // that is too small costs a second sweep, often a third; an allocation of
     // gigabytes costs 0.6 ms
     const int64_t least = std::max<int64_t>(1 << 16, (int64_t)n_sets * (n_scales / 4 + 2) * 32);
     int64_t est = least;
-    if (g->pool_hint == 0) {
+    if (g->pool_hint == 0 && prm.pool_hint <= 0) {
         size_t free_b = 0, total_b = 0;
-        HIPCHK(hipMemGetInfo(&free_b, &total_b));
-        est = std::max(least, std::min<int64_t>((int64_t)n_sets * (n_scales / 2 + 2) * std::min(512, g->n),
-                                                (int64_t)(free_b / 64)));
+        int64_t tables = 0;
+        if ((s = slabs_wanted(g, n_sets, prm, tables)) == LCD_OK &&
+            hipMemGetInfo(&free_b, &total_b) != hipSuccess)
+            s = fail(LCD_EDEVICE, "hipMemGetInfo failed");
+        if (s != LCD_OK) {
+            result_release(r);
+            return s;
+        }
+        // a record with its place in the pool, its counters and delta counts
+        const int64_t rec = 8 + 4 + 8 + 8 + 8 + 4 * 8 + 4 + 4;
+        est = first_pool(least, n_sets, n_scales, g->n, (int64_t)free_b, tables + rec * (int64_t)R);
     }
     est = std::max(est, g->pool_hint + g->pool_hint / 16);
     if (prm.pool_hint > 0)
         est = prm.pool_hint;
-    lcd_status s = LCD_OK;
     if ((s = dev_alloc(&r->scales, (size_t)n_scales)) != LCD_OK ||
         (s = dev_alloc(&r->seed_ptr, (size_t)n_sets + 1)) != LCD_OK ||
         (s = dev_alloc(&r->seed_nodes, (size_t)total)) != LCD_OK ||
         (s = dev_alloc(&r->rec.off, R)) != LCD_OK || (s = dev_alloc(&r->rec.cnt, R)) != LCD_OK ||
         (s = dev_alloc(&r->rec.K, R)) != LCD_OK || (s = dev_alloc(&r->rec.V, R)) != LCD_OK ||
         (s = dev_alloc(&r->rec.f, R)) != LCD_OK || (s = dev_alloc(&r->rec.ctr, 4 * R)) != LCD_OK ||
-        (s = dev_alloc(&r->pool, (size_t)est)) != LCD_OK ||
         (s = dev_alloc(&r->ctl, (size_t)r->n_ctl)) != LCD_OK ||
         (s = dev_alloc(&r->cursor, kCursorWords)) != LCD_OK ||
         (s = dev_alloc(&r->work[0], 2 * (kMaxTiers - 1) * (size_t)std::max(n_sets, 1))) != LCD_OK ||
         (prm.output_mode == LCD_OUT_DELTA &&
          ((s = dev_alloc(&r->rec.dadd, std::max<size_t>(R, 1))) != LCD_OK ||
-          (s = dev_alloc(&r->rec.drem, std::max<size_t>(R, 1))) != LCD_OK))) {
+          (s = dev_alloc(&r->rec.drem, std::max<size_t>(R, 1))) != LCD_OK)) ||
+        (s = dev_alloc(&r->pool, (size_t)est)) != LCD_OK) {
         result_release(r);
         return s;
     }

@@ -142,6 +142,16 @@ inline int64_t slab_bytes(int32_t kind, int32_t cap) {
            (kind == TIER_TEAM_GLOBAL ? (int64_t)4 << next_pow2_bits(2 * (int64_t)cap) : 0);
 }
 
+// Entries of a sweep's member pool when no earlier sweep of the graph tells
+// the size: at least `least`, and room for a record of up to 512 members every
+// second scale if that is no more than a sixteenth of the bytes that are free
+// beside the others the sweep takes (its tables and records).
+inline int64_t first_pool(int64_t least, int64_t n_sets, int64_t n_scales, int64_t n, int64_t free_bytes,
+                          int64_t other_bytes) {
+    return std::max(least, std::min(n_sets * (n_scales / 2 + 2) * std::min<int64_t>(512, n),
+                                    (free_bytes - other_bytes) / 64));
+}
+
 // The tier chain for n_sets communities on a graph of n nodes: tier 0 one
 // wave per community with an LDS table (lds_capacity entries), then tiers with
 // larger tables.  spill_mode 0: workgroup tiers (LDS tables if team_capacity
@@ -150,6 +160,10 @@ inline int64_t slab_bytes(int32_t kind, int32_t cap) {
 // (16,384 entries x 4,096 tables, then every node); 2: a one-wave global
 // tier, then workgroups.
 lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_params &p, TierPlan &tp);
+
+inline bool slab_fits(const Slab &sl, int32_t kind, int32_t cap, int32_t slots) {
+    return sl.buf && sl.kind == kind && sl.cap == cap && sl.slots >= slots;
+}
 
 // (Re)allocate a slab for cap entries x slots tables of a tier kind and mark
 // every hash slot empty; a clean slab of that shape with as many tables or

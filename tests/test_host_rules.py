@@ -1,0 +1,64 @@
+"""Rules that the library's host code decides by, on the CPU: a small program
+built from its internal headers prints what they answer."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+MAIN = """
+#include <cstdio>
+#include "lcd_host.h"
+using namespace lcd;
+int main() {
+    long long a[8];
+    char what[32];
+    while (std::scanf("%31s %lld %lld %lld %lld %lld %lld", what, a, a + 1, a + 2, a + 3, a + 4, a + 5) == 7) {
+        const std::string w = what;
+        long long r = -1;
+        if (w == "first_pool")
+            r = first_pool(a[0], a[1], a[2], a[3], a[4], a[5]);
+        std::printf("%lld\\n", r);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, exe = str(d / "rules.cpp"), str(d / "rules")
+    with open(src, "w") as f:
+        f.write("#include <string>\n" + MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all",
+                    "-D__HIP_PLATFORM_AMD__", "-I", ROCM + "/include", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_1301_0955_amd", "csrc"), src, "-o", exe], check=True)
+
+    def ask(rows):
+        text = "".join("%s %s\n" % (w, " ".join(str(x) for x in (list(a) + [0] * 6)[:6])) for w, *a in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout
+        return [int(x) for x in out.split()]
+    return ask
+
+
+def test_first_pool_leaves_the_tables_their_memory(rules):
+    """A sweep that fits with the least pool fits with the one that is chosen."""
+    G = 1 << 30
+    rows, at = [], []
+    for free in (G, 2 * G, 5 * G, 14 * G, 280 * G):
+        for other in (0, free // 2, free - G // 16, free - G // 256, free, free + G):
+            for sets, scales, n in ((1, 1, 1), (20_000, 32, 100_000), (115_000, 2, 1 << 22), (14_184, 64, 10 ** 7),
+                                    (2 ** 24, 100, 2 ** 27), (0, 8, 0)):
+                least = max(1 << 16, sets * (scales // 4 + 2) * 32)
+                rows.append(("first_pool", least, sets, scales, n, free, other))
+                at.append((least, free, other))
+    for (least, free, other), r in zip(at, rules(rows)):
+        assert r >= least
+        if r > least:
+            assert 4 * r <= (free - other) // 16
+
+
+def test_first_pool_has_room_for_a_record_every_second_scale(rules):
+    assert rules([("first_pool", 1 << 16, 4000, 8, 60_013, 280 << 30, 6 << 30)]) == [4000 * 6 * 512]
