@@ -59,6 +59,15 @@ struct Counters {
     uint32_t ovf_count[kMaxTiers];    // per tier: items pushed to the next tier
 };
 
+// Whether entry `off` of the row at beg can be read before the row's end is
+// known: a row holds at most k entries (its weighted degree) and ends within
+// the nnz there are.  Row starts reach 2^31 - 1, so beg + off is summed in 64
+// bits here; loops over lists step an offset from the list's start, for the
+// same reason.
+__host__ __device__ constexpr bool row_ahead(int32_t beg, int32_t off, int32_t k, int64_t nnz) {
+    return off < k && (int64_t)beg + off < nnz;
+}
+
 struct SweepArgs {
     GraphDev g;
     const double *scales;

@@ -347,17 +347,16 @@ enum { ROW_INIT = 0, ROW_ADD = 1, ROW_REMOVE = 2 };
 template <bool GLOBAL, int MODE>
 __device__ void row_update(const Tab &t, St &st, const Ctx &c, int32_t n, int lane) {
     const int32_t beg = c.row_ptr[n];
-    const int32_t end = c.row_ptr[n + 1];
+    const int32_t len = c.row_ptr[n + 1] - beg;
     st.rows += 1;
-    st.row_len += (uint64_t)(end - beg);
+    st.row_len += (uint64_t)len;
     if constexpr (MODE != ROW_INIT) {
         st.mrows += 1;
-        st.mrow_len += (uint64_t)(end - beg);
+        st.mrow_len += (uint64_t)len;
     }
-    for (int32_t base = beg; base < end; base += 64) {
-        const int32_t j = base + lane;
-        const bool act = j < end;
-        const Edge x = act ? edge_at(c, j) : no_edge();
+    for (int32_t base = 0; base < len; base += 64) {
+        const bool act = base + lane < len;
+        const Edge x = act ? edge_at(c, beg + base + lane) : no_edge();
         const int32_t u = x.e.x, wt = x.e.w;
         int32_t idx;
         if constexpr (MODE == ROW_REMOVE) {
@@ -1715,25 +1714,23 @@ __device__ int32_t team_ensure(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &
 
 // Apply the row of node n (row start beg, degree k) as team_row does on the
 // bucketed queue.  The first entries are loaded before the row's end is
-// known: a row holds at most k entries and stays below nnz.
+// known (row_ahead).
 template <int MODE, int L>
 __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
                                           int32_t n, int32_t beg, int32_t k) {
-    int32_t j = beg + id.tid;
-    Edge x = id.tid < k && (int64_t)j < c.nnz ? edge_at(c, j) : no_edge();
-    const int32_t end = __builtin_amdgcn_readfirstlane(c.row_ptr[n + 1]);
-    const bool solo = end - beg <= 64;   // the row is wave 0's alone
+    Edge x = row_ahead(beg, id.tid, k, c.nnz) ? edge_at(c, beg + id.tid) : no_edge();
+    const int32_t len = __builtin_amdgcn_readfirstlane(c.row_ptr[n + 1]) - beg;
+    const bool solo = len <= 64;   // the row is wave 0's alone
     st.rows += 1;
-    st.row_len += (uint64_t)(end - beg);
+    st.row_len += (uint64_t)len;
     st.mrows += 1;
-    st.mrow_len += (uint64_t)(end - beg);
-    for (int32_t base = beg; base < end; base += id.nt) {
-        if (base + id.wid * 64 >= end)
+    st.mrow_len += (uint64_t)len;
+    for (int32_t base = 0; base < len; base += id.nt) {
+        if (base + id.wid * 64 >= len)
             break;
-        j = base + id.tid;
-        const bool act = j < end;
-        if (base > beg)
-            x = act ? edge_at(c, j) : no_edge();
+        const bool act = base + id.tid < len;
+        if (base > 0)
+            x = act ? edge_at(c, beg + base + id.tid) : no_edge();
         const int4 e = x.e;
         int32_t idx = -1;
         uint32_t slot = kNoSlot;
@@ -2594,7 +2591,7 @@ __device__ __forceinline__ bool lq_step(const BTab<L> &t, TeamSh &sh, St &st, co
             if (last)
                 return false;
             at = end;
-            win *= 8;
+            win = min(win, 1 << 26) * 8;   // (at + win stays below 2^31)
             nf = 0;
             continue;
         }
@@ -3397,8 +3394,7 @@ __global__ void __launch_bounds__(256) check_graph_kernel(const int32_t *row_ptr
 }
 
 __global__ void node_info_kernel(const int32_t *row_ptr, const int32_t *kdeg, int2 *info, int32_t n) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u < n)
+    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (int64_t)gridDim.x * blockDim.x)
         info[u] = make_int2(row_ptr[u], kdeg[u]);
 }
 
@@ -3742,12 +3738,12 @@ __global__ void seed_min1_kernel(const int32_t *row_ptr, const int32_t *col, con
         if (m != INT32_MAX)
             cnt += 1;
         // four neighbours at a time: their reads are in flight together
-        const int32_t end = row_ptr[v + 1];
-        for (int32_t j = row_ptr[v]; j < end; j += 4) {
+        const int32_t beg = row_ptr[v], len = row_ptr[v + 1] - beg;
+        for (int32_t j = 0; j < len; j += 4) {
             int32_t u[4], x[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                u[q] = col[min(j + q, end - 1)];
+                u[q] = col[beg + min(j + q, len - 1)];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 x[q] = key[u[q]];
@@ -3907,19 +3903,21 @@ __global__ void __launch_bounds__(256) partner_kernel(const int32_t *comm_ptr, c
         if (item >= (unsigned)n_list)
             break;
         const int32_t c = list[item];
-        const int32_t c0 = comm_ptr[c], c1 = comm_ptr[c + 1];
-        const int64_t sc = c1 - c0;
+        const int32_t nm = comm_ptr[c + 1] - comm_ptr[c];
+        const int32_t *mem = members + comm_ptr[c];
+        const int64_t sc = nm;
         int32_t found = -1;
         // counts of the incidences of the members [q, q + 64 / per), per lanes
         // to a member's list; by: +1 (true when some community reaches its
         // threshold) or -1 (undone)
         const auto visit = [&](int32_t q, int32_t end, int per, int by) -> bool {
             const int32_t at = q + lane / per;
-            const int32_t v = at < end ? members[at] : -1;
-            const int32_t t1 = v >= 0 ? node_ptr[v + 1] : 0;
+            const int32_t v = at < end ? mem[at] : -1;
+            const int32_t t0 = v >= 0 ? node_ptr[v] : 0;
+            const int32_t len = v >= 0 ? node_ptr[v + 1] - t0 : 0;
             bool hit = false;
-            for (int32_t t = v >= 0 ? node_ptr[v] + lane % per : 0; t < t1; t += per) {
-                const int32_t i = node_sets[t];
+            for (int32_t t = lane % per; t < len; t += per) {
+                const int32_t i = node_sets[t0 + t];
                 if (i == c)
                     continue;
                 const int64_t x = (int64_t)atomicAdd(&cnt[i], by) + by;
@@ -3932,9 +3930,9 @@ __global__ void __launch_bounds__(256) partner_kernel(const int32_t *comm_ptr, c
             __builtin_amdgcn_wave_barrier();
             return __ballot(hit) != 0;
         };
-        int32_t done = c0;   // members before done have been counted
-        for (int32_t q = c0; q < c1 && found < 0; q += 64) {
-            done = min(q + 64, c1);
+        int32_t done = 0;   // members before done have been counted
+        for (int32_t q = 0; q < nm && found < 0; q += 64) {
+            done = min(q + 64, nm);
             if (!visit(q, done, 1, 1))
                 continue;
             visit(q, done, 1, -1);
@@ -3944,11 +3942,10 @@ __global__ void __launch_bounds__(256) partner_kernel(const int32_t *comm_ptr, c
                     continue;
                 visit(s, s1, 8, -1);
                 for (int32_t r = s; r < s1 && found < 0; ++r) {
-                    const int32_t v = members[r];
-                    const int32_t t1 = node_ptr[v + 1];
-                    for (int32_t t0 = node_ptr[v]; t0 < t1 && found < 0; t0 += 64) {
-                        const int32_t t = t0 + lane;
-                        const int32_t i = t < t1 ? node_sets[t] : -1;
+                    const int32_t v = mem[r];
+                    const int32_t t0 = node_ptr[v], len = node_ptr[v + 1] - t0;
+                    for (int32_t t = 0; t < len && found < 0; t += 64) {
+                        const int32_t i = t + lane < len ? node_sets[t0 + t + lane] : -1;
                         bool hit = false;
                         if (i >= 0 && i != c) {
                             const int64_t x = (int64_t)atomicAdd(&cnt[i], 1) + 1;
@@ -3964,8 +3961,8 @@ __global__ void __launch_bounds__(256) partner_kernel(const int32_t *comm_ptr, c
             }
         }
         // leave the counts at zero for the next community
-        for (int32_t q = c0 + lane; q < done; q += 64) {
-            const int32_t v = members[q];
+        for (int32_t q = lane; q < done; q += 64) {
+            const int32_t v = mem[q];
             for (int32_t t = node_ptr[v]; t < node_ptr[v + 1]; ++t) {
                 const int32_t i = node_sets[t];
                 if (i != c)
@@ -4073,8 +4070,9 @@ __global__ void __launch_bounds__(256) overlap_scatter_kernel(const int32_t *com
     const int64_t j = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
     if (j >= n_sets)
         return;
-    for (int32_t i = comm_ptr[j] + lane; i < comm_ptr[j + 1]; i += 64) {
-        const int32_t u = members[i];
+    const int32_t beg = comm_ptr[j], len = comm_ptr[j + 1] - beg;
+    for (int32_t i = lane; i < len; i += 64) {
+        const int32_t u = members[beg + i];
         const int32_t pos = atomicAdd(&fill[u], 1);
         node_sets[node_ptr[u] + pos] = (int32_t)j;
     }
@@ -4194,8 +4192,8 @@ __global__ void __launch_bounds__(256) nmi_half_kernel(const int32_t *px, const 
         const int32_t sx = x1 - x0;
         double out = -1.0;
         if (sx > 0) {
-            for (int32_t q = x0 + lane; q < x1; q += 64) {
-                const int32_t v = mx[q];
+            for (int32_t q = lane; q < sx; q += 64) {
+                const int32_t v = mx[x0 + q];
                 for (int32_t t = node_ptr[v]; t < node_ptr[v + 1]; ++t)
                     atomicAdd(&cnt[node_sets[t]], 1);
             }
@@ -4287,9 +4285,9 @@ __global__ void __launch_bounds__(256) cover_check_kernel(const int32_t *ptr, co
             breach = true;
             continue;
         }
-        for (int32_t q = a + lane; q < b; q += 64) {
-            const int32_t v = mem[q];
-            breach = breach || v < 0 || v >= n || (q > a && v <= mem[q - 1]);
+        for (int32_t q = lane; q < b - a; q += 64) {
+            const int32_t v = mem[a + q];
+            breach = breach || v < 0 || v >= n || (q > 0 && v <= mem[a + q - 1]);
         }
     }
     if (breach)

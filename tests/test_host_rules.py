@@ -20,6 +20,8 @@ int main() {
         long long r = -1;
         if (w == "first_pool")
             r = first_pool(a[0], a[1], a[2], a[3], a[4], a[5]);
+        else if (w == "row_ahead")
+            r = row_ahead((int32_t)a[0], (int32_t)a[1], (int32_t)a[2], a[3]);
         std::printf("%lld\\n", r);
     }
 }
@@ -62,3 +64,12 @@ def test_first_pool_leaves_the_tables_their_memory(rules):
 
 def test_first_pool_has_room_for_a_record_every_second_scale(rules):
     assert rules([("first_pool", 1 << 16, 4000, 8, 60_013, 280 << 30, 6 << 30)]) == [4000 * 6 * 512]
+
+
+def test_reading_ahead_ends_with_the_entries(rules):
+    """Offsets of a row that starts close to the largest index a graph can have."""
+    M = 2 ** 31 - 1
+    rows = [("row_ahead", beg, off, k, nnz) for nnz in (M, M - 600, 1000) for beg in (nnz - 600, nnz - 64, nnz - 9, nnz)
+            for off in (0, 8, 9, 63, 64, 511) for k in (0, 9, 2000) if beg >= 0]
+    for (_, beg, off, k, nnz), r in zip(rows, rules(rows)):
+        assert r == (off < k and beg + off < nnz), (beg, off, k, nnz)
