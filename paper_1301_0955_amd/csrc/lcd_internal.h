@@ -149,6 +149,16 @@ __host__ __device__ constexpr int64_t block_table_bytes(int32_t cap, int32_t hbi
     return (int64_t)kBlockLogs * 8 + ((int64_t)1 << hbits) * 4 + (int64_t)cap * kBlockEntryBytes + kFreshMax * 2;
 }
 
+// Entries that a workgroup table's hash slots can name: a slot is a tag over
+// an index field whose top bit marks a claim, 15 bits for the index below
+// kRecordMinEntries and as many as the table needs from there on.
+constexpr int32_t kPackMaxEntries = 1 << 15;
+constexpr int32_t kWideMaxEntries = 1 << 30;
+
+__host__ __device__ constexpr bool team_table_holds(int32_t cap) {
+    return cap > 0 && cap <= (cap >= kRecordMinEntries ? kWideMaxEntries : kPackMaxEntries);
+}
+
 // One workgroup table in global memory, without its hash (4 << hbits bytes).
 __host__ __device__ constexpr int64_t team_table_bytes(int32_t cap) {
     return ((int64_t)cap * (kRecordBytes + 4) +

@@ -4405,14 +4405,15 @@ hipError_t launch_sweep(const SweepArgs &a, int32_t blocks, int32_t waves_per_bl
         hipLaunchKernelGGL(q ? query_global_kernel : sweep_global_kernel, grid, block, 0, st, a);
         break;
     case TIER_TEAM_LDS: {
-        if (waves_per_block < 1 || 64 * waves_per_block > kTeamMaxThreads)
+        if (waves_per_block < 1 || 64 * waves_per_block > kTeamMaxThreads || a.cap > kPackMaxEntries)
             return hipErrorInvalidValue;
         const size_t smem = (size_t)block_table_bytes(a.cap, a.hbits);
         hipLaunchKernelGGL(q ? query_team_lds_kernel : sweep_team_lds_kernel, grid, block, smem, st, a);
         break;
     }
     case TIER_TEAM_GLOBAL:
-        if (waves_per_block < 1 || 64 * waves_per_block > kTeamMaxThreads || a.gtab == nullptr)
+        if (waves_per_block < 1 || 64 * waves_per_block > kTeamMaxThreads || a.gtab == nullptr ||
+            !team_table_holds(a.cap))
             return hipErrorInvalidValue;
         if (a.cap >= kRecordMinEntries)
             hipLaunchKernelGGL(q ? query_team_global_rec_kernel : sweep_team_global_rec_kernel, grid, block, 0, st,

@@ -22,6 +22,8 @@ int main() {
             r = first_pool(a[0], a[1], a[2], a[3], a[4], a[5]);
         else if (w == "row_ahead")
             r = row_ahead((int32_t)a[0], (int32_t)a[1], (int32_t)a[2], a[3]);
+        else if (w == "holds")
+            r = team_table_holds((int32_t)a[0]);
         std::printf("%lld\\n", r);
     }
 }
@@ -73,3 +75,10 @@ def test_reading_ahead_ends_with_the_entries(rules):
             for off in (0, 8, 9, 63, 64, 511) for k in (0, 9, 2000) if beg >= 0]
     for (_, beg, off, k, nnz), r in zip(rows, rules(rows)):
         assert r == (off < k and beg + off < nnz), (beg, off, k, nnz)
+
+
+def test_table_sizes_that_hash_slots_cannot_name_are_refused(rules):
+    """16-bit index fields keep one bit for claims: no table between 32,768 entries and the wide ones."""
+    caps = {1: 1, 16384: 1, 32768: 1, 32769: 0, 49152: 0, 65535: 0, 65536: 1, 131072: 1, 2 ** 30: 1, 2 ** 30 + 1: 0,
+            0: 0, -2 ** 31: 0}
+    assert rules([("holds", c) for c in caps]) == list(caps.values())
