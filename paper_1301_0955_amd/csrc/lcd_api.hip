@@ -152,8 +152,7 @@ lcd_status plan_tiers(const DevInfo &dev, int32_t n, int32_t n_sets, const lcd_p
     }
     if (p.team_capacity > 0) {
         const int32_t cl = p.team_capacity;
-        if (cl % 64 != 0 || cl > 8192 ||
-            table_bytes(cl, next_pow2_bits(2 * (int64_t)cl)) + 1024 > dev.lds_block)
+        if (!team_lds_fits(cl, dev.lds_block))
             return fail(LCD_EINVAL, "team_capacity must be a multiple of 64 whose table fits one workgroup's LDS");
         if (cl > have && n > have) {
             const int32_t hb = block_hbits(cl), waves = p.team_waves > 0 ? p.team_waves : 2;

@@ -130,6 +130,14 @@ inline int32_t block_hbits(int32_t cap) {
     return next_pow2_bits(std::max(((int64_t)cap * 4 + 2) / 3, (int64_t)cap + kMaxClaims));
 }
 
+// Whether a workgroup tier may have LDS tables of cap entries: what the tier
+// launches fits a workgroup's LDS, and so does the one-wave layout of that
+// size, by which the largest accepted capacity is stated (4,096 in 160 KiB).
+inline bool team_lds_fits(int32_t cap, int64_t lds_block) {
+    return cap % 64 == 0 && cap <= 8192 && block_table_bytes(cap, block_hbits(cap)) + kTeamShBytes <= lds_block &&
+           table_bytes(cap, next_pow2_bits(2 * (int64_t)cap)) + 1024 <= lds_block;
+}
+
 // Bytes between the tables of a slab, and of a table in all (a workgroup
 // table's hash lies apart, see carve_slab in the kernels).
 inline int64_t slab_stride(int32_t kind, int32_t cap) {

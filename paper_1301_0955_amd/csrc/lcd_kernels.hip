@@ -1247,7 +1247,7 @@ struct TeamSh {
     int32_t done;     // waves whose rows are finished (initialisation)
     int32_t moved[kMovedMax];   // entries added at the scale being grown, see emit_moved
 };
-static_assert(sizeof(TeamSh) <= kTeamShBytes, "the tier sizes count the workgroup's own LDS");
+static_assert(sizeof(TeamSh) <= kTeamShBytes, "team_lds_fits counts the workgroup's own LDS");
 
 struct TeamId {
     int tid, nt, lane, wid, nw;

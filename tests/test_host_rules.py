@@ -22,6 +22,10 @@ int main() {
             r = first_pool(a[0], a[1], a[2], a[3], a[4], a[5]);
         else if (w == "row_ahead")
             r = row_ahead((int32_t)a[0], (int32_t)a[1], (int32_t)a[2], a[3]);
+        else if (w == "lds_fits")
+            r = team_lds_fits((int32_t)a[0], a[1]);
+        else if (w == "lds_bytes")
+            r = block_table_bytes((int32_t)a[0], block_hbits((int32_t)a[0])) + kTeamShBytes;
         else if (w == "holds")
             r = team_table_holds((int32_t)a[0]);
         std::printf("%lld\\n", r);
@@ -82,3 +86,14 @@ def test_table_sizes_that_hash_slots_cannot_name_are_refused(rules):
     caps = {1: 1, 16384: 1, 32768: 1, 32769: 0, 49152: 0, 65535: 0, 65536: 1, 131072: 1, 2 ** 30: 1, 2 ** 30 + 1: 0,
             0: 0, -2 ** 31: 0}
     assert rules([("holds", c) for c in caps]) == list(caps.values())
+
+
+def test_lds_tables_fit_what_is_launched(rules):
+    """Every accepted capacity fits with the layout that runs; in 160 KiB the accepted ones end at 4,096."""
+    caps = list(range(64, 8256, 64))
+    for lds in (64 << 10, 160 << 10):
+        ok = rules([("lds_fits", c, lds) for c in caps])
+        size = rules([("lds_bytes", c) for c in caps])
+        assert all(b <= lds for a, b in zip(ok, size) if a) and any(ok) and not all(ok)
+    assert [c for c, a in zip(caps, ok) if a] == list(range(64, 4160, 64))
+    assert rules([("lds_fits", 100, 160 << 10), ("lds_fits", 8256, 1 << 30)]) == [0, 0]
