@@ -583,10 +583,16 @@ lcd_status bad_edge(int rule, int32_t u, int32_t v) {
     }
 }
 
+lcd_status bad_degree(int64_t k) {
+    return fail(LCD_EINVAL, "weighted degree %lld exceeds 2^27", (long long)k);
+}
+
 // The rules of check_graph_kernel on host arrays, for a graph that no device
 // can take: a malformed one is reported as such all the same.
 lcd_status check_graph_host(int32_t n, const int32_t *rp, const int32_t *cl, const uint8_t *w) {
-    for (int32_t u = 0; u < n; ++u)
+    int64_t maxk = 0;
+    for (int32_t u = 0; u < n; ++u) {
+        int64_t k = 0;
         for (int32_t j = rp[u]; j < rp[u + 1]; ++j) {
             const int32_t v = cl[j];
             int rule = v < 0 || v >= n ? 1 : v == u ? 2 : j > rp[u] && cl[j - 1] >= v ? 3 : w && w[j] < 1 ? 4 : 0;
@@ -596,8 +602,11 @@ lcd_status check_graph_host(int32_t n, const int32_t *rp, const int32_t *cl, con
             }
             if (rule)
                 return bad_edge(rule, u, v);
+            k += w ? w[j] : 1;
         }
-    return LCD_OK;
+        maxk = std::max(maxk, k);
+    }
+    return maxk >= ((int64_t)1 << 27) ? bad_degree(maxk) : LCD_OK;
 }
 
 // Make a CSR resident and validate it there (the body of lcd_graph_upload).
@@ -675,7 +684,7 @@ lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t 
         return bail(bad_edge((int)(chk.bad & 7), u, v));
     }
     if (chk.maxk >= (1ull << 27))
-        return bail(fail(LCD_EINVAL, "weighted degree %lld exceeds 2^27", (long long)chk.maxk));
+        return bail(bad_degree((int64_t)chk.maxk));
     g->maxk = (int64_t)chk.maxk;
     g->volume = (int64_t)chk.volume;
     g->logtab_n = (int32_t)(2 * g->maxk + 2);
