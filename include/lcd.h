@@ -95,7 +95,9 @@ typedef struct {
     int32_t use_graph;       /* 1 (persistent mode): capture the sweep's launch sequence
                                 (fill kernels and every tier) in a hipGraph, launch
                                 it, and replay it on lcd_result_rerun() */
-    int64_t pool_hint;       /* initial member-pool size in entries; 0 = estimate */
+    int64_t pool_hint;       /* initial member-pool size in entries; 0 = estimate (from
+                                the graph's earlier sweeps; for its first one up to a
+                                sixteenth of the free memory, held by the result) */
     int32_t watchdog_ms;     /* wall-clock budget of one seed set; past it the sweep
                                 stops with LCD_EDEVICE.  0 = default (20000);
                                 negative = no budget at all (tests the error path) */
@@ -185,10 +187,13 @@ void lcd_params_default(lcd_params *p);
  *            self-loops; symmetric (v in row u <=> u in row v)
  *   w        uint8[nnz] weights >= 1, equal on both directions, or NULL for
  *            all weights 1
- * Validation (host side, before any device work) returns LCD_EINVAL when
- * any rule above is broken, or the weighted degree exceeds 2^27.
- * Blocking.  Derived data built on the device: weighted degrees and the
- * table L(x) for x <= 2 * max weighted degree.
+ * Validation (on the device; on the host for host arrays that no device
+ * takes) returns LCD_EINVAL when any rule above is broken, naming the first
+ * entry that does, or when a weighted degree exceeds 2^27.
+ * Blocking.  Derived data built on the device: weighted degrees, the table
+ * L(x) for x <= 2 * max weighted degree, 8 bytes per node, and adjacency
+ * records of 24 bytes per directed entry unless they would take more than an
+ * eighth of the free memory.
  */
 lcd_status lcd_graph_upload(int32_t n, int64_t nnz, const int32_t *row_ptr,
                             const int32_t *col, const uint8_t *w, int32_t mem_kind,

@@ -396,7 +396,6 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
     r->stats.grid_blocks = tp.t[0].blocks;
     r->stats.tiers = tp.n;
     for (int k = 0; k < tp.n; ++k) {
-        // tiers that share a slot report the largest one's capacity
         r->stats.tier_kind[k] = tp.t[k].kind;
         r->stats.tier_capacity[k] = tp.t[k].cap;
     }
@@ -458,7 +457,7 @@ lcd_status run_sweep(lcd_result *r, hipStream_t st) {
             for (int k = 0; k < tp.n; ++k) {
                 float x = 0.f;
                 HIPCHK(hipEventElapsedTime(&x, ev[k], ev[k + 1]));
-                r->stats.ms_tier[k] += x;
+                r->stats.ms_tier[k] = x;
             }
         }
         const uint32_t err = (uint32_t)(cur[1] & 0xffffffffu);
@@ -690,9 +689,9 @@ lcd_status build_graph(int32_t n, int64_t nnz, const int32_t *rp, const int32_t 
     g->logtab_n = (int32_t)(2 * g->maxk + 2);
     if ((s = dev_alloc(&g->logtab, (size_t)g->logtab_n)) != LCD_OK)
         return bail(s);
-    // the adjacency records (24 bytes per directed entry) shorten a step on
-    // LDS tables; a graph that would give them more than an eighth of the
-    // free memory goes without
+    // the adjacency records (24 bytes per directed entry) make a row one
+    // dependent read instead of four; a graph that would give them more than
+    // an eighth of the free memory goes without
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && (uint64_t)nnz * 24 <= free_b / 8 &&
         (dev_alloc(&g->adj, (size_t)nnz) != LCD_OK || dev_alloc(&g->adjl, (size_t)nnz) != LCD_OK)) {

@@ -185,7 +185,7 @@ struct St {
     uint64_t ins_mark, c_ins;       // entries created: not counted before ins_mark;
                                     // committed count at the last record written
     uint64_t srows, srow_len;       // seed-set rows of a set in its first tier
-    double qtop, qscale;            // compact LDS tables: rank range of the queue's buckets
+    double qtop, qscale;            // workgroup tables: rank range of the queue's buckets
     double qhi, qlo, qalpha;        // the ranks' range at the last build, and its scale
     int32_t flen;                   // ... entries on the fresh list
     int32_t nadd, nrem;             // ... additions and removals at the scale being grown
@@ -1691,8 +1691,10 @@ __device__ __forceinline__ void block_added(const BTab<L> &t, St &st, bool need,
     lds_order();
 }
 
-// Entries of distinct ids, absent ones created; a barrier at the end (see
-// the Tab version).
+// The entry of u for every active thread (all ids of a call distinct), absent
+// ones created; -1 for inactive threads and for ids that no longer fit
+// (sh.row.ovf is then set).  Every thread of the workgroup calls it; a barrier
+// at the end.
 template <int L>
 __device__ int32_t team_ensure(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id, bool act,
                                int32_t u) {
@@ -1712,9 +1714,17 @@ __device__ int32_t team_ensure(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &
     return idx;
 }
 
-// Apply the row of node n (row start beg, degree k) as team_row does on the
-// bucketed queue.  The first entries are loaded before the row's end is
-// known (row_ahead).
+// Apply the row of node n (row start beg, degree k) to the table.
+// ROW_REMOVE: every neighbour's d falls by the edge's weight.  ROW_ADD: it
+// rises by it, absent neighbours are created, and every non-member neighbour
+// is (re)queued with its new rank: flagged kLive | kFresh | kTouch and put on
+// the fresh list unless it is there already.  It counts as a pop to come
+// (st.Gl) when it was not queued: a queue entry whose kLive was taken by a
+// step, or a fresh one that ranks above the node just added, whose pop is
+// still pending.  Entries past the fresh list's end carry place FM.
+// The first entries are loaded before the row's end is known (row_ahead).
+// Every thread calls it; a barrier at the end, after which all hold the same
+// count, flen, ovf and err.
 template <int MODE, int L>
 __device__ __forceinline__ void block_row(const BTab<L> &t, TeamSh &sh, St &st, const Ctx &c, const TeamId &id,
                                           int32_t n, int32_t beg, int32_t k) {
@@ -2424,8 +2434,10 @@ __device__ __forceinline__ int32_t fresh_limit(int32_t count) {
 // entry of the fresh list and of windows of whole buckets from the queue's
 // head.  It is the queue's first improving entry once its bucket lies before
 // the window's end (every entry outside ranks strictly below it); until then
-// the window holds no improving entry and is popped whole.  Pops as in
-// bq_step: at once in the queue, by the next scan in the fresh list.
+// the window holds no improving entry and is popped whole.  What ranks above
+// the addition is popped (kLive cleared): queue entries at once, fresh ones by
+// the next scan of the list, which drops an entry above the last addition
+// (st.pr, st.pu) unless that addition's row re-ranked it (kTouch).
 // Both lists are read as one, two entries per thread at a time and without
 // branches up to the choice, so that the reads and the chains of dependent
 // operations of the two overlap.
